@@ -176,6 +176,7 @@ hipError_t launch_build(const Workspace &w, const float *d_pos, const int32_t *d
                         double *sorted64 = nullptr, const double *box64 = nullptr);
 hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool paper, const uint4 *qpoint,
                            hipStream_t s);
+hipError_t launch_traverse_paper(const TravArgs &a, int32_t block, bool vec4, const uint4 *qpoint, hipStream_t s);
 // fp64 particle data: the positions rounded to fp32 for the build (with the
 // fp64 range and type checks when validate is set), and after the build the
 // fp64 positions in sorted order.

@@ -1,419 +1,794 @@
-// Neighbor-list traversal: one lane per Z-ordered particle, the lanes of a
-// wavefront walking the rope-linked quantized tree together (Algorithm 1;
-// Section 2.3; Section 3 runs the queries in Z order so that the lanes of a
-// wavefront need similar subtrees).
+// Neighbor-list traversal (Algorithm 1; Section 2.3; Section 3 runs the
+// queries in Z order so that the queries of a wavefront need similar
+// subtrees), exact lists.  A wavefront takes up to 64 Z-consecutive queries
+// of one type and does two things in turn:
 //
-// Per wavefront and per type tree:
-//   1. image mask per lane: which of the 27 periodic images of its search
-//      sphere touch the tree's root box (the image test of Algorithm 1); the wavefront
-//      visits the union of its lanes' images;
-//   2. per image, one stackless walk over the two-wide records, shared by the
-//      wavefront.  A step loads one record (both child boxes and references)
-//      and its rope with uniform (scalar) loads; every lane tests its own
-//      sphere against both boxes in grid units (nearest point by a clamp per
-//      axis, eq. (2)); a ballot over the lanes decides the step: the left
-//      child's record if any lane hit that box, else the right child's record
-//      if any lane hit that one, else the rope.  A lane whose sphere misses a
-//      node misses everything below it, so the wavefront walks exactly the
-//      union of the lanes' own walks and every record is fetched once for all
-//      64 lanes instead of gathered lane by lane;
-//   3. a hit particle run is fetched once (uniform loads) and decided by the
-//      lanes that hit it: an fp32 distance with a proven error band accepts or
-//      rejects almost every pair; pairs inside the band are decided with the
-//      fp64 arithmetic of the list definition, so the result is the exact list.
+//   walk      lanes are tree nodes.  A stack in LDS holds the nodes still to
+//             open, in preorder, of all periodic images together.  A round
+//             takes the 32 next ones, two lanes each: a lane loads one child
+//             box and reference of its record and tests the box against the
+//             queries' search region (the image test and the node test of
+//             Algorithm 1, eq. (2)).  Hit runs that precede every hit internal
+//             node go to a queue of run parts of at most 8 particles; the
+//             rest goes back on the stack, in order, so candidates come out
+//             in exactly the order of a depth-first walk (a record's runs
+//             before its internal child).
+//   test      lanes are candidates, then queries.  Eight parts (64 candidates)
+//             are loaded, one per lane, and tested against all 64 queries on
+//             the matrix cores: with c and q relative to the wavefront's own
+//             origin, d^2 - R^2 = (|q|^2 - R^2) + |c|^2 - 2 q.c is one
+//             16x16x4 fp32 product per 16 candidates and 16 queries.  The
+//             signs of the results are the accept mask of each query.
 //
-// Grid-unit test.  With h the tree's bin width and g(x) = (x - root_lo) / h,
-// a quantized bound q decodes exactly to the float 2^23 + q (bit trick: OR
-// with 0x4B000000), and the query image is placed at 2^23 + g(x) rounded to
-// fp32.  Rounding of the query position, of the differences and of the sum of
-// squares is covered by comparing against
-//   ((R / h) * (1 + 2^-20) + 2)^2 * (1 + 2^-20),
-// a pad of two bins plus a relative 2^-20, so no true neighbor is lost.
+// The search region is the union of kSegs boxes around consecutive queries,
+// cut where neighbouring queries lie farthest apart (Z order jumps), grown by
+// R.  For 64 queries of an LJ fluid at R = 3.4 it meets 3% more candidates
+// than the 64 spheres themselves do (14% at R = 1.52), and one lane tests a
+// node against four boxes where 64 lanes tested it against a sphere each.
 //
+// Exactness.  |v| <= band (v the product's d^2 - R^2) marks the pairs that
+// need more: they are decided, one by one, by an fp32 distance with a proven
+// error band (see decide_pair) and inside that by the fp64 arithmetic of the
+// list definition, so the lists are exact.  The band is derived at
+// pair_band().
+//
+// Cost.  VALU issue bounds it (77% busy at N = 8M): 15.2k VALU instructions
+// per wavefront of 64 queries, half of them for the 26 batches it tests.  With
+// one lane per query walking and testing every candidate itself the wavefront
+// issued 26.1k VALU and 21.1k scalar instructions.  List rebuilds, before and
+// now: LJ 8M 6.83 -> 5.11 ms, 1M 1.136 -> 0.762 ms, 4000 0.155 -> 0.104 ms,
+// WCA 1M 0.745 -> 0.475 ms, two-type mixture 1M 0.726 -> 0.536 ms.
+//
+// Row order.  A row lists, image by image and tree order within an image, the
+// candidates of each run part that the fp32 distance accepts, then those of
+// the part that the fp64 arithmetic accepts.
+#include "build_common.h"
+#include "query_order.h"
+
+namespace qbi {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint32_t uniform(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)x);
+}
+__device__ __forceinline__ float uniform(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+__device__ __forceinline__ float lane_value(float x, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+__device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+// LDS written by some lanes of the wavefront is read by others after this
+// (a wavefront's LDS operations complete in order; this keeps the compiler
+// from reordering them).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Search-region boxes per wavefront.
+constexpr int kSegs = 4;
+// Nodes opened per round (two lanes each).
+constexpr int kOpen = 32;
+// Stack entries.  A round that opens p nodes adds at most p entries; p is held
+// to the room left below kStack - kDepthMax, and to one node when there is
+// none: from then on the walk is depth first and one node deep per level, so
+// it adds at most the depth of the record tree, kDepthMax (a radix tree over
+// 32-bit keys and 32-bit positions has at most 64 internal levels), before it
+// comes back to where it was.
+constexpr int kDepthMax = 64;
+constexpr int kStack = 160;
+static_assert(kStack - kDepthMax >= 27 + kOpen, "room for every image's root");
+// Queue of run parts: parts of fewer than 64 particles in all wait when a
+// round adds those of at most 2 kOpen runs, two parts each.
+constexpr int kParts = 64 + 4 * kOpen;
+// Rows.  A batch leaves each query up to four words (16 candidates each) of
+// accepted candidates; empty ones are not kept.  They wait in LDS, with the
+// candidates' original indices, until a query's words or the index tables
+// might not hold another batch; then every lane writes its row from its words,
+// four entries (16 bytes) at a time.  Waiting pays twice: the lanes of a
+// wavefront step together, and over several batches their entries are of more
+// nearly equal number (one batch gives 0 to 16 entries a lane, five give 33 +- 7);
+// and a row's 128-byte lines are filled in one go instead of being written
+// back in parts.  Fewer than four entries are carried over in LDS.
+constexpr int kWords = 16;
+constexpr int kTables = 8;
+
+// One wavefront's LDS: 9.6 KB, so four wavefronts per SIMD fit a compute unit.
+struct WaveLds {
+    uint32_t word[kWords + 1][64];  // per query: candidate mask (16 bits, first candidate highest), index base
+    int32_t index[kTables * 64 + 64 * 4];  // original indices of each batch's candidates; the entries carried over
+    int32_t sref[kStack];           // stack: record index, or run reference (< 0)
+    uint32_t pstart[kParts];        // queue: first sorted position, length - 1 in bits 27-29
+    uint16_t poff[kParts];          // particles queued before the part
+    uint8_t simg[kStack];           // image codes
+    uint8_t pimg[kParts];
+    uint8_t map[64];                // scratch: part starts by slot; candidate slot of each query's own particle
+};
+static_assert(sizeof(WaveLds) <= 10240, "four wavefronts per SIMD");
+
+// Periodic image m in {-1, 0, 1}^3 as three 2-bit fields m + 1; kHome is m = 0.
+constexpr uint32_t kHome = 1u | (1u << 2) | (1u << 4);
+
+// Per-query state of a lane.
+struct Query {
+    int32_t k, orig;
+    int32_t cnt;      // entries of the row so far
+    int32_t done;     // entries written to the row (a multiple of 4)
+    uint32_t words;   // words waiting
+    uint32_t carry;   // entries carried over (fewer than 4)
+    bool valid;
+};
+
+// A type tree as the test sees it (wave-uniform).
+struct TreeTest {
+    float r2in, r2out;   // accept and reject thresholds of the fp32 distance
+    double r2;           // exact squared list radius
+    float band, band_img;  // |v| that needs the fp32 distance: home image, other images
+    bool force;          // coordinates too large for the product: every pair needs it
+};
+
+// ------------------------------------------------------------------ rows
+
+// Writes the rows' waiting entries, all but the last (fewer than 4) of each.
+template <bool kVec4>
+__device__ __forceinline__ void write_rows(Query &q, WaveLds &w, int32_t *nbr, int32_t max_nbr, uint32_t lane) {
+    const uint32_t mine = kTables * 64 + lane * 4;  // the lane's carried entries
+    w.word[q.words][lane] = 0;
+    // the word in hand and the next one
+    uint32_t cur = ~(0xFFFFFFFFu >> q.carry) | mine;
+    uint32_t nxt = w.word[0][lane];
+    uint32_t at = 0;
+    auto next = [&]() {
+        const bool empty = cur < 0x10000u;
+        cur = empty ? nxt : cur;
+        at += empty ? 1u : 0u;
+        nxt = w.word[at][lane];
+        const uint32_t b = (uint32_t)__builtin_clz(cur | 1u);
+        cur ^= 0x80000000u >> b;
+        return w.index[(cur & 0xFFFFu) + b];
+    };
+    int32_t left = q.cnt - q.done;
+    int32_t *row = nbr + ((int64_t)q.orig * max_nbr + q.done);
+    while (left >= 4) {
+        int4 e;
+        e.x = next();
+        e.y = next();
+        e.z = next();
+        e.w = next();
+        if (kVec4) {
+            // done and max_nbr are multiples of 4 here
+            if (q.done < max_nbr) *reinterpret_cast<int4 *>(row) = e;
+        } else {
+            if (q.done + 0 < max_nbr) row[0] = e.x;
+            if (q.done + 1 < max_nbr) row[1] = e.y;
+            if (q.done + 2 < max_nbr) row[2] = e.z;
+            if (q.done + 3 < max_nbr) row[3] = e.w;
+        }
+        row += 4;
+        q.done += 4;
+        left -= 4;
+    }
+    // (a step never reads a carried entry that an earlier one has replaced)
+    for (int32_t i = 0; i < left; ++i) w.index[mine + i] = next();
+    q.carry = (uint32_t)left;
+    q.words = 0;
+    wave_lds_sync();
+}
+
+// Queues the candidates `m` (first of 32 slots highest) of a batch whose
+// index table half starts at `base`.
+__device__ __forceinline__ void add_words(uint32_t m, uint32_t base, Query &q, WaveLds &w, uint32_t lane) {
+    const uint32_t a = m & 0xFFFF0000u, b = m << 16;
+    w.word[q.words][lane] = a | base;
+    q.words += a != 0u ? 1u : 0u;
+    w.word[q.words][lane] = b | (base + 16u);
+    q.words += b != 0u ? 1u : 0u;
+}
+
+// ------------------------------------------------------------------ pairs
+
+// Exchanges rows and registers: with rows the four groups of 16 lanes, on
+// return register t's row c holds what register c's row t held.
+__device__ __forceinline__ void transpose4(uint32_t &a, uint32_t &b, uint32_t &c, uint32_t &d) {
+    auto p = __builtin_amdgcn_permlane32_swap(a, c, false, false);
+    auto q = __builtin_amdgcn_permlane32_swap(b, d, false, false);
+    auto r = __builtin_amdgcn_permlane16_swap(p[0], q[0], false, false);
+    auto s = __builtin_amdgcn_permlane16_swap(p[1], q[1], false, false);
+    a = r[0];
+    b = r[1];
+    c = s[0];
+    d = s[1];
+}
+
+__device__ __forceinline__ void transpose4(float &a, float &b, float &c, float &d) {
+    uint32_t x = __float_as_uint(a), y = __float_as_uint(b), z = __float_as_uint(c), u = __float_as_uint(d);
+    transpose4(x, y, z, u);
+    a = __uint_as_float(x);
+    b = __uint_as_float(y);
+    c = __uint_as_float(z);
+    d = __uint_as_float(u);
+}
+
+// Batch slot of lane l's candidate (and lane of slot l's: the map is its own
+// inverse).  The product of candidate group t leaves candidate row 4 k + i in
+// register i of lane row k; with this order the (4 t + i)-th sign shifted into
+// the mask there is slot 16 k + 4 t + i, so the four rows' masks concatenate
+// to one mask in slot order, first slot highest.
+__device__ __forceinline__ uint32_t slot_of(uint32_t l) {
+    return (((l >> 2) & 3u) << 4) | (((l >> 4) & 3u) << 2) | (l & 3u);
+}
+
+__device__ __forceinline__ uint32_t shift_in_sign(uint32_t mask, float v) {
+    return __builtin_amdgcn_alignbit(mask, __float_as_uint(v), 31);
+}
+
+// 64 candidates against query group g: accept mask of the lane's 16
+// candidates and the smallest |v|.
+__device__ __forceinline__ void test_group(const float a[4], float b, float c, uint32_t &mask, float &near) {
+    const v4f cc = {c, c, c, c};
+    v4f d[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b, cc, 0, 0, 0);
+    uint32_t m = 0;
+    float nr = __builtin_inff();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m = shift_in_sign(m, d[t][i]);
+        nr = fminf(fminf(nr, fabsf(d[t][0])), fabsf(d[t][1]));
+        nr = fminf(fminf(nr, fabsf(d[t][2])), fabsf(d[t][3]));
+    }
+    mask = m;
+    near = nr;
+}
+
+// The same products, as the mask of the pairs with |v| < band.
+__device__ __forceinline__ uint32_t near_group(const float a[4], float b, float c, float band) {
+    const v4f cc = {c, c, c, c};
+    uint32_t m = 0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const v4f d = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b, cc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m = shift_in_sign(m, fabsf(d[i]) - band);
+    }
+    return m;
+}
+
 // fp32 pair test.  With qs = fl(x_i + m L) per axis and a = fl(x_j - qs), each
 // |a - dx| <= 2^-24 (2 L + |a|), so the computed distance differs from the
 // definition's by at most eta = sqrt(3) 2^-22 (2 L_max + 2 R) while the pair
 // is near the cutoff.  Pairs with d32^2 <= ((R - eta)(1 - 2^-20))^2 are in,
 // pairs with d32^2 > ((R + eta)(1 + 2^-20))^2 are out, the rest (a shell a few
-// 1e-4 wide) take the fp64 path.
-#include "build_common.h"
-
-namespace qbi {
-namespace {
-
-// Decoding a 16-bit bound q of a record word held in a scalar register: the
-// float with bits 0x4B000000 | q is exactly 2^23 + q.  The lower bound is
-// decoded by the scalar unit (s_pack_ll_b32_b16 puts 0x4B00 above the low half
-// word), the upper one by the VALU (v_or_b32 with a 16-bit source select of
-// the scalar word against the bias held in a VGPR).  Splitting the decodes
-// balances the two issue slots of the shared walk, and leaves the clamp with
-// one scalar and one vector bound (a VALU op may read one scalar operand).
-__device__ __forceinline__ uint32_t vgpr_bias() {
-    uint32_t v;
-    asm volatile("v_mov_b32 %0, 0x4b000000" : "=v"(v));
-    return v;
+// 1e-4 wide) take the fp64 arithmetic of the definition.
+// Returns 0: out, 1: in, 2: in by the fp64 arithmetic.
+template <bool kF64, class LArr>
+__device__ __forceinline__ int decide_pair(const float4 &qp, int32_t k, const float4 &p, int32_t idx, uint32_t img,
+                                           const TreeTest &tt, const LArr &L, const double *__restrict__ sorted64) {
+    const double sx = (double)((int)(img & 3u) - 1) * L[0];
+    const double sy = (double)((int)((img >> 2) & 3u) - 1) * L[1];
+    const double sz = (double)((int)((img >> 4) & 3u) - 1) * L[2];
+    const float ax = p.x - (float)((double)qp.x + sx), ay = p.y - (float)((double)qp.y + sy),
+                az = p.z - (float)((double)qp.z + sz);
+    const float d2 = __builtin_fmaf(az, az, __builtin_fmaf(ay, ay, ax * ax));
+    if (d2 <= tt.r2in) return 1;
+    if (!(d2 <= tt.r2out)) return 0;
+    double dx, dy, dz;
+    if (kF64) {
+        // fp64 data: the pair's own fp64 positions
+        const double *q64 = sorted64 + 4 * (int64_t)k, *p64 = sorted64 + 4 * (int64_t)idx;
+        dx = (p64[0] - q64[0]) - sx;
+        dy = (p64[1] - q64[1]) - sy;
+        dz = (p64[2] - q64[2]) - sz;
+    } else {
+        dx = ((double)p.x - (double)qp.x) - sx;
+        dy = ((double)p.y - (double)qp.y) - sy;
+        dz = ((double)p.z - (double)qp.z) - sz;
+    }
+    return (dx * dx + dy * dy) + dz * dz <= tt.r2 ? 2 : 0;
 }
 
-__device__ __forceinline__ float lo_bound(uint32_t w) {
-    float r;
-    asm("s_pack_ll_b32_b16 %0, %1, 0x4b00" : "=s"(r) : "s"(w));
-    return r;
+// Band of the matrix-core test.  Let T be a pair's squared distance as the
+// fp32 positions and the exact image shift give it, and e_s the fp32
+// distance's own error near the cutoff (eta above for a shifted image; the
+// unshifted one has no rounded shift: 2^-21 R).  A pair outside the band must
+// be one that the fp32 distance certainly accepts (d32 <= sqrt(r2in) whenever
+// T <= (sqrt(r2in) - e_s)^2) or certainly rejects, so the band is
+//   max(R^2 - (sqrt(r2in) - e_s)^2, (sqrt(r2out) + e_s)^2 - R^2) + E
+// with E the error of v.  With u = 2^-24, S = 2 M + R (M the largest |q|, so
+// |q| + |c| <= S for a pair near the cutoff) the products and their sum cost
+// at most 12 u (S^2 + R^2) (five terms, two roundings' worth each), |c|^2 and
+// |q|^2 - R^2 at most 5 u (S^2 + R^2); rounding c and q moves the distance by
+// at most u S, a rounded image origin by sqrt(3) u 2 L_max.  E = 24 u (S^2 +
+// R^2) + 2.5 R (u S + 3.5 u L_max) covers them with room, which also keeps
+// candidates far from the cutoff (their error grows with |c|^2 2^-20, their
+// distance with |c|^2) from ever falling below -band.
+__device__ __forceinline__ float pair_band(double R, double rin, double rout, double e_s, double e_o, double M) {
+    const double u = 0x1p-24, S = 2.0 * M + R;
+    const double E = 24.0 * u * (S * S + R * R) + 2.5 * R * (u * S + e_o);
+    // r2in and r2out are rin^2 and rout^2 up to less than 2^-19 of themselves
+    const double in = fmax(rin * (1.0 - 0x1p-20) - e_s, 0.0), out = rout * (1.0 + 0x1p-20) + e_s;
+    const double b = fmax(R * R - in * in, out * out - R * R) + E;
+    return (float)(b * (1.0 + 0x1p-20) + 1e-30);
 }
 
-__device__ __forceinline__ float hi_bound(uint32_t w, uint32_t bias) {
-    float r;
-    asm("v_or_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD"
-        : "=v"(r)
-        : "s"(w), "v"(bias));
-    return r;
-}
-
-// Squared grid-unit distance from the query (ux, uy, uz) to a packed box.
-__device__ __forceinline__ float box_d2(uint32_t wx, uint32_t wy, uint32_t wz, float ux, float uy, float uz,
-                                        uint32_t bias) {
-    const float cx = __builtin_amdgcn_fmed3f(ux, lo_bound(wx), hi_bound(wx, bias)) - ux;
-    const float cy = __builtin_amdgcn_fmed3f(uy, lo_bound(wy), hi_bound(wy, bias)) - uy;
-    const float cz = __builtin_amdgcn_fmed3f(uz, lo_bound(wz), hi_bound(wz, bias)) - uz;
-    return __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx));
-}
-
-__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-
-// Row staging.  Each lane keeps its newest list entries in a ring of kRing
-// LDS slots (its own column, so lanes never share a bank row) and writes them
-// to its row kFlush at a time: with 16-byte aligned rows as two 16-byte
-// stores.  A candidate's index is written to the lane's next free slot
-// whether or not it is accepted, and the count advances only on acceptance,
-// so the per-candidate path has no branch.  Runs are taken 8 particles at a
-// time and the ring is flushed after each such part once kFlush entries wait,
-// so no more than 15 entries are ever pending.
-constexpr int kRing = 16;
-constexpr int kFlush = 8;
-
-struct Lane {
-    float x, y, z;         // query position
-    float qsx, qsy, qsz;   // fl(query + image shift)
-    float ux, uy, uz;      // query image in grid units (2^23 offset form)
-    float r2g;             // padded squared radius in grid units (negative: lane idle)
-    float r2in, r2out;     // fp32 accept / reject thresholds
-    double r2;             // exact squared list radius
-    int32_t k, orig;
-    int32_t cnt;           // entries of the list so far
-    int32_t flushed;       // entries already written to the row (a multiple of kFlush)
-    float px, py, pz;      // paper mode: query image in per-axis grid units (plain, not offset)
-    float phx, phy, phz;   // paper mode: bin width of each axis
-    float rp2;             // paper mode: squared tight radius (world units)
+// A batch: the queue's next parts, as many whole ones as 64 slots hold; this
+// lane's candidate is that of slot slot_of(lane).
+struct Batch {
+    uint64_t starts;   // slots at which a part starts
+    uint32_t parts, slots;
+    float4 p;
+    int32_t idx;       // sorted position, -1: an empty slot
+    uint32_t img;
 };
 
-template <bool kVec4, int kBlock>
-__device__ __forceinline__ void flush_ring(Lane &q, int32_t (*s_out)[kBlock], int32_t *nbr, int32_t max_nbr) {
-    const int32_t f = q.flushed;
-    const int s0 = f & (kRing - 1);
-    int32_t *row = nbr + ((int64_t)q.orig * max_nbr + f);
-    if (kVec4) {
-        // f and max_nbr are multiples of 4 here; one compare covers the usual
-        // case of a row with room for all eight
-        const int4 lo = make_int4(s_out[s0][threadIdx.x], s_out[s0 + 1][threadIdx.x], s_out[s0 + 2][threadIdx.x],
-                                  s_out[s0 + 3][threadIdx.x]);
-        if (f <= max_nbr - 8) {
-            *reinterpret_cast<int4 *>(row) = lo;
-            *reinterpret_cast<int4 *>(row + 4) = make_int4(s_out[s0 + 4][threadIdx.x], s_out[s0 + 5][threadIdx.x],
-                                                           s_out[s0 + 6][threadIdx.x], s_out[s0 + 7][threadIdx.x]);
-        } else if (f <= max_nbr - 4) {
-            *reinterpret_cast<int4 *>(row) = lo;
-        }
+__device__ __forceinline__ Batch take_batch(uint32_t at, uint32_t parts, WaveLds &w,
+                                            const float4 *__restrict__ sorted, uint32_t lane) {
+    Batch b;
+    const uint32_t base = uniform((uint32_t)w.poff[at]);
+    const uint32_t i = min(at + lane, parts - 1u);
+    const uint32_t s0 = w.poff[i] - base, s1 = s0 + (w.pstart[i] >> 27) + 1u;
+    const uint64_t take = __ballot(at + lane < parts && s1 <= 64u);
+    b.parts = (uint32_t)__popcll(take);
+    b.slots = (uint32_t)__builtin_amdgcn_readlane((int32_t)s1, (int32_t)b.parts - 1);
+    w.map[lane] = 0;
+    wave_lds_sync();
+    if ((take >> lane) & 1u) w.map[s0] = 1;
+    wave_lds_sync();
+    b.starts = __ballot(w.map[lane] != 0);
+    wave_lds_sync();
+    const uint32_t slot = slot_of(lane);
+    const uint64_t upto = b.starts & (~0ull >> (63u - slot));
+    const uint32_t part = at + (uint32_t)__popcll(upto) - 1u;
+    const bool on = slot < b.slots;
+    const uint32_t first = w.pstart[part] & 0x7FFFFFFu;
+    b.img = w.pimg[part];
+    b.idx = (int32_t)(first + (on ? slot - (w.poff[part] - base) : 0u));
+    b.p = sorted[b.idx];
+    if (!on) b.idx = -1;
+    return b;
+}
+
+// Slots [from, to) of a half batch as a mask, first slot highest.
+__device__ __forceinline__ uint32_t slot_range(uint32_t from, uint32_t to, uint32_t half) {
+    const uint32_t lo = half * 32u, a = from > lo ? min(from - lo, 32u) : 0u, b = to > lo ? min(to - lo, 32u) : 0u;
+    const uint64_t ones = 0xFFFFFFFF00000000ull;
+    return b > a ? (uint32_t)((ones >> b) & ~(ones >> a)) : 0u;
+}
+
+// The batch against the wavefront's queries; accepted candidates are queued
+// for the rows.  `table` is the index table it uses.
+template <bool kVec4, bool kF64, class Args>
+__device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Batch &t, uint32_t table, int groups,
+                                           const float *bq, const float *cq, float ox, float oy, float oz,
+                                           int32_t kw0, Query &q, WaveLds &w, const float4 *__restrict__ sorted,
+                                           const double *__restrict__ sorted64, uint32_t lane) {
+    const uint32_t slot = slot_of(lane);
+    const bool on = t.idx >= 0;
+    float osx = ox, osy = oy, osz = oz;
+    const bool shifted = __any(on && t.img != kHome);
+    if (shifted) {
+        osx = (float)((double)ox + (double)((int)(t.img & 3u) - 1) * a.L[0]);
+        osy = (float)((double)oy + (double)((int)((t.img >> 2) & 3u) - 1) * a.L[1]);
+        osz = (float)((double)oz + (double)((int)((t.img >> 4) & 3u) - 1) * a.L[2]);
+    }
+    float c[4];
+    c[0] = on ? t.p.x - osx : 0.0f;
+    c[1] = on ? t.p.y - osy : 0.0f;
+    c[2] = on ? t.p.z - osz : 0.0f;
+    c[3] = on ? __builtin_fmaf(c[2], c[2], __builtin_fmaf(c[1], c[1], c[0] * c[0])) : 1e30f;
+    w.index[table * 64u + slot] = ~__float_as_int(t.p.w);
+    // a query's own particle is never listed: it can only come up unshifted
+    const uint64_t mine = __ballot(on && t.img == kHome && (uint32_t)(t.idx - kw0) < 64u);
+    uint32_t self_lo = 0, self_hi = 0;
+    if (mine) {
+        w.map[lane] = 64;
+        wave_lds_sync();
+        if ((mine >> lane) & 1u) w.map[t.idx - kw0] = (uint8_t)slot;
+        wave_lds_sync();
+        const uint32_t s = w.map[lane];
+        self_lo = s < 32u ? 0x80000000u >> s : 0u;
+        self_hi = s >= 32u && s < 64u ? 0x80000000u >> (s - 32u) : 0u;
+        wave_lds_sync();
+    }
+    transpose4(c[0], c[1], c[2], c[3]);
+
+    uint32_t m[4] = {0u, 0u, 0u, 0u};
+    float nr[4] = {__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
+    if (groups == 4) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) test_group(c, bq[g], cq[g], m[g], nr[g]);
     } else {
-#pragma unroll
-        for (int e = 0; e < kFlush; ++e)
-            if (f + e < max_nbr) row[e] = s_out[s0 + e][threadIdx.x];
+        test_group(c, bq[0], cq[0], m[0], nr[0]);
+        if (groups > 1) test_group(c, bq[1], cq[1], m[1], nr[1]);
+        if (groups > 2) test_group(c, bq[2], cq[2], m[2], nr[2]);
     }
-    q.flushed = f + kFlush;
-}
-
-// The candidate's original index, inverted from its float4 w word (held in a
-// scalar register) straight into a VGPR: one VALU op, no scalar op.
-__device__ __forceinline__ int32_t orig_of(float w) {
-    int32_t r;
-    asm("v_not_b32 %0, %1" : "=v"(r) : "s"(__float_as_int(w)));
-    return r;
-}
-
-// Particle u of a run, addressed as the array base plus a byte offset.
-__device__ __forceinline__ float4 particle(const char *__restrict__ base, uint32_t off, uint32_t u) {
-    return reinterpret_cast<const float4 *>(base + off)[u];
-}
-
-// fp32 pass over the particles of a run for every lane.  Accepts what is
-// surely in (d2 <= thr; thr = r2in for hitting lanes, -1 otherwise) and
-// returns whether some lane has a pair in the shell (thr, out] (out = r2out
-// for hitting lanes, -1 otherwise), which then needs the exact test.  The
-// whole run (8 float4, padding included) is fetched with uniform loads up
-// front.  kSelf: the run may hold the lane's own particle at index `rel`,
-// which is never listed (nor taken as a shell pair).
-template <bool kSelf, int kBlock>
-__device__ __forceinline__ bool run_fp32(const char *__restrict__ base, uint32_t roff, uint32_t count, uint32_t rel,
-                                         float thr, float out, Lane &q, int32_t (*s_out)[kBlock]) {
-    float4 p[8];
+    const float band = shifted ? tt.band_img : tt.band;
+    const bool near_any = __any(fminf(fminf(nr[0], nr[1]), fminf(nr[2], nr[3])) <= band) || tt.force;
+    transpose4(m[0], m[1], m[2], m[3]);
+    uint32_t lo = ((m[0] << 16) | m[1]) & ~self_lo, hi = ((m[2] << 16) | m[3]) & ~self_hi;
+    const uint32_t base = table * 64u;
+    if (near_any) {
+        // some pair lies too near the cutoff for the product to decide
+        uint32_t e[4];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) p[u] = particle(base, roff, (uint32_t)u);
-    // both halves of the run are requested before the first test (the
-    // compiler would otherwise delay the second load behind the early exits)
-    asm volatile("" ::"s"(p[0].x), "s"(p[4].x));
-    // lanes with a pair in the shell: the band masks are combined on the
-    // scalar unit, which leaves the VALU one compare per candidate for them
-    uint64_t band = 0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        if ((uint32_t)u >= count) break;
-        const float ax = p[u].x - q.qsx, ay = p[u].y - q.qsy, az = p[u].z - q.qsz;
-        const float d2 = __builtin_fmaf(az, az, __builtin_fmaf(ay, ay, ax * ax));
-        const bool other = !kSelf || (uint32_t)u != rel;
-        const bool in = d2 <= thr && other;
-        s_out[q.cnt & (kRing - 1)][threadIdx.x] = orig_of(p[u].w);
-        q.cnt += in ? 1 : 0;
-        band |= __ballot(d2 <= out && other) & ~__ballot(in);
-    }
-    return band != 0;
-}
-
-// Sparse runs.  When at most 8 lanes hit a run, testing every particle on
-// all 64 lanes wastes most of them.  Instead each lane takes one
-// (hitting lane, particle) pair: lane l takes particle l % 8 of the (l / 8)-th
-// hitting lane (lanes whose particle index reaches the run length idle).  The
-// query's image and thresholds come from its lane by a cross-lane read, the
-// particle by a vector load.  An accepted pair is written into the ring of its
-// query's lane at that lane's count plus the number of accepted pairs of the
-// same query before it, so every row receives exactly the entries, in exactly
-// the order, of the per-lane pass.  Returns whether some pair fell in the
-// shell (thr, out] (then the caller decides the shell exactly).  Never used
-// for runs that may hold a lane's own particle.  s_src is the wavefront's
-// 64-entry LDS table rank -> lane.  Every cross-lane read runs on all lanes:
-// a lane left out of one would hand its readers 0.
-template <int kBlock>
-__device__ __forceinline__ bool run_sparse(const char *__restrict__ base, uint32_t roff, uint32_t count, bool hit,
-                                           uint64_t hits,
-                                           float thr, float out, Lane &q, int32_t (*s_out)[kBlock],
-                                           int32_t *s_src) {
-    const uint32_t lane = __lane_id();
-    const uint32_t i = lane >> 3, j = lane & 7u;
-    const uint32_t h = (uint32_t)__popcll(hits);
-    const bool pv = i < h && j < count;
-    const float4 p = particle(base, roff, j);  // j < 8: inside the run or its padding
-    const uint32_t rank =
-        __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
-    if (hit) s_src[rank] = (int32_t)lane;
-    __builtin_amdgcn_wave_barrier();
-    const int32_t src = s_src[i < h ? i : 0u];
-    const float sx = __shfl(q.qsx, src), sy = __shfl(q.qsy, src), sz = __shfl(q.qsz, src);
-    const float th = __shfl(thr, src), ou = __shfl(out, src);
-    const int32_t c0 = __shfl(q.cnt, src);
-    const float ax = p.x - sx, ay = p.y - sy, az = p.z - sz;
-    const float d2 = __builtin_fmaf(az, az, __builtin_fmaf(ay, ay, ax * ax));
-    const bool acc = pv && d2 <= th;
-    const bool shell = __any(pv && !(d2 <= th) && d2 <= ou);
-    const uint64_t A = __ballot(acc);
-    const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(A >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)A, 0u));
-    const uint32_t below0 = (uint32_t)__shfl((int32_t)below, (int32_t)(lane & ~7u));
-    if (acc) {
-        const uint32_t pos = (uint32_t)c0 + below - below0;
-        s_out[pos & (kRing - 1)][(threadIdx.x & ~63u) + (uint32_t)src] = ~__float_as_int(p.w);
-    }
-    // every hitting lane adds the accepted pairs of its own 8 lanes
-    const uint32_t e0 = (rank & 7u) << 3;
-    const uint32_t b0 = (uint32_t)__shfl((int32_t)below, (int32_t)e0);
-    const uint32_t b1r = (uint32_t)__shfl((int32_t)below, (int32_t)((e0 + 8u) & 63u));
-    const uint32_t b1 = e0 + 8u < 64u ? b1r : (uint32_t)__popcll(A);
-    if (hit) q.cnt += (int32_t)(b1 - b0);
-    return shell;
-}
-
-// 16-bit bound of a record-style word held in a scalar register, as a float.
-__device__ __forceinline__ float cvt_lo(uint32_t w) {
-    float r;
-    asm("v_cvt_f32_u32_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0" : "=v"(r) : "s"(w));
-    return r;
-}
-
-__device__ __forceinline__ float cvt_hi(uint32_t w) {
-    float r;
-    asm("v_cvt_f32_u32_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1" : "=v"(r) : "s"(w));
-    return r;
-}
-
-// Paper-mode pass (Section 2.3): a particle of the run is listed when the
-// lane's sphere overlaps the particle's own cell box (its leaf box in the
-// quantized tree, on the paper's per-axis grid), with no distance check.  The
-// nearest point is found in each axis's grid units and scaled to world units
-// by that axis's bin width; the test is against the tight radius
-// R (1 + 2^-20) + 0.02 max_d h_d.
-template <bool kSelf, int kBlock>
-__device__ __forceinline__ void run_paper(const uint4 *__restrict__ qrun, uint32_t count, uint32_t rel, bool hit,
-                                          Lane &q, int32_t (*s_out)[kBlock]) {
-    uint4 b[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) b[u] = qrun[u];
-    asm volatile("" ::"s"(b[0].x), "s"(b[4].x));
-    const float r2 = hit ? q.rp2 : -1.0f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        if ((uint32_t)u >= count) break;
-        const float cx = (__builtin_amdgcn_fmed3f(q.px, cvt_lo(b[u].x), cvt_hi(b[u].x)) - q.px) * q.phx;
-        const float cy = (__builtin_amdgcn_fmed3f(q.py, cvt_lo(b[u].y), cvt_hi(b[u].y)) - q.py) * q.phy;
-        const float cz = (__builtin_amdgcn_fmed3f(q.pz, cvt_lo(b[u].z), cvt_hi(b[u].z)) - q.pz) * q.phz;
-        const float d2 = __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx));
-        const bool other = !kSelf || (uint32_t)u != rel;
-        s_out[q.cnt & (kRing - 1)][threadIdx.x] = (int32_t)b[u].w;
-        q.cnt += (d2 <= r2 && other) ? 1 : 0;
-    }
-}
-
-// Decide the particles of one hit run for the lanes with `hit` set.  A run
-// of up to 16 particles is taken in halves of at most 8: each half adds at
-// most 8 entries to a ring holding fewer than kFlush, and the ring is
-// flushed after every half.
-template <bool kVec4, int kBlock, bool kPaper, bool kF64, class LArr>
-__device__ __forceinline__ void take_run(int32_t ref, bool hit, uint64_t hits, Lane &q, int img, const LArr &L,
-                                         const float4 *__restrict__ sorted, const uint4 *__restrict__ qpoint,
-                                         const double *__restrict__ sorted64, uint32_t nend,
-                                         int32_t (*s_out)[kBlock], int32_t *s_src, int32_t *nbr, int32_t max_nbr) {
-    const int32_t v = ~ref;
-    const uint32_t first = (uint32_t)uniform(v >> kRunCountBits);
-    const uint32_t count = (uint32_t)uniform((v & kRunCountMask) + 1);
-    // a well-formed tree never fails this; it keeps a corrupt reference from
-    // reading outside the particle array
-    if (first + count > nend) return;
-    const float thr = hit ? q.r2in : -1.0f;
-    const float out = hit ? q.r2out : -1.0f;
-    // (two 32-bit counts keep the comparison on the scalar unit)
-    const bool sparse = __popc((uint32_t)hits) + __popc((uint32_t)(hits >> 32)) <= 8;
-    for (uint32_t h0 = 0; h0 < count; h0 += 8) {
-        const uint32_t c8 = count - h0 < 8u ? count - h0 : 8u;
-        const char *sbase = reinterpret_cast<const char *>(sorted);
-        const uint32_t roff = (first + h0) * 16u;
-        // the lane's own particle can only be accepted through the unshifted image
-        const uint32_t rel = (uint32_t)(q.k - (int32_t)(first + h0));
-        const bool self = img == 13 && __any(hit && rel < c8);
-        if (kPaper) {
-            if (self)
-                run_paper<true, kBlock>(qpoint + first + h0, c8, rel, hit, q, s_out);
-            else
-                run_paper<false, kBlock>(qpoint + first + h0, c8, rel, hit, q, s_out);
-        } else {
-            bool shell;
-            if (!self && sparse) {
-                shell = run_sparse<kBlock>(sbase, roff, c8, hit, hits, thr, out, q, s_out, s_src);
-            } else {
-                shell = self ? run_fp32<true, kBlock>(sbase, roff, c8, rel, thr, out, q, s_out)
-                             : run_fp32<false, kBlock>(sbase, roff, c8, rel, thr, out, q, s_out);
-            }
-            if (shell) {
-                // some pair lies in the shell around the cutoff: decide the
-                // shell pairs with the definition's fp64 arithmetic
-                const double sx = (double)(img % 3 - 1) * L[0];
-                const double sy = (double)((img / 3) % 3 - 1) * L[1];
-                const double sz = (double)(img / 9 - 1) * L[2];
-                // fp64 data: the query's and the candidates' own fp64 positions
-                const double *q64 = kF64 ? sorted64 + 4 * (int64_t)(hit ? q.k : (int32_t)first) : nullptr;
-                const double qx = kF64 ? q64[0] : (double)q.x, qy = kF64 ? q64[1] : (double)q.y,
-                             qz = kF64 ? q64[2] : (double)q.z;
-                for (uint32_t j = 0; j < c8; ++j) {
-                    const float4 p = particle(sbase, roff, j);
-                    const float ax = p.x - q.qsx, ay = p.y - q.qsy, az = p.z - q.qsz;
-                    const float d2 = __builtin_fmaf(az, az, __builtin_fmaf(ay, ay, ax * ax));
-                    if (hit && !(d2 <= thr) && d2 <= q.r2out && j != rel) {
-                        const double *p64 = kF64 ? sorted64 + 4 * (int64_t)(first + h0 + j) : nullptr;
-                        const double dx = ((kF64 ? p64[0] : (double)p.x) - qx) - sx;
-                        const double dy = ((kF64 ? p64[1] : (double)p.y) - qy) - sy;
-                        const double dz = ((kF64 ? p64[2] : (double)p.z) - qz) - sz;
-                        if ((dx * dx + dy * dy) + dz * dz <= q.r2) {
-                            s_out[q.cnt & (kRing - 1)][threadIdx.x] = ~__float_as_int(p.w);
-                            ++q.cnt;
-                        }
-                    }
+        for (int g = 0; g < 4; ++g) e[g] = __any(nr[g] <= band) ? near_group(c, bq[g], cq[g], band) : 0u;
+        transpose4(e[0], e[1], e[2], e[3]);
+        uint32_t nlo = (e[0] << 16) | e[1], nhi = (e[2] << 16) | e[3];
+        if (tt.force) nlo = nhi = 0xFFFFFFFFu;
+        nlo = q.valid ? nlo & ~self_lo : 0u;
+        nhi = q.valid ? nhi & ~self_hi : 0u;
+        lo &= ~nlo;
+        hi &= ~nhi;
+        uint32_t xlo = 0, xhi = 0;  // accepted by the fp64 arithmetic
+        const float4 qp = sorted[q.k];
+        while (__any((nlo | nhi) != 0u)) {
+            const uint32_t b = nlo ? (uint32_t)__builtin_clz(nlo) : 32u + (uint32_t)__builtin_clz(nhi | 1u);
+            const uint32_t bit = 0x80000000u >> (b & 31u);
+            const int from = (int)slot_of(b);
+            const int32_t ci = __shfl(t.idx, from);
+            const uint32_t im = (uint32_t)__shfl((int32_t)t.img, from);
+            if ((nlo | nhi) != 0u) {
+                int r = 0;
+                if (ci >= 0) r = decide_pair<kF64>(qp, q.k, sorted[ci], ci, im, tt, a.L, sorted64);
+                if (b < 32u) {
+                    nlo ^= bit;
+                    lo |= r == 1 ? bit : 0u;
+                    xlo |= r == 2 ? bit : 0u;
+                } else {
+                    nhi ^= bit;
+                    hi |= r == 1 ? bit : 0u;
+                    xhi |= r == 2 ? bit : 0u;
                 }
             }
         }
-        // a plain per-lane branch: the wavefront skips it when no lane's
-        // condition holds, with one compare instead of a ballot and a test
-        if (q.cnt - q.flushed >= kFlush)
-            flush_ring<kVec4, kBlock>(q, s_out, nbr, max_nbr);
-    }
-}
-
-// The read-only arrays come as separate __restrict__ parameters: that lets the
-// compiler fetch wave-uniform records and particles with scalar loads.
-template <bool kVec4, int kBlock, bool kPaper, bool kF64, class Args>
-__device__ __forceinline__ void traverse_block(Args &a, int32_t li, const uint4 *__restrict__ records,
-                                               const int32_t *__restrict__ ropes,
-                                               const float4 *__restrict__ sorted,
-                                               const uint4 *__restrict__ qpoint,
-                                               const double *__restrict__ sorted64,
-                                               const TreeMeta *__restrict__ meta, int32_t (*s_out)[kBlock],
-                                               int32_t (*s_src)[64]);
-
-// Workgroups are dealt round-robin to the 8 XCDs; each XCD gets one
-// contiguous stretch of the Z-ordered queries so its L2 holds one region.
-__device__ __forceinline__ int32_t xcd_logical_block() {
-    const uint32_t nb = gridDim.x, b = blockIdx.x;
-    const uint32_t xcd = b & 7u, qq = nb >> 3, rr = nb & 7u;
-    return (int32_t)(xcd * qq + (xcd < rr ? xcd : rr) + (b >> 3));
-}
-
-// Query order.  A system of one type takes its queries in sorted (Z) order,
-// a.qpw per wavefront.  In a system of several types, the workgroups form
-// eight equal stretches (one per XCD when the system covers the whole
-// launch); stretch x takes the x-th eighth of every type's queries, smallest
-// type first, in wavefronts of type_qpw queries of one type.  A sparse type's
-// wavefronts span the widest regions and run longest: this way they start
-// first, are spread over the stretches, and each takes few queries, instead
-// of closing the launch on one XCD.  `wg` is the system's workgroup in
-// dispatch order and `nwg` its workgroup count (trav_blocks, an upper bound
-// for several types); returns the lane's position in the system, or a.n for
-// an idle lane.
-template <int kBlock, class Args>
-__device__ __forceinline__ int32_t query_position(Args &a, const TreeMeta *__restrict__ meta, int32_t wg,
-                                                  int32_t nwg) {
-    const int32_t lane = (int32_t)(threadIdx.x & 63u), wave = (int32_t)(threadIdx.x >> 6);
-    if (a.ntypes <= 1) {
-        // wavefronts of a.qpw queries: lanes past a.qpw idle
-        const int32_t qpw = a.qpw;
-        if (lane >= qpw) return a.n;
-        return (wg * (kBlock / 64) + wave) * qpw + lane;
-    }
-    const int32_t per = nwg / 8;
-    const int64_t part = wg / per;
-    int32_t wi = (wg % per) * (kBlock / 64) + wave;  // wavefront of the stretch
-    for (int r = 0; r < a.ntypes; ++r) {
-        // the type of rank r by (count, type index)
-        int t = 0;
-        for (int u = 0; u < a.ntypes; ++u) {
-            int rank = 0;
-            for (int w = 0; w < a.ntypes; ++w)
-                rank += (meta[w].count < meta[u].count || (meta[w].count == meta[u].count && w < u)) ? 1 : 0;
-            if (rank == r) t = u;
+        if (__any((xlo | xhi) != 0u)) {
+            // a part's candidates that the fp64 arithmetic accepted follow
+            // those the fp32 distance accepted
+            auto room = [&]() {
+                if (__any(q.words > (uint32_t)kWords - 4u)) {
+                    wave_lds_sync();
+                    write_rows<kVec4>(q, w, a.nbr, a.max_nbr, lane);
+                }
+            };
+            uint32_t from = 0;
+            for (uint64_t st = t.starts; st; st &= st - 1u) {
+                const uint32_t p0 = (uint32_t)__builtin_ctzll(st);
+                const uint64_t more = st & (st - 1u);
+                const uint32_t p1 = more ? (uint32_t)__builtin_ctzll(more) : t.slots;
+                const uint32_t x0 = xlo & slot_range(p0, p1, 0), x1 = xhi & slot_range(p0, p1, 1);
+                if (!__any((x0 | x1) != 0u)) continue;
+                const uint32_t y0 = lo & slot_range(from, p1, 0), y1 = hi & slot_range(from, p1, 1);
+                room();
+                add_words(y0, base, q, w, lane);
+                add_words(y1, base + 32u, q, w, lane);
+                q.cnt += (int32_t)(__popc(y0) + __popc(y1));
+                room();
+                add_words(x0, base, q, w, lane);
+                add_words(x1, base + 32u, q, w, lane);
+                q.cnt += (int32_t)(__popc(x0) + __popc(x1));
+                from = p1;
+            }
+            lo &= slot_range(from, 64u, 0);
+            hi &= slot_range(from, 64u, 1);
+            room();
         }
-        const int64_t len = meta[t].count;
-        const int32_t lo = stretch_lo(len, part), hi = stretch_lo(len, part + 1);
-        const int32_t qt = type_qpw(len, a.n, a.qpw);
-        const int32_t nw = type_waves(len, a.n, a.qpw, part);
-        if (wi < nw) {
-            const int32_t j = wi * qt + lane;
-            return (lane < qt && j < hi - lo) ? meta[t].start - a.start + lo + j : a.n;
-        }
-        wi -= nw;
     }
-    return a.n;
+    add_words(lo, base, q, w, lane);
+    add_words(hi, base + 32u, q, w, lane);
+    q.cnt += (int32_t)(__popc(lo) + __popc(hi));
+    wave_lds_sync();
 }
 
-template <bool kVec4, int kBlock, bool kPaper, bool kF64>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_traverse(
-    TravArgs a, const uint4 *__restrict__ records, const int32_t *__restrict__ ropes,
-    const float4 *__restrict__ sorted, const uint4 *__restrict__ qpoint, const TreeMeta *__restrict__ meta) {
-    __shared__ int32_t s_out[kRing][kBlock];
-    __shared__ int32_t s_src[kBlock / 64][64];
+// ------------------------------------------------------------------ walk
+
+// Prefix minimum (maximum) over the lanes of each segment, up to and with the
+// lane's own value; `seg0` is the first lane of the lane's segment.
+__device__ __forceinline__ float seg_scan(float x, uint32_t lane, uint32_t seg0, bool want_min) {
+#pragma unroll
+    for (uint32_t o = 1; o < 64; o <<= 1) {
+        const float y = __shfl_up(x, o);
+        if (lane >= seg0 + o) x = want_min ? fminf(x, y) : fmaxf(x, y);
+    }
+    return x;
+}
+
+// Sum over the lanes up to and with this one.
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
+    int32_t v = (int32_t)x;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+    return (uint32_t)v;
+}
+
+__device__ __forceinline__ float wave_max(float x) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
+    return uniform(x);
+}
+
+// One wavefront of queries; this lane's query is position `li` of the system
+// `a` (li >= a.n: an idle lane; the valid lanes come first).
+template <bool kVec4, bool kF64, class Args>
+__device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *__restrict__ records,
+                                              const float4 *__restrict__ sorted, const double *__restrict__ sorted64,
+                                              const TreeMeta *__restrict__ meta, WaveLds &w) {
+    const uint32_t lane = (uint32_t)(threadIdx.x & 63u);
+    Query q;
+    q.valid = li < a.n;
+    const int32_t nq = (int32_t)__popcll(__ballot(q.valid));
+    if (nq == 0) return;
+    const int32_t kw0 = uniform(a.start + li);  // lane 0 is valid
+    const uint32_t nend = (uint32_t)(a.start + a.n);
+    q.k = kw0 + min((int32_t)lane, nq - 1);  // idle lanes repeat the last query
+    const float4 qp = sorted[q.k];
+    q.orig = ~__float_as_int(qp.w);
+    q.cnt = 0;
+    q.done = 0;
+    q.words = 0;
+    q.carry = 0;
+    int ta = 0;
+    for (int t = 1; t < a.ntypes; ++t)
+        if (kw0 >= meta[t].start && meta[t].count > 0) ta = t;
+    ta = uniform(ta);
+    const int groups = (nq + 15) >> 4;
+
+    // cut the queries where neighbours lie farthest apart
+    const float gx = qp.x - __shfl_up(qp.x, 1), gy = qp.y - __shfl_up(qp.y, 1), gz = qp.z - __shfl_up(qp.z, 1);
+    float gap = lane == 0 ? -1.0f : __builtin_fmaf(gz, gz, __builtin_fmaf(gy, gy, gx * gx));
+    uint64_t cuts = 1u;  // first lanes of the segments
+#pragma unroll
+    for (int s = 1; s < kSegs; ++s) {
+        const float top = wave_max(gap);
+        const uint64_t at = __ballot(gap == top && gap > 0.0f);
+        if (at) {
+            const uint32_t c = (uint32_t)__builtin_ctzll(at);
+            cuts |= 1ull << c;
+            if (lane == c) gap = -1.0f;
+        }
+    }
+    // bounds of each segment, at its last lane
+    const uint64_t upto = cuts & (~0ull >> (63u - lane));
+    const uint32_t seg0 = 63u - (uint32_t)__builtin_clzll(upto);
+    const float blx = seg_scan(qp.x, lane, seg0, true), bly = seg_scan(qp.y, lane, seg0, true),
+                blz = seg_scan(qp.z, lane, seg0, true);
+    const float bhx = seg_scan(qp.x, lane, seg0, false), bhy = seg_scan(qp.y, lane, seg0, false),
+                bhz = seg_scan(qp.z, lane, seg0, false);
+    uint32_t last[kSegs];  // last lane of each segment (segments that do not exist repeat the final one)
+    {
+        uint64_t ends = (cuts >> 1) | (1ull << 63);
+#pragma unroll
+        for (int s = 0; s < kSegs; ++s) {
+            last[s] = (uint32_t)__builtin_ctzll(ends);
+            if (ends & (ends - 1u)) ends &= ends - 1u;
+        }
+    }
+    // the wavefront's origin: the middle of its queries
+    float olo[3] = {lane_value(blx, last[0]), lane_value(bly, last[0]), lane_value(blz, last[0])};
+    float ohi[3] = {lane_value(bhx, last[0]), lane_value(bhy, last[0]), lane_value(bhz, last[0])};
+#pragma unroll
+    for (int s = 1; s < kSegs; ++s) {
+        olo[0] = fminf(olo[0], lane_value(blx, last[s]));
+        olo[1] = fminf(olo[1], lane_value(bly, last[s]));
+        olo[2] = fminf(olo[2], lane_value(blz, last[s]));
+        ohi[0] = fmaxf(ohi[0], lane_value(bhx, last[s]));
+        ohi[1] = fmaxf(ohi[1], lane_value(bhy, last[s]));
+        ohi[2] = fmaxf(ohi[2], lane_value(bhz, last[s]));
+    }
+    const float ox = uniform(0.5f * (olo[0] + ohi[0])), oy = uniform(0.5f * (olo[1] + ohi[1])),
+                oz = uniform(0.5f * (olo[2] + ohi[2]));
+    const float rx = qp.x - ox, ry = qp.y - oy, rz = qp.z - oz;
+    const float q2 = __builtin_fmaf(rz, rz, __builtin_fmaf(ry, ry, rx * rx));
+    const float M2 = wave_max(q2);  // (rounded: the bands below leave room for it)
+    float bq[4] = {-2.0f * rx, -2.0f * ry, -2.0f * rz, 1.0f};
+    transpose4(bq[0], bq[1], bq[2], bq[3]);
+
+    uint32_t table = 0;  // index tables in use
+    for (int tb = 0; tb < a.ntypes; ++tb) {
+        const TreeMeta &m = meta[tb];
+        const double r2 = a.rlist2[ta * QBVH_MAX_TYPES + tb];
+        if (m.count == 0 || !(r2 >= 0.0)) continue;
+        const double R = sqrt(r2);
+        // fp64 data: the tree and the queries are the data rounded to fp32,
+        // which moves each point by up to 2^-24 L_max per axis, so a pair's
+        // distance by up to sqrt(3) 2^-23 L_max: the node test widens the
+        // search by that much, and the fp32 pair band is doubled
+        const double rshift = kF64 ? 1.7320508075688772 * 0x1p-23 * a.lmax : 0.0;
+        const double eta = (kF64 ? 2.0 : 1.0) * 1.7320508075688772 * 0x1p-22 * (2.0 * a.lmax + 2.0 * R);
+        const double rin = fmax(R - eta, 0.0) * (1.0 - 0x1p-20);
+        const double rout = (R + eta) * (1.0 + 0x1p-20);
+        TreeTest tt;
+        tt.r2 = r2;
+        tt.r2in = (float)(rin * rin * (1.0 - 0x1p-20));
+        tt.r2out = (float)(rout * rout * (1.0 + 0x1p-20));
+        const double M = (double)(sqrtf(M2) * (1.0f + 0x1p-20f));
+        tt.band = uniform(pair_band(R, rin, rout, R * 0x1p-21, 0.0, M));
+        tt.band_img = uniform(pair_band(R, rin, rout, 1.7320508075688772 * 0x1p-22 * (2.0 * a.lmax + 2.0 * R),
+                                        3.5 * 0x1p-24 * a.lmax, M));
+        // (squares of such coordinates would overflow)
+        tt.force = !(M2 < 1e28f) || !(a.lmax < 1e14);
+        const float c0 = q.valid ? q2 - (float)r2 : 1e30f;
+        float cq[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) cq[g] = __shfl(c0, 16 * g + (int)(lane & 15u));
+
+        // Node test in grid units.  A quantized bound is an exact float; a
+        // search box bound and an image shift are rounded once each, the
+        // radius is padded by two bins, 2^-20 of itself and 2^-21 of the
+        // largest box edge in bins (far above those roundings).
+        const double ih = m.inv_h;
+        const double rgp = (R + rshift) * ih * (1.0 + 0x1p-20) + 2.0 + 0x1p-21 * (a.lmax * ih);
+        const float r2g = uniform((float)(rgp * rgp * (1.0 + 0x1p-20)));
+        const float ulx = (float)(((double)blx - (double)m.lo[0]) * ih), uly = (float)(((double)bly - (double)m.lo[1]) * ih),
+                    ulz = (float)(((double)blz - (double)m.lo[2]) * ih);
+        const float uhx = (float)(((double)bhx - (double)m.lo[0]) * ih), uhy = (float)(((double)bhy - (double)m.lo[1]) * ih),
+                    uhz = (float)(((double)bhz - (double)m.lo[2]) * ih);
+        float sl[kSegs][3], sh[kSegs][3];
+#pragma unroll
+        for (int s = 0; s < kSegs; ++s) {
+            sl[s][0] = lane_value(ulx, last[s]);
+            sl[s][1] = lane_value(uly, last[s]);
+            sl[s][2] = lane_value(ulz, last[s]);
+            sh[s][0] = lane_value(uhx, last[s]);
+            sh[s][1] = lane_value(uhy, last[s]);
+            sh[s][2] = lane_value(uhz, last[s]);
+        }
+        const float gLx = uniform((float)(a.L[0] * ih)), gLy = uniform((float)(a.L[1] * ih)),
+                    gLz = uniform((float)(a.L[2] * ih));
+        const int32_t end = m.end;
+
+        // every image's root, the first image on top
+        if (lane < 27u) {
+            const uint32_t img = lane % 3u | ((lane / 3u) % 3u) << 2 | (lane / 9u) << 4;
+            w.sref[26u - lane] = m.root;
+            w.simg[26u - lane] = (uint8_t)img;
+        }
+        uint32_t size = 27, parts = 0, queued = 0;  // nodes to open; parts and particles queued
+        wave_lds_sync();
+        while (size) {
+            // (1) open the next nodes
+            const uint32_t room = size < (uint32_t)(kStack - kDepthMax) ? (uint32_t)(kStack - kDepthMax) - size : 1u;
+            const uint32_t p = min(min(size, (uint32_t)kOpen), room);
+            const uint32_t e = lane >> 1;
+            const bool act = e < p;
+            const uint32_t at = size - 1u - (act ? e : 0u);
+            const int32_t ref = w.sref[at];
+            const uint32_t img = w.simg[at];
+            wave_lds_sync();
+            size -= p;
+            int32_t nref = ref;
+            bool hit = act && (lane & 1u) == 0u, swap = false;
+            if (act && ref >= 0) {
+                const char *rec = reinterpret_cast<const char *>(records) + ((uint64_t)(uint32_t)ref << 5);
+                const uint32_t *box = reinterpret_cast<const uint32_t *>(rec + (lane & 1u) * 12u);
+                const int2 child = *reinterpret_cast<const int2 *>(rec + 24);
+                const uint32_t wx = box[0], wy = box[1], wz = box[2];
+                // a run on the right of an internal child comes before it: the
+                // two lanes then exchange their children (after the box test)
+                swap = child.x >= 0 && child.y < 0;
+                nref = ((lane & 1u) != 0u) != swap ? child.y : child.x;
+                float lx = (float)(wx & 0xFFFFu), ly = (float)(wy & 0xFFFFu), lz = (float)(wz & 0xFFFFu);
+                float hx = (float)(wx >> 16), hy = (float)(wy >> 16), hz = (float)(wz >> 16);
+                if (img != kHome) {
+                    // the search box of the shifted queries against the node is the
+                    // unshifted one against the node shifted back
+                    const float tx = (float)((int)(img & 3u) - 1) * gLx, ty = (float)((int)((img >> 2) & 3u) - 1) * gLy,
+                                tz = (float)((int)((img >> 4) & 3u) - 1) * gLz;
+                    lx -= tx;
+                    hx -= tx;
+                    ly -= ty;
+                    hy -= ty;
+                    lz -= tz;
+                    hz -= tz;
+                }
+                float best = __builtin_inff();
+#pragma unroll
+                for (int s = 0; s < kSegs; ++s) {
+                    const float cx = fmaxf(fmaxf(lx - sh[s][0], sl[s][0] - hx), 0.0f);
+                    const float cy = fmaxf(fmaxf(ly - sh[s][1], sl[s][1] - hy), 0.0f);
+                    const float cz = fmaxf(fmaxf(lz - sh[s][2], sl[s][2] - hz), 0.0f);
+                    best = fminf(best, __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx)));
+                }
+                hit = best <= r2g;
+            }
+            const uint32_t v = (uint32_t)~nref;
+            const uint32_t first = v >> kRunCountBits, count = (v & (uint32_t)kRunCountMask) + 1u;
+            uint64_t H = __ballot(hit);
+            const uint64_t S = __ballot(swap);
+            H = (H & ~S) | (((H & 0x5555555555555555ull) << 1 | (H >> 1 & 0x5555555555555555ull)) & S);
+            // (a well-formed tree's references point forward and its runs end
+            // inside the system: this only keeps a corrupt one from running on)
+            H &= __ballot(nref >= 0 ? (ref < 0 || (nref > ref && nref < end)) : first + count <= nend);
+            // runs before the first internal node are next in order
+            const uint64_t I = H & __ballot(nref >= 0);
+            const uint64_t E = I ? H & ((I & (~I + 1ull)) - 1ull) : H;
+            const uint64_t P = H & ~E;
+            const uint32_t np = (uint32_t)__popcll(P);
+            if ((P >> lane) & 1u) {
+                const uint32_t to = size + np - 1u - mbcnt(P);
+                w.sref[to] = nref;
+                w.simg[to] = (uint8_t)img;
+            }
+            size += np;
+            // (2) queue their parts
+            const bool run = (E >> lane) & 1u;
+            const uint64_t two = __ballot(run && count > 8u);
+            const uint32_t sum = wave_prefix_sum(run ? count : 0u);
+            if (run) {
+                const uint32_t to = parts + mbcnt(E) + mbcnt(two), off = queued + sum - count;
+                w.pstart[to] = first | ((count > 8u ? 7u : count - 1u) << 27);
+                w.poff[to] = (uint16_t)off;
+                w.pimg[to] = (uint8_t)img;
+                if (count > 8u) {
+                    w.pstart[to + 1u] = (first + 8u) | ((count - 9u) << 27);
+                    w.poff[to + 1u] = (uint16_t)(off + 8u);
+                    w.pimg[to + 1u] = (uint8_t)img;
+                }
+            }
+            parts += (uint32_t)__popcll(E) + (uint32_t)__popcll(two);
+            queued += (uint32_t)__builtin_amdgcn_readlane((int32_t)sum, 63);
+            wave_lds_sync();
+            // (3) test full batches; what the walk's end leaves is tested too
+            if (queued >= 64u || size == 0u) {
+                uint32_t done = 0, rest = queued;
+                while (rest >= 64u || (size == 0u && rest > 0u)) {
+                    if (table == (uint32_t)kTables || __any(q.words > (uint32_t)kWords - 4u)) {
+                        write_rows<kVec4>(q, w, a.nbr, a.max_nbr, lane);
+                        table = 0;
+                    }
+                    const Batch t = take_batch(done, parts, w, sorted, lane);
+                    test_batch<kVec4, kF64>(a, tt, t, table, groups, bq, cq, ox, oy, oz, kw0, q, w, sorted, sorted64,
+                                            lane);
+                    ++table;
+                    done += t.parts;
+                    rest -= t.slots;
+                }
+                const uint32_t left = parts - done, gone = queued - rest;
+                uint32_t ps = 0, po = 0, pi = 0;
+                if (lane < left) {
+                    ps = w.pstart[done + lane];
+                    po = w.poff[done + lane];
+                    pi = w.pimg[done + lane];
+                }
+                wave_lds_sync();
+                if (lane < left) {
+                    w.pstart[lane] = ps;
+                    w.poff[lane] = (uint16_t)(po - gone);
+                    w.pimg[lane] = (uint8_t)pi;
+                }
+                parts = left;
+                queued = rest;
+                wave_lds_sync();
+            }
+        }
+    }
+
+    write_rows<kVec4>(q, w, a.nbr, a.max_nbr, lane);
+    if (!q.valid) return;
+    a.count[q.orig] = q.cnt;
+    int32_t *row = a.nbr + ((int64_t)q.orig * a.max_nbr + q.done);
+    for (uint32_t e = 0; e < q.carry; ++e)
+        if (q.done + (int32_t)e < a.max_nbr) row[e] = w.index[kTables * 64 + lane * 4 + e];
+    if (q.cnt > a.max_nbr) atomicOr(a.overflow, 1);
+}
+
+template <bool kVec4, int kBlock, bool kF64>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_traverse(
+    TravArgs a, const uint4 *__restrict__ records, const float4 *__restrict__ sorted,
+    const TreeMeta *__restrict__ meta) {
+    __shared__ WaveLds s_wave[kBlock / 64];
     const int32_t li = query_position<kBlock>(a, meta, xcd_logical_block(), (int32_t)gridDim.x);
-    traverse_block<kVec4, kBlock, kPaper, kF64, const TravArgs>(a, li, records, ropes, sorted, qpoint, a.sorted64, meta,
-                                                                s_out, s_src);
+    traverse_wave<kVec4, kF64, const TravArgs>(a, li, records, sorted, a.sorted64, meta, s_wave[threadIdx.x >> 6]);
 }
 
 // Batched form: the workgroups of all systems form one grid; each workgroup
@@ -421,12 +796,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
 // reads that system's arguments from the device table, so every per-system
 // value stays wave-uniform.
 template <bool kVec4, int kBlock>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_traverse_batch(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_traverse_batch(
     const TravArgs *__restrict__ table, const int32_t *__restrict__ tblk_first, int32_t nsys,
-    const uint4 *__restrict__ records, const int32_t *__restrict__ ropes, const float4 *__restrict__ sorted,
-    const TreeMeta *__restrict__ meta_all) {
-    __shared__ int32_t s_out[kRing][kBlock];
-    __shared__ int32_t s_src[kBlock / 64][64];
+    const uint4 *__restrict__ records, const float4 *__restrict__ sorted, const TreeMeta *__restrict__ meta_all) {
+    __shared__ WaveLds s_wave[kBlock / 64];
     const int32_t logical = xcd_logical_block();
     const int32_t sys = find_seg(tblk_first, nsys, logical);
     // the system's arguments are read through the constant address space, as
@@ -436,209 +809,33 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     ConstArgs *args = reinterpret_cast<ConstArgs *>(reinterpret_cast<uintptr_t>(table + sys));
     const TreeMeta *meta = meta_all + sys * QBVH_MAX_TYPES;
     const int32_t li = query_position<kBlock>(*args, meta, logical - tblk_first[sys], tblk_first[sys + 1] - tblk_first[sys]);
-    traverse_block<kVec4, kBlock, false, false, ConstArgs>(*args, li, records, ropes, sorted, nullptr, nullptr, meta,
-                                                           s_out, s_src);
-}
-
-// One workgroup of queries; this lane's query is position `li` of the system
-// `a` (li >= a.n: an idle lane).
-template <bool kVec4, int kBlock, bool kPaper, bool kF64, class Args>
-__device__ __forceinline__ void traverse_block(Args &a, int32_t li, const uint4 *__restrict__ records,
-                                               const int32_t *__restrict__ ropes,
-                                               const float4 *__restrict__ sorted,
-                                               const uint4 *__restrict__ qpoint,
-                                               const double *__restrict__ sorted64,
-                                               const TreeMeta *__restrict__ meta, int32_t (*s_out)[kBlock],
-                                               int32_t (*s_src_all)[64]) {
-    int32_t *s_src = s_src_all[threadIdx.x >> 6];
-    const bool valid = li < a.n;  // idle lanes still take part in the shared walk
-    const int32_t k = a.start + li;
-    const uint32_t nend = (uint32_t)(a.start + a.n);
-
-    Lane q;
-    const float4 qp = sorted[valid ? k : a.start];
-    q.x = qp.x;
-    q.y = qp.y;
-    q.z = qp.z;
-    q.k = k;
-    q.orig = ~__float_as_int(qp.w);
-    int ta = 0;
-    for (int t = 1; t < a.ntypes; ++t)
-        if (k >= meta[t].start) ta = t;
-
-    q.cnt = 0;
-    q.flushed = 0;
-    const uint32_t bias = vgpr_bias();
-    for (int tb = 0; tb < a.ntypes; ++tb) {
-        const TreeMeta &m = meta[tb];
-        if (m.count == 0) continue;
-        double r2 = a.rlist2[tb];
-        for (int t = 1; t < a.ntypes; ++t)
-            if (ta == t) r2 = a.rlist2[t * QBVH_MAX_TYPES + tb];
-        const bool lane_on = valid && r2 >= 0.0;
-        q.r2 = r2;
-        const double R = lane_on ? sqrt(r2) : 0.0;
-
-        // (1) image mask against the root box (the image test of Algorithm 1), in fp32
-        // with an outward pad of 2^-18 of the largest box edge (far above the
-        // fp32 rounding of the shifted coordinates) plus 2^-20 relative.
-        uint32_t bits = 0;
-        if (lane_on) {
-            const float pad = (float)(a.lmax * 0x1p-18);
-            const float rimg = (float)R * (1.0f + 0x1p-20f) + pad;
-            const float rimg2 = rimg * rimg;
-            float e2[3][3];
-            const float xq[3] = {q.x, q.y, q.z};
-#pragma unroll
-            for (int dd = 0; dd < 3; ++dd) {
-#pragma unroll
-                for (int sh = 0; sh < 3; ++sh) {
-                    const float p = xq[dd] + (float)(sh - 1) * a.Lf[dd];
-                    const float e = fmaxf(fmaxf(m.lo[dd] - p, p - m.hi[dd]), 0.0f);
-                    e2[dd][sh] = e * e;
-                }
-            }
-#pragma unroll
-            for (int img = 0; img < 27; ++img) {
-                const float sum = (e2[0][img % 3] + e2[1][(img / 3) % 3]) + e2[2][img / 9];
-                if (sum <= rimg2) bits |= 1u << img;
-            }
-        }
-        uint32_t wave_bits = bits;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) wave_bits |= (uint32_t)__shfl_xor((int)wave_bits, o, 64);
-        wave_bits = (uint32_t)uniform((int32_t)wave_bits);
-
-        // fp64 data: the tree and the query are the data rounded to fp32, which
-        // moves each point by up to 2^-24 L_max per axis, so a pair's distance
-        // by up to sqrt(3) 2^-23 L_max; the node test widens the sphere by that
-        // much before the two-bin pad (which alone covers it only when the
-        // tree's root box is not much smaller than the periodic box)
-        const double rshift = kF64 ? 1.7320508075688772 * 0x1p-23 * a.lmax : 0.0;
-        const double rg = (R + rshift) * m.inv_h;
-        const double rgp = rg * (1.0 + 0x1p-20) + 2.0;
-        const float r2g = lane_on ? (float)(rgp * rgp * (1.0 + 0x1p-20)) : -1.0f;
-        // fp64 data adds the rounding of both points to fp32 (2^-24 L each per
-        // axis); the band is doubled for it
-        const double eta = (kF64 ? 2.0 : 1.0) * 1.7320508075688772 * 0x1p-22 * (2.0 * a.lmax + 2.0 * R);
-        const double rin = fmax(R - eta, 0.0) * (1.0 - 0x1p-20);
-        const double rout = (R + eta) * (1.0 + 0x1p-20);
-        q.r2in = (float)(rin * rin * (1.0 - 0x1p-20));
-        q.r2out = (float)(rout * rout * (1.0 + 0x1p-20));
-        const int32_t root = m.root, end = m.end;
-        double ph[3] = {1.0, 1.0, 1.0};
-        if (kPaper) {
-            // the paper's per-axis bins (as the cell boxes were quantized); the
-            // pad covers the rounding of the query's grid position (at most
-            // 2^-24 of 65535 bins per axis) and of the fp32 distance
-            double hmax = 0.0;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                ph[d] = axis_spacing(m.lo[d], m.hi[d], a.lmax * 0x1p-24, a.qbits);
-                hmax = ph[d] > hmax ? ph[d] : hmax;
-            }
-            q.phx = (float)ph[0];
-            q.phy = (float)ph[1];
-            q.phz = (float)ph[2];
-            const double rp = R * (1.0 + 0x1p-20) + 0.02 * hmax;
-            q.rp2 = (float)(rp * rp * (1.0 + 0x1p-20));
-        }
-
-        // (2) one shared stackless walk per image in the union (the walk of Algorithm 1)
-        while (wave_bits) {
-            const int img = __builtin_ctz(wave_bits);
-            wave_bits &= wave_bits - 1u;
-            const bool on = (bits >> img) & 1u;
-            q.r2g = on ? r2g : -1.0f;
-            const double sx = (double)(img % 3 - 1) * a.L[0];
-            const double sy = (double)((img / 3) % 3 - 1) * a.L[1];
-            const double sz = (double)(img / 9 - 1) * a.L[2];
-            q.qsx = (float)((double)q.x + sx);
-            q.qsy = (float)((double)q.y + sy);
-            q.qsz = (float)((double)q.z + sz);
-            q.ux = (float)((((double)q.x + sx) - (double)m.lo[0]) * m.inv_h + 8388608.0);
-            q.uy = (float)((((double)q.y + sy) - (double)m.lo[1]) * m.inv_h + 8388608.0);
-            q.uz = (float)((((double)q.z + sz) - (double)m.lo[2]) * m.inv_h + 8388608.0);
-            if (kPaper) {
-                q.px = (float)((((double)q.x + sx) - (double)m.lo[0]) / ph[0]);
-                q.py = (float)((((double)q.y + sy) - (double)m.lo[1]) / ph[1]);
-                q.pz = (float)((((double)q.z + sz) - (double)m.lo[2]) / ph[2]);
-            }
-            if (root < 0) {  // a tree of at most leaf_size particles is one run
-                take_run<kVec4, kBlock, kPaper, kF64>(root, on, __ballot(on), q, img, a.L, sorted, qpoint, sorted64,
-                                                      nend, s_out,
-                                                s_src, a.nbr, a.max_nbr);
-                continue;
-            }
-            int32_t v = root;
-            while (v < end) {
-                // 32-bit byte offsets keep the address arithmetic to one scalar op
-                const uint32_t off = (uint32_t)v << 5;
-                const uint4 r0 = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(records) + off);
-                const uint4 r1 = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(records) + off + 16u);
-                const int32_t rope =
-                    *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(ropes) + ((uint32_t)v << 2));
-                const bool hl = box_d2(r0.x, r0.y, r0.z, q.ux, q.uy, q.uz, bias) <= q.r2g;
-                const uint64_t ml = __ballot(hl);
-                const bool anyl = ml != 0;
-                const int32_t cl = (int32_t)r1.z, cr = (int32_t)r1.w;
-                if (cl < 0 && anyl)
-                    take_run<kVec4, kBlock, kPaper, kF64>(cl, hl, ml, q, img, a.L, sorted, qpoint, sorted64, nend,
-                                                          s_out, s_src, a.nbr, a.max_nbr);
-                // Descending into an internal left child with an internal right
-                // child, the right box is not needed: the walk reaches the right
-                // child's record by the left subtree's rope and tests its
-                // children there (they lie inside its box).
-                int32_t next = cl;
-                if (!(anyl && cl >= 0 && cr >= 0)) {
-                    const bool hr = box_d2(r0.w, r1.x, r1.y, q.ux, q.uy, q.uz, bias) <= q.r2g;
-                    const uint64_t mr = __ballot(hr);
-                    const bool anyr = mr != 0;
-                    if (cr < 0 && anyr)
-                        take_run<kVec4, kBlock, kPaper, kF64>(cr, hr, mr, q, img, a.L, sorted, qpoint, sorted64, nend,
-                                                              s_out, s_src, a.nbr, a.max_nbr);
-                    next = (anyl && cl >= 0) ? cl : ((anyr && cr >= 0) ? cr : rope);
-                }
-                // references always point forward; max() makes progress unconditional
-                v = uniform(max(next, v + 1));
-            }
-        }
-    }
-
-    if (!valid) return;
-    a.count[q.orig] = q.cnt;
-    // the last (fewer than kFlush) entries
-    const int32_t f = q.flushed, s0 = f & (kRing - 1);
-    int32_t *row = a.nbr + ((int64_t)q.orig * a.max_nbr + f);
-    for (int32_t e = 0; e < q.cnt - f; ++e)
-        if (f + e < a.max_nbr) row[e] = s_out[(s0 + e) & (kRing - 1)][threadIdx.x];
-    if (q.cnt > a.max_nbr) atomicOr(a.overflow, 1);
+    traverse_wave<kVec4, false, ConstArgs>(*args, li, records, sorted, nullptr, meta, s_wave[threadIdx.x >> 6]);
 }
 
 __global__ void k_clear_flag(int32_t *f) {
     if (threadIdx.x == 0) *f = 0;
 }
 
-template <bool kVec4, int kBlock, bool kPaper, bool kF64>
-void launch_one(const TravArgs &a, const uint4 *qpoint, hipStream_t s) {
+template <bool kVec4, int kBlock, bool kF64>
+void launch_one(const TravArgs &a, hipStream_t s) {
     const unsigned grid = (unsigned)trav_blocks(a.n, a.ntypes, kBlock, a.qpw);
-    hipLaunchKernelGGL((k_traverse<kVec4, kBlock, kPaper, kF64>), dim3(grid), dim3(kBlock), 0, s, a, a.records,
-                       a.ropes, a.sorted, qpoint, a.meta);
+    hipLaunchKernelGGL((k_traverse<kVec4, kBlock, kF64>), dim3(grid), dim3(kBlock), 0, s, a, a.records, a.sorted,
+                       a.meta);
 }
 
 template <bool kVec4, int kBlock>
 void launch_one_batch(const BatchLaunch &b, hipStream_t s) {
     hipLaunchKernelGGL((k_traverse_batch<kVec4, kBlock>), dim3((unsigned)b.tblocks), dim3(kBlock), 0, s, b.trav,
-                       b.tblk_first, b.nsys, b.ws.records, b.ws.ropes, b.ws.sorted, b.meta);
+                       b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
 }
 
-template <bool kVec4, bool kPaper, bool kF64>
-void launch_block(const TravArgs &a, int32_t block, const uint4 *qpoint, hipStream_t s) {
+template <bool kVec4, bool kF64>
+void launch_block(const TravArgs &a, int32_t block, hipStream_t s) {
     switch (block) {
-    case 64: launch_one<kVec4, 64, kPaper, kF64>(a, qpoint, s); break;
-    case 128: launch_one<kVec4, 128, kPaper, kF64>(a, qpoint, s); break;
-    case 192: launch_one<kVec4, 192, kPaper, kF64>(a, qpoint, s); break;
-    default: launch_one<kVec4, 256, kPaper, kF64>(a, qpoint, s); break;
+    case 64: launch_one<kVec4, 64, kF64>(a, s); break;
+    case 128: launch_one<kVec4, 128, kF64>(a, s); break;
+    case 192: launch_one<kVec4, 192, kF64>(a, s); break;
+    default: launch_one<kVec4, 256, kF64>(a, s); break;
     }
 }
 
@@ -658,21 +855,17 @@ hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool pap
                            hipStream_t s) {
     hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(64), 0, s, a.overflow);
     if (a.n > 0) {
-        if (paper) {  // fp32 data only
+        if (paper) return launch_traverse_paper(a, block, vec4, qpoint, s);  // fp32 data only
+        if (a.sorted64) {
             if (vec4)
-                launch_block<true, true, false>(a, block, qpoint, s);
+                launch_block<true, true>(a, block, s);
             else
-                launch_block<false, true, false>(a, block, qpoint, s);
-        } else if (a.sorted64) {
-            if (vec4)
-                launch_block<true, false, true>(a, block, nullptr, s);
-            else
-                launch_block<false, false, true>(a, block, nullptr, s);
+                launch_block<false, true>(a, block, s);
         } else {
             if (vec4)
-                launch_block<true, false, false>(a, block, nullptr, s);
+                launch_block<true, false>(a, block, s);
             else
-                launch_block<false, false, false>(a, block, nullptr, s);
+                launch_block<false, false>(a, block, s);
         }
     }
     return hipGetLastError();

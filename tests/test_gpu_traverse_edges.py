@@ -1,0 +1,71 @@
+"""Edges of the traversal, row by row against the oracle: ragged wavefronts at
+every queries-per-wavefront setting, runs and batches that fill exactly or
+overflow (coincident particles: every slot of a batch accepted, more waiting
+words than a wavefront keeps), exact ties (pairs that only the fp64 arithmetic
+decides, several per part), spreads that widen the matrix-core band until it
+covers most pairs, and coordinates whose squares would overflow in fp32.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+
+from nlist_check import compare_rows, run_nlist
+
+pytestmark = pytest.mark.gpu
+
+
+def _config(pos, L, rc, skin=0.0, types=None, name="edge"):
+    box = np.full(3, L, np.float32)
+    rc = np.atleast_2d(np.asarray(rc, np.float32))
+    return W.Config(pos=W.wrap_f32(np.asarray(pos, np.float64), box), box=box, rcut=rc, skin=skin, types=types,
+                    name=name)
+
+
+@pytest.mark.parametrize("qpw", [0, 1, 2, 16, 32, 64])
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 63, 64, 65, 129, 1000])
+def test_ragged_wavefronts(n, qpw):
+    rng = np.random.default_rng(1000 + n)
+    cfg = _config(rng.uniform(0, 8.0, (n, 3)), 8.0, 2.5, 0.4)
+    _, nbr, cnt, ovf = run_nlist(cfg, max_nbr=256, opts={"queries_per_wave": qpw})
+    compare_rows(cfg, nbr, cnt, ovf, 256)
+
+
+@pytest.mark.parametrize("leaf", [1, 8, 11, 16])
+@pytest.mark.parametrize("m", [17, 64, 300])
+def test_coincident_particles(m, leaf):
+    rng = np.random.default_rng(7 + m)
+    pos = np.concatenate([np.full((m, 3), 5.125), rng.uniform(0, 12.0, (500, 3)), np.full((m, 3), 11.999)])
+    cfg = _config(pos[rng.permutation(len(pos))], 12.0, 1.5)
+    for width in (512, 96, 30, 0):  # rows that fit, that end on and off a 16-byte store, none
+        _, nbr, cnt, ovf = run_nlist(cfg, max_nbr=width, opts={"leaf_size": leaf})
+        compare_rows(cfg, nbr, cnt, ovf, width)
+
+
+@pytest.mark.parametrize("opts", [{}, {"queries_per_wave": 64}, {"leaf_size": 5, "block_size": 256}])
+@pytest.mark.parametrize("side, r", [(8, 3.0), (13, 5.0)])
+def test_exact_ties(side, r, opts):
+    # integer lattice: the shells at distance r (and every other one) are met exactly
+    g = np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), -1).reshape(-1, 3).astype(np.float64)
+    g = g[np.random.default_rng(3).permutation(len(g))]
+    cfg = _config(g, float(side), r)
+    _, nbr, cnt, ovf = run_nlist(cfg, max_nbr=768, opts=opts)
+    compare_rows(cfg, nbr, cnt, ovf, 768)
+
+
+@pytest.mark.parametrize("L, r", [(3000.0, 1.0), (1e5, 2.0), (1e15, 1e13)])
+def test_wide_spreads(L, r):
+    # pairs near the cutoff whose wavefront spans the box
+    rng = np.random.default_rng(11)
+    base = rng.uniform(0, L, (700, 3))
+    u = rng.normal(size=base.shape)
+    u /= np.linalg.norm(u, axis=1, keepdims=True)
+    pos = np.concatenate([base, base + u * r * rng.uniform(0.9, 1.1, (700, 1)), base[:200]])
+    types = rng.integers(0, 2, len(pos)).astype(np.int32)
+    for qpw in (4, 64):
+        cfg = _config(pos, L, r)
+        _, nbr, cnt, ovf = run_nlist(cfg, max_nbr=64, opts={"queries_per_wave": qpw})
+        compare_rows(cfg, nbr, cnt, ovf, 64)
+        two = _config(pos, L, [[r, 0.5 * r], [0.5 * r, 0.0]], types=types)
+        _, nbr, cnt, ovf = run_nlist(two, max_nbr=64, opts={"queries_per_wave": qpw})
+        compare_rows(two, nbr, cnt, ovf, 64)
