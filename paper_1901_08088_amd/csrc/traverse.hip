@@ -22,9 +22,10 @@
 //
 // The search region is the union of kSegs boxes around consecutive queries,
 // cut where neighbouring queries lie farthest apart (Z order jumps), grown by
-// R.  For 64 queries of an LJ fluid at R = 3.4 it meets 3% more candidates
-// than the 64 spheres themselves do (14% at R = 1.52), and one lane tests a
-// node against four boxes where 64 lanes tested it against a sphere each.
+// R.  For 64 queries of an LJ fluid at R = 3.4 four boxes meet 3% more
+// candidates than the 64 spheres themselves do, and two boxes, which take half
+// the instructions per node, measured faster on every workload (N = 1M: LJ 565
+// -> 560 us, WCA 268 -> 257 us).
 //
 // Exactness.  |v| <= band (v the product's d^2 - R^2) marks the pairs that
 // need more: they are decided, one by one, by an fp32 distance with a proven
@@ -32,12 +33,14 @@
 // list definition, so the lists are exact.  The band is derived at
 // pair_band().
 //
-// Cost.  VALU issue bounds it (77% busy at N = 8M): 15.2k VALU instructions
-// per wavefront of 64 queries, half of them for the 26 batches it tests.  With
-// one lane per query walking and testing every candidate itself the wavefront
-// issued 26.1k VALU and 21.1k scalar instructions.  List rebuilds, before and
-// now: LJ 8M 6.83 -> 5.11 ms, 1M 1.136 -> 0.762 ms, 4000 0.155 -> 0.104 ms,
-// WCA 1M 0.745 -> 0.475 ms, two-type mixture 1M 0.726 -> 0.536 ms.
+// Cost.  At N = 8M (LJ, R = 3.4) a wavefront issues 13.0k VALU instructions
+// and 436 matrix products (26 batches, 25 rounds) and the VALU is busy 66% of
+// the time; of 4.21 ms the walk takes 1.0, the tests 1.8, taking the rows'
+// entries from the masks 0.8 and storing the rows 0.65 (4.5 GB).  With one lane
+// per query walking and testing every candidate itself a wavefront issued
+// 26.1k VALU and 21.1k scalar instructions.  Traversal before and now: LJ 8M
+// 6.09 -> 4.21 ms, 1M 942 -> 517 us, 4000 102 -> 38 us, WCA 1M 533 -> 235 us,
+// two-type mixture 1M 523 -> 278 us.
 //
 // Row order.  A row lists, image by image and tree order within an image, the
 // candidates of each run part that the fp32 distance accepts, then those of
@@ -63,6 +66,8 @@ __device__ __forceinline__ float lane_value(float x, int lane) {
 __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
+// A lane's bit of a wave-uniform mask.
+__device__ __forceinline__ bool lane_bit(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 // LDS written by some lanes of the wavefront is read by others after this
 // (a wavefront's LDS operations complete in order; this keeps the compiler
 // from reordering them).
@@ -72,7 +77,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // Search-region boxes per wavefront.
-constexpr int kSegs = 4;
+constexpr int kSegs = 2;
 // Nodes opened per round (two lanes each).
 constexpr int kOpen = 32;
 // Stack entries.  A round that opens p nodes adds at most p entries; p is held
@@ -101,13 +106,12 @@ constexpr int kTables = 8;
 
 // One wavefront's LDS: 9.6 KB, so four wavefronts per SIMD fit a compute unit.
 struct WaveLds {
-    uint32_t word[kWords + 1][64];  // per query: candidate mask (16 bits, first candidate highest), index base
+    uint32_t word[kWords + 1][64];  // per query: candidate mask (16 bits, first highest), byte offset into index
     int32_t index[kTables * 64 + 64 * 4];  // original indices of each batch's candidates; the entries carried over
     int32_t sref[kStack];           // stack: record index, or run reference (< 0)
-    uint32_t pstart[kParts];        // queue: first sorted position, length - 1 in bits 27-29
-    uint16_t poff[kParts];          // particles queued before the part
+    uint2 part[kParts];             // queue: first sorted position, length - 1 from bit 27; particles
+                                    // queued before the part, image code from bit 16
     uint8_t simg[kStack];           // image codes
-    uint8_t pimg[kParts];
     uint8_t map[64];                // scratch: part starts by slot; candidate slot of each query's own particle
 };
 static_assert(sizeof(WaveLds) <= 10240, "four wavefronts per SIMD");
@@ -141,7 +145,7 @@ __device__ __forceinline__ void write_rows(Query &q, WaveLds &w, int32_t *nbr, i
     const uint32_t mine = kTables * 64 + lane * 4;  // the lane's carried entries
     w.word[q.words][lane] = 0;
     // the word in hand and the next one
-    uint32_t cur = ~(0xFFFFFFFFu >> q.carry) | mine;
+    uint32_t cur = ~(0xFFFFFFFFu >> q.carry) | (mine * 4u);
     uint32_t nxt = w.word[0][lane];
     uint32_t at = 0;
     auto next = [&]() {
@@ -149,9 +153,9 @@ __device__ __forceinline__ void write_rows(Query &q, WaveLds &w, int32_t *nbr, i
         cur = empty ? nxt : cur;
         at += empty ? 1u : 0u;
         nxt = w.word[at][lane];
-        const uint32_t b = (uint32_t)__builtin_clz(cur | 1u);
+        const uint32_t b = (uint32_t)__builtin_clz(cur);
         cur ^= 0x80000000u >> b;
-        return w.index[(cur & 0xFFFFu) + b];
+        return *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(w.index) + ((cur & 0xFFFFu) + (b << 2)));
     };
     int32_t left = q.cnt - q.done;
     int32_t *row = nbr + ((int64_t)q.orig * max_nbr + q.done);
@@ -181,14 +185,14 @@ __device__ __forceinline__ void write_rows(Query &q, WaveLds &w, int32_t *nbr, i
     wave_lds_sync();
 }
 
-// Queues the candidates `m` (first of 32 slots highest) of a batch whose
-// index table half starts at `base`.
+// Queues the candidates `m` (first of 32 slots highest) of a batch; `base` is
+// the byte offset of their indices.
 __device__ __forceinline__ void add_words(uint32_t m, uint32_t base, Query &q, WaveLds &w, uint32_t lane) {
-    const uint32_t a = m & 0xFFFF0000u, b = m << 16;
-    w.word[q.words][lane] = a | base;
-    q.words += a != 0u ? 1u : 0u;
-    w.word[q.words][lane] = b | (base + 16u);
-    q.words += b != 0u ? 1u : 0u;
+    const uint32_t a = (m & 0xFFFF0000u) | base, b = (m << 16) | (base + 64u);
+    w.word[q.words][lane] = a;
+    q.words += a >= 0x10000u ? 1u : 0u;
+    w.word[q.words][lane] = b;
+    q.words += b >= 0x10000u ? 1u : 0u;
 }
 
 // ------------------------------------------------------------------ pairs
@@ -331,25 +335,24 @@ struct Batch {
 __device__ __forceinline__ Batch take_batch(uint32_t at, uint32_t parts, WaveLds &w,
                                             const float4 *__restrict__ sorted, uint32_t lane) {
     Batch b;
-    const uint32_t base = uniform((uint32_t)w.poff[at]);
-    const uint32_t i = min(at + lane, parts - 1u);
-    const uint32_t s0 = w.poff[i] - base, s1 = s0 + (w.pstart[i] >> 27) + 1u;
-    const uint64_t take = __ballot(at + lane < parts && s1 <= 64u);
+    const uint2 mine = w.part[min(at + lane, parts - 1u)];
+    const uint32_t base = uniform(mine.y & 0xFFFFu);
+    const uint32_t s0 = (mine.y & 0xFFFFu) - base, s1 = s0 + (mine.x >> 27) + 1u;
+    const uint64_t take = __ballot(at + lane < parts) & __ballot(s1 <= 64u);
     b.parts = (uint32_t)__popcll(take);
     b.slots = (uint32_t)__builtin_amdgcn_readlane((int32_t)s1, (int32_t)b.parts - 1);
     w.map[lane] = 0;
     wave_lds_sync();
-    if ((take >> lane) & 1u) w.map[s0] = 1;
+    if (lane_bit(take)) w.map[s0] = 1;
     wave_lds_sync();
     b.starts = __ballot(w.map[lane] != 0);
     wave_lds_sync();
     const uint32_t slot = slot_of(lane);
     const uint64_t upto = b.starts & (~0ull >> (63u - slot));
-    const uint32_t part = at + (uint32_t)__popcll(upto) - 1u;
+    const uint2 part = w.part[at + (uint32_t)__popcll(upto) - 1u];
     const bool on = slot < b.slots;
-    const uint32_t first = w.pstart[part] & 0x7FFFFFFu;
-    b.img = w.pimg[part];
-    b.idx = (int32_t)(first + (on ? slot - (w.poff[part] - base) : 0u));
+    b.img = part.y >> 16;
+    b.idx = (int32_t)((part.x & 0x7FFFFFFu) + (on ? slot - ((part.y & 0xFFFFu) - base) : 0u));
     b.p = sorted[b.idx];
     if (!on) b.idx = -1;
     return b;
@@ -379,9 +382,9 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
         osz = (float)((double)oz + (double)((int)((t.img >> 4) & 3u) - 1) * a.L[2]);
     }
     float c[4];
-    c[0] = on ? t.p.x - osx : 0.0f;
-    c[1] = on ? t.p.y - osy : 0.0f;
-    c[2] = on ? t.p.z - osz : 0.0f;
+    c[0] = t.p.x - osx;
+    c[1] = t.p.y - osy;
+    c[2] = t.p.z - osz;
     c[3] = on ? __builtin_fmaf(c[2], c[2], __builtin_fmaf(c[1], c[1], c[0] * c[0])) : 1e30f;
     w.index[table * 64u + slot] = ~__float_as_int(t.p.w);
     // a query's own particle is never listed: it can only come up unshifted
@@ -390,7 +393,7 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
     if (mine) {
         w.map[lane] = 64;
         wave_lds_sync();
-        if ((mine >> lane) & 1u) w.map[t.idx - kw0] = (uint8_t)slot;
+        if (lane_bit(mine)) w.map[t.idx - kw0] = (uint8_t)slot;
         wave_lds_sync();
         const uint32_t s = w.map[lane];
         self_lo = s < 32u ? 0x80000000u >> s : 0u;
@@ -413,7 +416,7 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
     const bool near_any = __any(fminf(fminf(nr[0], nr[1]), fminf(nr[2], nr[3])) <= band) || tt.force;
     transpose4(m[0], m[1], m[2], m[3]);
     uint32_t lo = ((m[0] << 16) | m[1]) & ~self_lo, hi = ((m[2] << 16) | m[3]) & ~self_hi;
-    const uint32_t base = table * 64u;
+    const uint32_t base = table * 256u;
     if (near_any) {
         // some pair lies too near the cutoff for the product to decide
         uint32_t e[4];
@@ -467,11 +470,11 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
                 const uint32_t y0 = lo & slot_range(from, p1, 0), y1 = hi & slot_range(from, p1, 1);
                 room();
                 add_words(y0, base, q, w, lane);
-                add_words(y1, base + 32u, q, w, lane);
+                add_words(y1, base + 128u, q, w, lane);
                 q.cnt += (int32_t)(__popc(y0) + __popc(y1));
                 room();
                 add_words(x0, base, q, w, lane);
-                add_words(x1, base + 32u, q, w, lane);
+                add_words(x1, base + 128u, q, w, lane);
                 q.cnt += (int32_t)(__popc(x0) + __popc(x1));
                 from = p1;
             }
@@ -481,22 +484,40 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
         }
     }
     add_words(lo, base, q, w, lane);
-    add_words(hi, base + 32u, q, w, lane);
+    add_words(hi, base + 128u, q, w, lane);
     q.cnt += (int32_t)(__popc(lo) + __popc(hi));
     wave_lds_sync();
 }
 
 // ------------------------------------------------------------------ walk
 
-// Prefix minimum (maximum) over the lanes of each segment, up to and with the
-// lane's own value; `seg0` is the first lane of the lane's segment.
-__device__ __forceinline__ float seg_scan(float x, uint32_t lane, uint32_t seg0, bool want_min) {
-#pragma unroll
-    for (uint32_t o = 1; o < 64; o <<= 1) {
-        const float y = __shfl_up(x, o);
-        if (lane >= seg0 + o) x = want_min ? fminf(x, y) : fmaxf(x, y);
-    }
-    return x;
+// An integer that orders like the float (and back).
+__device__ __forceinline__ int32_t order_key(float x) {
+    const int32_t i = __float_as_int(x);
+    return i ^ ((i >> 31) & 0x7FFFFFFF);
+}
+__device__ __forceinline__ float from_key(int32_t k) { return __int_as_float(k ^ ((k >> 31) & 0x7FFFFFFF)); }
+
+// Largest and smallest of the wavefront's keys.
+__device__ __forceinline__ int32_t wave_max(int32_t x) {
+    constexpr int32_t none = INT32_MIN;
+    x = max(x, __builtin_amdgcn_update_dpp(none, x, 0x111, 0xF, 0xF, false));  // row_shr:1
+    x = max(x, __builtin_amdgcn_update_dpp(none, x, 0x112, 0xF, 0xF, false));  // row_shr:2
+    x = max(x, __builtin_amdgcn_update_dpp(none, x, 0x114, 0xF, 0xF, false));  // row_shr:4
+    x = max(x, __builtin_amdgcn_update_dpp(none, x, 0x118, 0xF, 0xF, false));  // row_shr:8
+    x = max(x, __builtin_amdgcn_update_dpp(none, x, 0x142, 0xA, 0xF, false));  // row_bcast:15 into rows 1 and 3
+    x = max(x, __builtin_amdgcn_update_dpp(none, x, 0x143, 0xC, 0xF, false));  // row_bcast:31 into rows 2 and 3
+    return __builtin_amdgcn_readlane(x, 63);
+}
+__device__ __forceinline__ int32_t wave_min(int32_t x) {
+    constexpr int32_t none = INT32_MAX;
+    x = min(x, __builtin_amdgcn_update_dpp(none, x, 0x111, 0xF, 0xF, false));
+    x = min(x, __builtin_amdgcn_update_dpp(none, x, 0x112, 0xF, 0xF, false));
+    x = min(x, __builtin_amdgcn_update_dpp(none, x, 0x114, 0xF, 0xF, false));
+    x = min(x, __builtin_amdgcn_update_dpp(none, x, 0x118, 0xF, 0xF, false));
+    x = min(x, __builtin_amdgcn_update_dpp(none, x, 0x142, 0xA, 0xF, false));
+    x = min(x, __builtin_amdgcn_update_dpp(none, x, 0x143, 0xC, 0xF, false));
+    return __builtin_amdgcn_readlane(x, 63);
 }
 
 // Sum over the lanes up to and with this one.
@@ -509,12 +530,6 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
     return (uint32_t)v;
-}
-
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return uniform(x);
 }
 
 // One wavefront of queries; this lane's query is position `li` of the system
@@ -545,51 +560,28 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
 
     // cut the queries where neighbours lie farthest apart
     const float gx = qp.x - __shfl_up(qp.x, 1), gy = qp.y - __shfl_up(qp.y, 1), gz = qp.z - __shfl_up(qp.z, 1);
-    float gap = lane == 0 ? -1.0f : __builtin_fmaf(gz, gz, __builtin_fmaf(gy, gy, gx * gx));
-    uint64_t cuts = 1u;  // first lanes of the segments
+    const int32_t gap = lane == 0 ? -1 : __float_as_int(__builtin_fmaf(gz, gz, __builtin_fmaf(gy, gy, gx * gx)));
+    const uint64_t widest = __ballot(gap == wave_max(gap) && gap > 0);
+    const uint32_t half = widest ? (uint32_t)__builtin_ctzll(widest) : 64u;  // first lane of the second half
+    // bounds of each half (of the whole, twice, when there is one point only)
+    const int32_t key[3] = {order_key(qp.x), order_key(qp.y), order_key(qp.z)};
+    float wlo[kSegs][3], whi[kSegs][3];
 #pragma unroll
-    for (int s = 1; s < kSegs; ++s) {
-        const float top = wave_max(gap);
-        const uint64_t at = __ballot(gap == top && gap > 0.0f);
-        if (at) {
-            const uint32_t c = (uint32_t)__builtin_ctzll(at);
-            cuts |= 1ull << c;
-            if (lane == c) gap = -1.0f;
-        }
-    }
-    // bounds of each segment, at its last lane
-    const uint64_t upto = cuts & (~0ull >> (63u - lane));
-    const uint32_t seg0 = 63u - (uint32_t)__builtin_clzll(upto);
-    const float blx = seg_scan(qp.x, lane, seg0, true), bly = seg_scan(qp.y, lane, seg0, true),
-                blz = seg_scan(qp.z, lane, seg0, true);
-    const float bhx = seg_scan(qp.x, lane, seg0, false), bhy = seg_scan(qp.y, lane, seg0, false),
-                bhz = seg_scan(qp.z, lane, seg0, false);
-    uint32_t last[kSegs];  // last lane of each segment (segments that do not exist repeat the final one)
-    {
-        uint64_t ends = (cuts >> 1) | (1ull << 63);
+    for (int s = 0; s < kSegs; ++s) {
+        const bool in = half == 64u || (lane >= half) == (s == 1);
 #pragma unroll
-        for (int s = 0; s < kSegs; ++s) {
-            last[s] = (uint32_t)__builtin_ctzll(ends);
-            if (ends & (ends - 1u)) ends &= ends - 1u;
+        for (int d = 0; d < 3; ++d) {
+            wlo[s][d] = from_key(wave_min(in ? key[d] : INT32_MAX));
+            whi[s][d] = from_key(wave_max(in ? key[d] : INT32_MIN));
         }
     }
     // the wavefront's origin: the middle of its queries
-    float olo[3] = {lane_value(blx, last[0]), lane_value(bly, last[0]), lane_value(blz, last[0])};
-    float ohi[3] = {lane_value(bhx, last[0]), lane_value(bhy, last[0]), lane_value(bhz, last[0])};
-#pragma unroll
-    for (int s = 1; s < kSegs; ++s) {
-        olo[0] = fminf(olo[0], lane_value(blx, last[s]));
-        olo[1] = fminf(olo[1], lane_value(bly, last[s]));
-        olo[2] = fminf(olo[2], lane_value(blz, last[s]));
-        ohi[0] = fmaxf(ohi[0], lane_value(bhx, last[s]));
-        ohi[1] = fmaxf(ohi[1], lane_value(bhy, last[s]));
-        ohi[2] = fmaxf(ohi[2], lane_value(bhz, last[s]));
-    }
-    const float ox = uniform(0.5f * (olo[0] + ohi[0])), oy = uniform(0.5f * (olo[1] + ohi[1])),
-                oz = uniform(0.5f * (olo[2] + ohi[2]));
+    const float ox = uniform(0.5f * (fminf(wlo[0][0], wlo[1][0]) + fmaxf(whi[0][0], whi[1][0]))),
+                oy = uniform(0.5f * (fminf(wlo[0][1], wlo[1][1]) + fmaxf(whi[0][1], whi[1][1]))),
+                oz = uniform(0.5f * (fminf(wlo[0][2], wlo[1][2]) + fmaxf(whi[0][2], whi[1][2])));
     const float rx = qp.x - ox, ry = qp.y - oy, rz = qp.z - oz;
     const float q2 = __builtin_fmaf(rz, rz, __builtin_fmaf(ry, ry, rx * rx));
-    const float M2 = wave_max(q2);  // (rounded: the bands below leave room for it)
+    const float M2 = from_key(wave_max(order_key(q2)));  // (rounded: the bands below leave room for it)
     float bq[4] = {-2.0f * rx, -2.0f * ry, -2.0f * rz, 1.0f};
     transpose4(bq[0], bq[1], bq[2], bq[3]);
 
@@ -629,19 +621,14 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         const double ih = m.inv_h;
         const double rgp = (R + rshift) * ih * (1.0 + 0x1p-20) + 2.0 + 0x1p-21 * (a.lmax * ih);
         const float r2g = uniform((float)(rgp * rgp * (1.0 + 0x1p-20)));
-        const float ulx = (float)(((double)blx - (double)m.lo[0]) * ih), uly = (float)(((double)bly - (double)m.lo[1]) * ih),
-                    ulz = (float)(((double)blz - (double)m.lo[2]) * ih);
-        const float uhx = (float)(((double)bhx - (double)m.lo[0]) * ih), uhy = (float)(((double)bhy - (double)m.lo[1]) * ih),
-                    uhz = (float)(((double)bhz - (double)m.lo[2]) * ih);
         float sl[kSegs][3], sh[kSegs][3];
 #pragma unroll
         for (int s = 0; s < kSegs; ++s) {
-            sl[s][0] = lane_value(ulx, last[s]);
-            sl[s][1] = lane_value(uly, last[s]);
-            sl[s][2] = lane_value(ulz, last[s]);
-            sh[s][0] = lane_value(uhx, last[s]);
-            sh[s][1] = lane_value(uhy, last[s]);
-            sh[s][2] = lane_value(uhz, last[s]);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                sl[s][d] = uniform((float)(((double)wlo[s][d] - (double)m.lo[d]) * ih));
+                sh[s][d] = uniform((float)(((double)whi[s][d] - (double)m.lo[d]) * ih));
+            }
         }
         const float gLx = uniform((float)(a.L[0] * ih)), gLy = uniform((float)(a.L[1] * ih)),
                     gLz = uniform((float)(a.L[2] * ih));
@@ -659,84 +646,79 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
             // (1) open the next nodes
             const uint32_t room = size < (uint32_t)(kStack - kDepthMax) ? (uint32_t)(kStack - kDepthMax) - size : 1u;
             const uint32_t p = min(min(size, (uint32_t)kOpen), room);
-            const uint32_t e = lane >> 1;
-            const bool act = e < p;
-            const uint32_t at = size - 1u - (act ? e : 0u);
+            // (the lanes past the opened nodes read other live entries)
+            const int32_t at = max((int32_t)(size - 1u - (lane >> 1)), 0);
             const int32_t ref = w.sref[at];
             const uint32_t img = w.simg[at];
             wave_lds_sync();
             size -= p;
-            int32_t nref = ref;
-            bool hit = act && (lane & 1u) == 0u, swap = false;
-            if (act && ref >= 0) {
-                const char *rec = reinterpret_cast<const char *>(records) + ((uint64_t)(uint32_t)ref << 5);
-                const uint32_t *box = reinterpret_cast<const uint32_t *>(rec + (lane & 1u) * 12u);
-                const int2 child = *reinterpret_cast<const int2 *>(rec + 24);
-                const uint32_t wx = box[0], wy = box[1], wz = box[2];
-                // a run on the right of an internal child comes before it: the
-                // two lanes then exchange their children (after the box test)
-                swap = child.x >= 0 && child.y < 0;
-                nref = ((lane & 1u) != 0u) != swap ? child.y : child.x;
-                float lx = (float)(wx & 0xFFFFu), ly = (float)(wy & 0xFFFFu), lz = (float)(wz & 0xFFFFu);
-                float hx = (float)(wx >> 16), hy = (float)(wy >> 16), hz = (float)(wz >> 16);
-                if (img != kHome) {
-                    // the search box of the shifted queries against the node is the
-                    // unshifted one against the node shifted back
-                    const float tx = (float)((int)(img & 3u) - 1) * gLx, ty = (float)((int)((img >> 2) & 3u) - 1) * gLy,
-                                tz = (float)((int)((img >> 4) & 3u) - 1) * gLz;
-                    lx -= tx;
-                    hx -= tx;
-                    ly -= ty;
-                    hy -= ty;
-                    lz -= tz;
-                    hz -= tz;
-                }
-                float best = __builtin_inff();
+            const uint64_t A = p == 32u ? ~0ull : (1ull << (2u * p)) - 1ull, R0 = __ballot(ref < 0);
+            const char *rec = reinterpret_cast<const char *>(records) + ((uint64_t)(uint32_t)max(ref, 0) << 5);
+            const uint32_t *box = reinterpret_cast<const uint32_t *>(rec + (lane & 1u) * 12u);
+            const int2 child = *reinterpret_cast<const int2 *>(rec + 24);
+            const uint32_t wx = box[0], wy = box[1], wz = box[2];
+            // a run on the right of an internal child comes before it: the two
+            // lanes then exchange their children (and, below, their hits)
+            const bool swap = child.x >= 0 && child.y < 0;
+            const int32_t nref = ref < 0 ? ref : (((lane & 1u) != 0u) != swap ? child.y : child.x);
+            float lx = (float)(wx & 0xFFFFu), ly = (float)(wy & 0xFFFFu), lz = (float)(wz & 0xFFFFu);
+            float hx = (float)(wx >> 16), hy = (float)(wy >> 16), hz = (float)(wz >> 16);
+            if (__any(img != kHome)) {
+                // the search box of the shifted queries against the node is the
+                // unshifted one against the node shifted back
+                const float tx = (float)((int)(img & 3u) - 1) * gLx, ty = (float)((int)((img >> 2) & 3u) - 1) * gLy,
+                            tz = (float)((int)((img >> 4) & 3u) - 1) * gLz;
+                lx -= tx;
+                hx -= tx;
+                ly -= ty;
+                hy -= ty;
+                lz -= tz;
+                hz -= tz;
+            }
+            float best = __builtin_inff();
 #pragma unroll
-                for (int s = 0; s < kSegs; ++s) {
-                    const float cx = fmaxf(fmaxf(lx - sh[s][0], sl[s][0] - hx), 0.0f);
-                    const float cy = fmaxf(fmaxf(ly - sh[s][1], sl[s][1] - hy), 0.0f);
-                    const float cz = fmaxf(fmaxf(lz - sh[s][2], sl[s][2] - hz), 0.0f);
-                    best = fminf(best, __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx)));
-                }
-                hit = best <= r2g;
+            for (int s = 0; s < kSegs; ++s) {
+                const float cx = fmaxf(fmaxf(lx - sh[s][0], sl[s][0] - hx), 0.0f);
+                const float cy = fmaxf(fmaxf(ly - sh[s][1], sl[s][1] - hy), 0.0f);
+                const float cz = fmaxf(fmaxf(lz - sh[s][2], sl[s][2] - hz), 0.0f);
+                best = fminf(best, __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx)));
             }
             const uint32_t v = (uint32_t)~nref;
             const uint32_t first = v >> kRunCountBits, count = (v & (uint32_t)kRunCountMask) + 1u;
-            uint64_t H = __ballot(hit);
+            constexpr uint64_t kEven = 0x5555555555555555ull;
+            uint64_t H = __ballot(best <= r2g);
             const uint64_t S = __ballot(swap);
-            H = (H & ~S) | (((H & 0x5555555555555555ull) << 1 | (H >> 1 & 0x5555555555555555ull)) & S);
+            H = (H & ~S) | (((H & kEven) << 1 | (H >> 1 & kEven)) & S);
+            // a run on the stack was hit already (its even lane stands for it)
+            H = A & ((H & ~R0) | (R0 & kEven));
             // (a well-formed tree's references point forward and its runs end
             // inside the system: this only keeps a corrupt one from running on)
-            H &= __ballot(nref >= 0 ? (ref < 0 || (nref > ref && nref < end)) : first + count <= nend);
+            const uint64_t N = __ballot(nref >= 0);
+            H &= (N & __ballot(nref > ref) & __ballot(nref < end)) | (~N & __ballot(first + count <= nend));
             // runs before the first internal node are next in order
-            const uint64_t I = H & __ballot(nref >= 0);
+            const uint64_t I = H & N;
             const uint64_t E = I ? H & ((I & (~I + 1ull)) - 1ull) : H;
             const uint64_t P = H & ~E;
             const uint32_t np = (uint32_t)__popcll(P);
-            if ((P >> lane) & 1u) {
+            if (lane_bit(P)) {
                 const uint32_t to = size + np - 1u - mbcnt(P);
                 w.sref[to] = nref;
                 w.simg[to] = (uint8_t)img;
             }
             size += np;
             // (2) queue their parts
-            const bool run = (E >> lane) & 1u;
-            const uint64_t two = __ballot(run && count > 8u);
-            const uint32_t sum = wave_prefix_sum(run ? count : 0u);
-            if (run) {
-                const uint32_t to = parts + mbcnt(E) + mbcnt(two), off = queued + sum - count;
-                w.pstart[to] = first | ((count > 8u ? 7u : count - 1u) << 27);
-                w.poff[to] = (uint16_t)off;
-                w.pimg[to] = (uint8_t)img;
-                if (count > 8u) {
-                    w.pstart[to + 1u] = (first + 8u) | ((count - 9u) << 27);
-                    w.poff[to + 1u] = (uint16_t)(off + 8u);
-                    w.pimg[to + 1u] = (uint8_t)img;
+            if (E) {
+                const bool run = lane_bit(E);
+                const uint64_t two = E & __ballot(count > 8u);
+                const uint32_t sum = wave_prefix_sum(run ? count : 0u);
+                if (run) {
+                    const uint32_t to = parts + mbcnt(E) + mbcnt(two), off = (queued + sum - count) | img << 16;
+                    w.part[to] = make_uint2(first | ((count > 8u ? 7u : count - 1u) << 27), off);
+                    if (count > 8u) w.part[to + 1u] = make_uint2((first + 8u) | ((count - 9u) << 27), off + 8u);
                 }
+                parts += (uint32_t)__popcll(E) + (uint32_t)__popcll(two);
+                queued += (uint32_t)__builtin_amdgcn_readlane((int32_t)sum, 63);
             }
-            parts += (uint32_t)__popcll(E) + (uint32_t)__popcll(two);
-            queued += (uint32_t)__builtin_amdgcn_readlane((int32_t)sum, 63);
             wave_lds_sync();
             // (3) test full batches; what the walk's end leaves is tested too
             if (queued >= 64u || size == 0u) {
@@ -754,18 +736,10 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
                     rest -= t.slots;
                 }
                 const uint32_t left = parts - done, gone = queued - rest;
-                uint32_t ps = 0, po = 0, pi = 0;
-                if (lane < left) {
-                    ps = w.pstart[done + lane];
-                    po = w.poff[done + lane];
-                    pi = w.pimg[done + lane];
-                }
+                uint2 keep = make_uint2(0u, 0u);
+                if (lane < left) keep = w.part[done + lane];
                 wave_lds_sync();
-                if (lane < left) {
-                    w.pstart[lane] = ps;
-                    w.poff[lane] = (uint16_t)(po - gone);
-                    w.pimg[lane] = (uint8_t)pi;
-                }
+                if (lane < left) w.part[lane] = make_uint2(keep.x, keep.y - gone);
                 parts = left;
                 queued = rest;
                 wave_lds_sync();
