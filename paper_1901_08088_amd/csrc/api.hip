@@ -203,7 +203,6 @@ int launch_list(const Workspace &w, int32_t n, int32_t ntypes, const qbvh_opts_t
                 int32_t max_nbr, int32_t mode, int32_t *d_nbr, int32_t *d_count, int32_t *d_overflow,
                 hipStream_t s) {
     a.records = w.records;
-    a.ropes = w.ropes;
     a.sorted = w.sorted;
     a.meta = w.meta;
     a.nbr = d_nbr;

@@ -331,7 +331,6 @@ void fill_table(const BatchCtx &c, int32_t nsys, const qbvh_system_t *sys, const
         q.ext_floor = lmax * 0x1p-24;
         TravArgs a = trav[s];
         a.records = c.ws.records;
-        a.ropes = c.ws.ropes;
         a.sorted = c.ws.sorted;
         a.meta = meta_dev + (size_t)s * QBVH_MAX_TYPES;
         a.start = off;

@@ -703,14 +703,14 @@ size_t workspace_bytes(int32_t cap) {
     size_t b = 0;
     b += 4 * al(c * 4);                       // keys, vals, keys2, vals2
     b += al(256 * tiles * 4) + al(256 * 4);   // histograms
-    b += al((c + kSortedPad) * 16);           // sorted (+ padding read by whole-run loads)
+    b += al(c * 16);                         // sorted
     b += 6 * al(c * 4);                       // left right rf rl parent leaf_parent
     b += al(c * 4);                           // visit (split weights, then kept flags)
     b += al(c * 4);                           // cost (subtree collapse)
     b += al(c * 32);                          // boxes (lower and upper bound per node)
     b += al((c + 1) * 4) + al(sb * 4);        // kept + scan partials
     b += al(c * 32) + al(c * 4);              // records + ropes
-    b += al((c + kSortedPad) * 16);           // cell boxes (paper-mode lists)
+    b += al(c * 16);                          // cell boxes (paper-mode lists)
     b += al(QBVH_MAX_TYPES * sizeof(TreeMeta)) + al(QBVH_MAX_TYPES * 4) + al(4);
     const size_t nf = (size_t)fit_chunks0((int32_t)c);
     b += 2 * (al(nf * kFrontierCap * 4) + al(nf * 4));  // tree-build frontiers (ping-pong)
@@ -737,7 +737,7 @@ void workspace_carve(Workspace &w, void *base, int32_t cap) {
     w.vals2 = (uint32_t *)take(c * 4);
     w.hist = (uint32_t *)take(256 * tiles * 4);
     w.digit_total = (uint32_t *)take(256 * 4);
-    w.sorted = (float4 *)take((c + kSortedPad) * 16);
+    w.sorted = (float4 *)take(c * 16);
     w.left = (int32_t *)take(c * 4);
     w.right = (int32_t *)take(c * 4);
     w.rf = (int32_t *)take(c * 4);
@@ -750,7 +750,7 @@ void workspace_carve(Workspace &w, void *base, int32_t cap) {
     w.kept = (uint32_t *)take((c + 1) * 4);
     w.scan_part = (uint32_t *)take(sb * 4);
     w.records = (uint4 *)take(c * 32);
-    w.qpoint = (uint4 *)take((c + kSortedPad) * 16);
+    w.qpoint = (uint4 *)take(c * 16);
     w.ropes = (int32_t *)take(c * 4);
     w.meta = (TreeMeta *)take(QBVH_MAX_TYPES * sizeof(TreeMeta));
     w.type_count = (uint32_t *)take(QBVH_MAX_TYPES * 4);

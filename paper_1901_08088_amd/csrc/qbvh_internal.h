@@ -38,12 +38,6 @@ struct TreeMeta {
 };
 static_assert(sizeof(TreeMeta) == 64, "TreeMeta is 64 bytes");
 
-// The traversal loads the particles of a leaf run 8 float4 at a time from the
-// run's start and from its ninth particle, whatever the run's length; the
-// sorted array carries this many spare entries after its last particle so
-// those loads stay inside the buffer.
-constexpr int32_t kSortedPad = 16;
-
 // Device workspace of one built tree (all arrays sized for `cap` particles).
 struct Workspace {
     int32_t cap = 0;
@@ -54,7 +48,7 @@ struct Workspace {
     uint32_t *keys2 = nullptr, *vals2 = nullptr;  // sort ping-pong; keys2 then holds the tree build's exchange slots
     uint32_t *hist = nullptr;       // [256][tiles]
     uint32_t *digit_total = nullptr;// [256]
-    float4 *sorted = nullptr;       // [cap + kSortedPad]
+    float4 *sorted = nullptr;       // [cap]
     int32_t *left = nullptr, *right = nullptr, *rf = nullptr, *rl = nullptr;
     int32_t *parent = nullptr, *leaf_parent = nullptr;
     uint32_t *visit = nullptr;      // split weights during the tree build; with the cost model, then kept flags
@@ -63,7 +57,7 @@ struct Workspace {
     uint32_t *kept = nullptr;       // [cap + 1]: kept-node counts, scanned in place
     uint32_t *scan_part = nullptr;  // [scan blocks + 1]
     uint4 *records = nullptr;       // [cap][2]: two-wide quantized records
-    uint4 *qpoint = nullptr;        // [cap + kSortedPad]: per sorted particle, its quantized cell box
+    uint4 *qpoint = nullptr;        // [cap]: per sorted particle, its quantized cell box
                                     // (words 0-2 as a record box) and original index (word 3);
                                     // written only for paper-mode lists
     int32_t *ropes = nullptr;       // [cap]
@@ -80,7 +74,6 @@ void workspace_carve(Workspace &w, void *base, int32_t cap);
 // Traversal arguments (passed by value as the kernel argument block).
 struct TravArgs {
     const uint4 *records;
-    const int32_t *ropes;
     const float4 *sorted;
     const TreeMeta *meta;
     const double *sorted64;  // fp64 data: sorted positions [n][4] (x, y, z, unused); nullptr for fp32 data
@@ -176,7 +169,6 @@ hipError_t launch_build(const Workspace &w, const float *d_pos, const int32_t *d
                         double *sorted64 = nullptr, const double *box64 = nullptr);
 hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool paper, const uint4 *qpoint,
                            hipStream_t s);
-hipError_t launch_traverse_paper(const TravArgs &a, int32_t block, bool vec4, const uint4 *qpoint, hipStream_t s);
 // fp64 particle data: the positions rounded to fp32 for the build (with the
 // fp64 range and type checks when validate is set), and after the build the
 // fp64 positions in sorted order.

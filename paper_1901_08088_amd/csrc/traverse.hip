@@ -1,6 +1,6 @@
 // Neighbor-list traversal (Algorithm 1; Section 2.3; Section 3 runs the
 // queries in Z order so that the queries of a wavefront need similar
-// subtrees), exact lists.  A wavefront takes up to 64 Z-consecutive queries
+// subtrees).  A wavefront takes up to 64 Z-consecutive queries
 // of one type and does two things in turn:
 //
 //   walk      lanes are tree nodes.  A stack in LDS holds the nodes still to
@@ -42,11 +42,17 @@
 // 6.09 -> 4.21 ms, 1M 942 -> 517 us, 4000 102 -> 38 us, WCA 1M 533 -> 235 us,
 // two-type mixture 1M 523 -> 278 us.
 //
+// Paper-mode lists (Section 2.3: a particle is listed when the query's sphere
+// overlaps the particle's own cell box, with no distance check) take the same
+// walk and the same products.  The cell box holds the particle, so a pair
+// within R is listed; one farther apart than the tight radius and the cell's
+// diagonal is not; the pairs between, as a wider band, are decided one by one
+// by the cell box (see decide_cell).
+//
 // Row order.  A row lists, image by image and tree order within an image, the
 // candidates of each run part that the fp32 distance accepts, then those of
 // the part that the fp64 arithmetic accepts.
 #include "build_common.h"
-#include "query_order.h"
 
 namespace qbi {
 namespace {
@@ -119,6 +125,9 @@ static_assert(sizeof(WaveLds) <= 10240, "four wavefronts per SIMD");
 // Periodic image m in {-1, 0, 1}^3 as three 2-bit fields m + 1; kHome is m = 0.
 constexpr uint32_t kHome = 1u | (1u << 2) | (1u << 4);
 
+// List semantics: exact lists of fp32 or of fp64 data, paper-mode lists.
+enum Mode { kExact, kExact64, kPaper };
+
 // Per-query state of a lane.
 struct Query {
     int32_t k, orig;
@@ -135,6 +144,10 @@ struct TreeTest {
     double r2;           // exact squared list radius
     float band, band_img;  // |v| that needs the fp32 distance: home image, other images
     bool force;          // coordinates too large for the product: every pair needs it
+    // paper mode: bin width of each axis, squared tight radius, squared radius
+    // of the image test
+    double h[3];
+    float rp2, rimg2;
 };
 
 // ------------------------------------------------------------------ rows
@@ -298,6 +311,32 @@ __device__ __forceinline__ int decide_pair(const float4 &qp, int32_t k, const fl
     return (dx * dx + dy * dy) + dz * dz <= tt.r2 ? 2 : 0;
 }
 
+// Paper mode: whether the query's sphere (tight radius R (1 + 2^-20) +
+// 0.02 max_d h_d) overlaps the candidate's cell box `b`.  The nearest point is
+// found in each axis's grid units and scaled to world units by that axis's bin
+// width; the pad covers the rounding of the query's grid position (at most
+// 2^-24 of 65535 bins per axis) and of the fp32 distance.  A periodic image
+// counts when the sphere touches the tree's root box, in fp32 with an outward
+// pad of 2^-18 of the largest box edge plus 2^-20 relative.
+template <class LArr, class FArr>
+__device__ __forceinline__ bool decide_cell(const float4 &qp, const uint4 &b, uint32_t img, const TreeTest &tt,
+                                            const TreeMeta &m, const LArr &L, const FArr &Lf) {
+    const float x[3] = {qp.x, qp.y, qp.z};
+    const uint32_t w[3] = {b.x, b.y, b.z};
+    float c[3], e2[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int sh = (int)((img >> (2 * d)) & 3u) - 1;
+        const float p = (float)((((double)x[d] + (double)sh * L[d]) - (double)m.lo[d]) / tt.h[d]);
+        c[d] = (__builtin_amdgcn_fmed3f(p, (float)(w[d] & 0xFFFFu), (float)(w[d] >> 16)) - p) * (float)tt.h[d];
+        const float y = x[d] + (float)sh * Lf[d];
+        const float e = fmaxf(fmaxf(m.lo[d] - y, y - m.hi[d]), 0.0f);
+        e2[d] = e * e;
+    }
+    const float d2 = __builtin_fmaf(c[2], c[2], __builtin_fmaf(c[1], c[1], c[0] * c[0]));
+    return d2 <= tt.rp2 && (e2[0] + e2[1]) + e2[2] <= tt.rimg2;
+}
+
 // Band of the matrix-core test.  Let T be a pair's squared distance as the
 // fp32 positions and the exact image shift give it, and e_s the fp32
 // distance's own error near the cutoff (eta above for a shifted image; the
@@ -312,14 +351,20 @@ __device__ __forceinline__ int decide_pair(const float4 &qp, int32_t k, const fl
 // at most u S, a rounded image origin by sqrt(3) u 2 L_max.  E = 24 u (S^2 +
 // R^2) + 2.5 R (u S + 3.5 u L_max) covers them with room, which also keeps
 // candidates far from the cutoff (their error grows with |c|^2 2^-20, their
-// distance with |c|^2) from ever falling below -band.
-__device__ __forceinline__ float pair_band(double R, double rin, double rout, double e_s, double e_o, double M) {
+// distance with |c|^2) from ever falling below -band.  In paper mode v is
+// taken against the middle of R^2 and the squared rejection radius, and the
+// band is half their difference and E.
+__device__ __forceinline__ double product_error(double R, double e_o, double M) {
     const double u = 0x1p-24, S = 2.0 * M + R;
-    const double E = 24.0 * u * (S * S + R * R) + 2.5 * R * (u * S + e_o);
+    return 24.0 * u * (S * S + R * R) + 2.5 * R * (u * S + e_o);
+}
+
+__device__ __forceinline__ float round_band(double b) { return (float)(b * (1.0 + 0x1p-20) + 1e-30); }
+
+__device__ __forceinline__ float pair_band(double R, double rin, double rout, double e_s, double e_o, double M) {
     // r2in and r2out are rin^2 and rout^2 up to less than 2^-19 of themselves
     const double in = fmax(rin * (1.0 - 0x1p-20) - e_s, 0.0), out = rout * (1.0 + 0x1p-20) + e_s;
-    const double b = fmax(R * R - in * in, out * out - R * R) + E;
-    return (float)(b * (1.0 + 0x1p-20) + 1e-30);
+    return round_band(fmax(R * R - in * in, out * out - R * R) + product_error(R, e_o, M));
 }
 
 // A batch: the queue's next parts, as many whole ones as 64 slots hold; this
@@ -367,11 +412,12 @@ __device__ __forceinline__ uint32_t slot_range(uint32_t from, uint32_t to, uint3
 
 // The batch against the wavefront's queries; accepted candidates are queued
 // for the rows.  `table` is the index table it uses.
-template <bool kVec4, bool kF64, class Args>
+template <bool kVec4, Mode kMode, class Args>
 __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Batch &t, uint32_t table, int groups,
                                            const float *bq, const float *cq, float ox, float oy, float oz,
                                            int32_t kw0, Query &q, WaveLds &w, const float4 *__restrict__ sorted,
-                                           const double *__restrict__ sorted64, uint32_t lane) {
+                                           const double *__restrict__ sorted64, const uint4 *__restrict__ qpoint,
+                                           const TreeMeta &tree, uint32_t lane) {
     const uint32_t slot = slot_of(lane);
     const bool on = t.idx >= 0;
     float osx = ox, osy = oy, osz = oz;
@@ -439,7 +485,12 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
             const uint32_t im = (uint32_t)__shfl((int32_t)t.img, from);
             if ((nlo | nhi) != 0u) {
                 int r = 0;
-                if (ci >= 0) r = decide_pair<kF64>(qp, q.k, sorted[ci], ci, im, tt, a.L, sorted64);
+                if (ci >= 0) {
+                    if constexpr (kMode == kPaper)
+                        r = decide_cell(qp, qpoint[ci], im, tt, tree, a.L, a.Lf) ? 1 : 0;
+                    else
+                        r = decide_pair<kMode == kExact64>(qp, q.k, sorted[ci], ci, im, tt, a.L, sorted64);
+                }
                 if (b < 32u) {
                     nlo ^= bit;
                     lo |= r == 1 ? bit : 0u;
@@ -451,7 +502,7 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
                 }
             }
         }
-        if (__any((xlo | xhi) != 0u)) {
+        if (kMode != kPaper && __any((xlo | xhi) != 0u)) {
             // a part's candidates that the fp64 arithmetic accepted follow
             // those the fp32 distance accepted
             auto room = [&]() {
@@ -534,10 +585,11 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
 
 // One wavefront of queries; this lane's query is position `li` of the system
 // `a` (li >= a.n: an idle lane; the valid lanes come first).
-template <bool kVec4, bool kF64, class Args>
+template <bool kVec4, Mode kMode, class Args>
 __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *__restrict__ records,
                                               const float4 *__restrict__ sorted, const double *__restrict__ sorted64,
-                                              const TreeMeta *__restrict__ meta, WaveLds &w) {
+                                              const uint4 *__restrict__ qpoint, const TreeMeta *__restrict__ meta,
+                                              WaveLds &w) {
     const uint32_t lane = (uint32_t)(threadIdx.x & 63u);
     Query q;
     q.valid = li < a.n;
@@ -595,8 +647,8 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         // which moves each point by up to 2^-24 L_max per axis, so a pair's
         // distance by up to sqrt(3) 2^-23 L_max: the node test widens the
         // search by that much, and the fp32 pair band is doubled
-        const double rshift = kF64 ? 1.7320508075688772 * 0x1p-23 * a.lmax : 0.0;
-        const double eta = (kF64 ? 2.0 : 1.0) * 1.7320508075688772 * 0x1p-22 * (2.0 * a.lmax + 2.0 * R);
+        const double rshift = kMode == kExact64 ? 1.7320508075688772 * 0x1p-23 * a.lmax : 0.0;
+        const double eta = (kMode == kExact64 ? 2.0 : 1.0) * 1.7320508075688772 * 0x1p-22 * (2.0 * a.lmax + 2.0 * R);
         const double rin = fmax(R - eta, 0.0) * (1.0 - 0x1p-20);
         const double rout = (R + eta) * (1.0 + 0x1p-20);
         TreeTest tt;
@@ -604,12 +656,33 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         tt.r2in = (float)(rin * rin * (1.0 - 0x1p-20));
         tt.r2out = (float)(rout * rout * (1.0 + 0x1p-20));
         const double M = (double)(sqrtf(M2) * (1.0f + 0x1p-20f));
-        tt.band = uniform(pair_band(R, rin, rout, R * 0x1p-21, 0.0, M));
-        tt.band_img = uniform(pair_band(R, rin, rout, 1.7320508075688772 * 0x1p-22 * (2.0 * a.lmax + 2.0 * R),
-                                        3.5 * 0x1p-24 * a.lmax, M));
+        const double e_o = 3.5 * 0x1p-24 * a.lmax;  // of a shifted origin
+        double mid = r2;                            // v is the squared distance less this
+        if constexpr (kMode == kPaper) {
+            // listed surely within R, surely not beyond the tight radius and a
+            // cell's diagonal (with room for the rounding of the cell test)
+            double hmax = 0.0, diag = 0.0;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                tt.h[d] = axis_spacing(m.lo[d], m.hi[d], a.lmax * 0x1p-24, a.qbits);
+                hmax = fmax(hmax, tt.h[d]);
+                diag += tt.h[d] * tt.h[d];
+            }
+            const double rp = R * (1.0 + 0x1p-20) + 0.02 * hmax;
+            tt.rp2 = (float)(rp * rp * (1.0 + 0x1p-20));
+            const float rimg = (float)R * (1.0f + 0x1p-20f) + (float)(a.lmax * 0x1p-18);
+            tt.rimg2 = rimg * rimg;
+            const double far = rp * (1.0 + 0x1p-18) + sqrt(diag) + 0.05 * hmax;
+            mid = 0.5 * (r2 + far * far);
+            tt.band = tt.band_img = uniform(round_band(0.5 * (far * far - r2) + product_error(far, e_o, M)));
+        } else {
+            tt.band = uniform(pair_band(R, rin, rout, R * 0x1p-21, 0.0, M));
+            tt.band_img =
+                uniform(pair_band(R, rin, rout, 1.7320508075688772 * 0x1p-22 * (2.0 * a.lmax + 2.0 * R), e_o, M));
+        }
         // (squares of such coordinates would overflow)
         tt.force = !(M2 < 1e28f) || !(a.lmax < 1e14);
-        const float c0 = q.valid ? q2 - (float)r2 : 1e30f;
+        const float c0 = q.valid ? q2 - (float)mid : 1e30f;
         float cq[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) cq[g] = __shfl(c0, 16 * g + (int)(lane & 15u));
@@ -729,8 +802,8 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
                         table = 0;
                     }
                     const Batch t = take_batch(done, parts, w, sorted, lane);
-                    test_batch<kVec4, kF64>(a, tt, t, table, groups, bq, cq, ox, oy, oz, kw0, q, w, sorted, sorted64,
-                                            lane);
+                    test_batch<kVec4, kMode>(a, tt, t, table, groups, bq, cq, ox, oy, oz, kw0, q, w, sorted, sorted64,
+                                             qpoint, m, lane);
                     ++table;
                     done += t.parts;
                     rest -= t.slots;
@@ -756,13 +829,68 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
     if (q.cnt > a.max_nbr) atomicOr(a.overflow, 1);
 }
 
-template <bool kVec4, int kBlock, bool kF64>
+// Workgroups are dealt round-robin to the 8 XCDs; each XCD gets one
+// contiguous stretch of the Z-ordered queries so its L2 holds one region.
+__device__ __forceinline__ int32_t xcd_logical_block() {
+    const uint32_t nb = gridDim.x, b = blockIdx.x;
+    const uint32_t xcd = b & 7u, qq = nb >> 3, rr = nb & 7u;
+    return (int32_t)(xcd * qq + (xcd < rr ? xcd : rr) + (b >> 3));
+}
+
+// Query order.  A system of one type takes its queries in sorted (Z) order,
+// a.qpw per wavefront.  In a system of several types, the workgroups form
+// eight equal stretches (one per XCD when the system covers the whole
+// launch); stretch x takes the x-th eighth of every type's queries, smallest
+// type first, in wavefronts of type_qpw queries of one type.  A sparse type's
+// wavefronts span the widest regions and run longest: this way they start
+// first, are spread over the stretches, and each takes few queries, instead
+// of closing the launch on one XCD.  `wg` is the system's workgroup in
+// dispatch order and `nwg` its workgroup count (trav_blocks, an upper bound
+// for several types); returns the lane's position in the system, or a.n for
+// an idle lane.
+template <int kBlock, class Args>
+__device__ __forceinline__ int32_t query_position(Args &a, const TreeMeta *__restrict__ meta, int32_t wg,
+                                                  int32_t nwg) {
+    const int32_t lane = (int32_t)(threadIdx.x & 63u), wave = (int32_t)(threadIdx.x >> 6);
+    if (a.ntypes <= 1) {
+        // wavefronts of a.qpw queries: lanes past a.qpw idle
+        const int32_t qpw = a.qpw;
+        if (lane >= qpw) return a.n;
+        return (wg * (kBlock / 64) + wave) * qpw + lane;
+    }
+    const int32_t per = nwg / 8;
+    const int64_t part = wg / per;
+    int32_t wi = (wg % per) * (kBlock / 64) + wave;  // wavefront of the stretch
+    for (int r = 0; r < a.ntypes; ++r) {
+        // the type of rank r by (count, type index)
+        int t = 0;
+        for (int u = 0; u < a.ntypes; ++u) {
+            int rank = 0;
+            for (int w = 0; w < a.ntypes; ++w)
+                rank += (meta[w].count < meta[u].count || (meta[w].count == meta[u].count && w < u)) ? 1 : 0;
+            if (rank == r) t = u;
+        }
+        const int64_t len = meta[t].count;
+        const int32_t lo = stretch_lo(len, part), hi = stretch_lo(len, part + 1);
+        const int32_t qt = type_qpw(len, a.n, a.qpw);
+        const int32_t nw = type_waves(len, a.n, a.qpw, part);
+        if (wi < nw) {
+            const int32_t j = wi * qt + lane;
+            return (lane < qt && j < hi - lo) ? meta[t].start - a.start + lo + j : a.n;
+        }
+        wi -= nw;
+    }
+    return a.n;
+}
+
+template <bool kVec4, int kBlock, Mode kMode>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_traverse(
     TravArgs a, const uint4 *__restrict__ records, const float4 *__restrict__ sorted,
-    const TreeMeta *__restrict__ meta) {
+    const uint4 *__restrict__ qpoint, const TreeMeta *__restrict__ meta) {
     __shared__ WaveLds s_wave[kBlock / 64];
     const int32_t li = query_position<kBlock>(a, meta, xcd_logical_block(), (int32_t)gridDim.x);
-    traverse_wave<kVec4, kF64, const TravArgs>(a, li, records, sorted, a.sorted64, meta, s_wave[threadIdx.x >> 6]);
+    traverse_wave<kVec4, kMode, const TravArgs>(a, li, records, sorted, a.sorted64, qpoint, meta,
+                                                s_wave[threadIdx.x >> 6]);
 }
 
 // Batched form: the workgroups of all systems form one grid; each workgroup
@@ -783,18 +911,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     ConstArgs *args = reinterpret_cast<ConstArgs *>(reinterpret_cast<uintptr_t>(table + sys));
     const TreeMeta *meta = meta_all + sys * QBVH_MAX_TYPES;
     const int32_t li = query_position<kBlock>(*args, meta, logical - tblk_first[sys], tblk_first[sys + 1] - tblk_first[sys]);
-    traverse_wave<kVec4, false, ConstArgs>(*args, li, records, sorted, nullptr, meta, s_wave[threadIdx.x >> 6]);
+    traverse_wave<kVec4, kExact, ConstArgs>(*args, li, records, sorted, nullptr, nullptr, meta,
+                                            s_wave[threadIdx.x >> 6]);
 }
 
 __global__ void k_clear_flag(int32_t *f) {
     if (threadIdx.x == 0) *f = 0;
 }
 
-template <bool kVec4, int kBlock, bool kF64>
-void launch_one(const TravArgs &a, hipStream_t s) {
+template <bool kVec4, int kBlock, Mode kMode>
+void launch_one(const TravArgs &a, const uint4 *qpoint, hipStream_t s) {
     const unsigned grid = (unsigned)trav_blocks(a.n, a.ntypes, kBlock, a.qpw);
-    hipLaunchKernelGGL((k_traverse<kVec4, kBlock, kF64>), dim3(grid), dim3(kBlock), 0, s, a, a.records, a.sorted,
-                       a.meta);
+    hipLaunchKernelGGL((k_traverse<kVec4, kBlock, kMode>), dim3(grid), dim3(kBlock), 0, s, a, a.records, a.sorted,
+                       qpoint, a.meta);
 }
 
 template <bool kVec4, int kBlock>
@@ -803,14 +932,22 @@ void launch_one_batch(const BatchLaunch &b, hipStream_t s) {
                        b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
 }
 
-template <bool kVec4, bool kF64>
-void launch_block(const TravArgs &a, int32_t block, hipStream_t s) {
+template <Mode kMode, bool kVec4>
+void launch_block(const TravArgs &a, int32_t block, const uint4 *qpoint, hipStream_t s) {
     switch (block) {
-    case 64: launch_one<kVec4, 64, kF64>(a, s); break;
-    case 128: launch_one<kVec4, 128, kF64>(a, s); break;
-    case 192: launch_one<kVec4, 192, kF64>(a, s); break;
-    default: launch_one<kVec4, 256, kF64>(a, s); break;
+    case 64: launch_one<kVec4, 64, kMode>(a, qpoint, s); break;
+    case 128: launch_one<kVec4, 128, kMode>(a, qpoint, s); break;
+    case 192: launch_one<kVec4, 192, kMode>(a, qpoint, s); break;
+    default: launch_one<kVec4, 256, kMode>(a, qpoint, s); break;
     }
+}
+
+template <Mode kMode>
+void launch_mode(const TravArgs &a, int32_t block, bool vec4, const uint4 *qpoint, hipStream_t s) {
+    if (vec4)
+        launch_block<kMode, true>(a, block, qpoint, s);
+    else
+        launch_block<kMode, false>(a, block, qpoint, s);
 }
 
 template <bool kVec4>
@@ -829,18 +966,12 @@ hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool pap
                            hipStream_t s) {
     hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(64), 0, s, a.overflow);
     if (a.n > 0) {
-        if (paper) return launch_traverse_paper(a, block, vec4, qpoint, s);  // fp32 data only
-        if (a.sorted64) {
-            if (vec4)
-                launch_block<true, true>(a, block, s);
-            else
-                launch_block<false, true>(a, block, s);
-        } else {
-            if (vec4)
-                launch_block<true, false>(a, block, s);
-            else
-                launch_block<false, false>(a, block, s);
-        }
+        if (paper)  // fp32 data only
+            launch_mode<kPaper>(a, block, vec4, qpoint, s);
+        else if (a.sorted64)
+            launch_mode<kExact64>(a, block, vec4, nullptr, s);
+        else
+            launch_mode<kExact>(a, block, vec4, nullptr, s);
     }
     return hipGetLastError();
 }

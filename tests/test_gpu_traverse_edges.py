@@ -69,3 +69,19 @@ def test_wide_spreads(L, r):
         two = _config(pos, L, [[r, 0.5 * r], [0.5 * r, 0.0]], types=types)
         _, nbr, cnt, ovf = run_nlist(two, max_nbr=64, opts={"queries_per_wave": qpw})
         compare_rows(two, nbr, cnt, ovf, 64)
+
+
+@pytest.mark.parametrize("n, qpw, edges, r, qbits", [
+    (1, 0, (8, 8, 8), 2.5, 10), (17, 16, (8, 8, 8), 2.5, 8), (65, 64, (10, 10, 40), 1.0, 8),
+    (700, 64, (10, 10, 40), 0.3, 8), (1500, 0, (40, 9, 12), 0.05, 8), (900, 32, (12, 12, 12), 3.0, 16),
+])
+def test_paper_mode(n, qpw, edges, r, qbits):
+    # cells from far below the radius to three times it: few or all pairs fall
+    # between "surely within R" and "surely beyond the cell's diagonal"
+    import test_gpu_paper as P
+    rng = np.random.default_rng(n)
+    box = np.asarray(edges, np.float32)
+    cfg = W.Config(pos=W.wrap_f32(rng.uniform(0, 1, (n, 3)) * box.astype(np.float64), box), box=box,
+                   rcut=np.array([[r]], np.float32), skin=0.0, name="paper_edge")
+    nbr, cnt, ovf = P._paper_rows(cfg, {"queries_per_wave": qpw, "qbits": qbits, "leaf_size": 7})
+    P._check(cfg, qbits, nbr, cnt, ovf, 512)
