@@ -94,30 +94,38 @@ __global__ void k_type_count(const uint32_t *__restrict__ keys, int32_t n, uint3
 // children and goes on (the agglomerative order of Apetrei's construction).
 //
 // The climb is split by sorted position into chunks, so that an exchange and
-// the child boxes it hands over are synchronized within one workgroup: a
-// split's two children meet only in a chunk holding both its neighbours.  (An
-// agent-scope acquire/release on gfx950 writes back and invalidates the XCD's
-// L2 at every step, far too slow for N atomic steps.)  The first level takes
-// chunks of kFitChunk positions with keys, split weights, particles, boxes and
-// exchange slots in LDS; every further level multiplies the chunk by
-// kFitFanout and climbs in global memory from the nodes the level before left
-// at its chunk borders (the "frontier": finished nodes whose parent did not
-// finish there).  The last level has one chunk and reaches every root.  The
-// unfinished nodes of a chunk nest along its two borders (a radix tree over
-// 32-bit keys plus 32-bit positions has at most 64 internal levels) and each
-// has at most one finished child in the chunk, so kFrontierCap suffices.
+// the child boxes it hands over stay in one workgroup's LDS: a split's two
+// children meet only in a chunk holding both its neighbours.  (An agent-scope
+// acquire/release on gfx950 writes back and invalidates the XCD's L2 at every
+// step, far too slow for N atomic steps.)  The first level takes chunks of
+// kFitChunk positions; every further level multiplies the chunk by kFitFanout
+// and climbs from the nodes the level before left at its chunk borders (the
+// "frontier": finished nodes whose parent did not finish there).  Those nodes
+// tile the chunk's part of every unfinished tree, so with them in order as
+// leaves, and the splits between neighbours, a level is the first level's
+// climb again.  The last level has
+// one chunk and reaches every root.  The unfinished nodes of a chunk nest
+// along its two borders (a radix tree over 32-bit keys plus 32-bit positions
+// has at most 64 internal levels) and each has at most one finished child in
+// the chunk, so kFrontierCap suffices.
 constexpr int kFitChunk = 1024;
 constexpr int kFitThreads = 1024;
-// A small fanout keeps every level's climbs short (about five tree levels from
-// each frontier node) and its workgroups many; N = 8M takes three level launches.
-constexpr int kFitFanout = 32;
-constexpr int kFrontierCap = 160;
-static_assert(kFrontierCap >= 2 * (64 + 1), "fit frontier bound");
-// A level's climbs stop at most once each on a first arrival.
-constexpr int kPendCap = kFitFanout * kFrontierCap;
-// Exchange slot states besides a far end (a sorted position, >= 0).
+// Fanouts whose frontiers fit LDS whatever the keys (4160 entries of 37 bytes,
+// 3120 of 41 with costs); N = 8M takes three level launches.
+template <bool kCost>
+constexpr int kFitFanout = kCost ? 24 : 32;
+constexpr int kFrontierCap = 2 * (64 + 1);
+constexpr int kFrontierStride = 160;  // entries of a chunk's list in the workspace
+static_assert(kFrontierCap <= kFrontierStride, "frontier list");
+template <bool kCost>
+constexpr int kLevelCap = kFitFanout<kCost> * kFrontierCap;
+// Exchange slot states besides a far end (>= 0).
 constexpr int32_t kSlotEmpty = -1;
 constexpr int32_t kSlotDone = -2;
+// Upper levels: a finished split's slot holds its node's first and last entry
+// instead (13 bits each below the sign; never all ones).
+constexpr int32_t kSlotNode = INT32_MIN;
+static_assert(kLevelCap<false> < (1 << 13) - 1, "entries in 13 bits");
 
 // Sorted position i's particle (x, y, z, bits of ~input index within its system).
 __device__ __forceinline__ float4 gather_particle(const TreeSource &src, const uint32_t *__restrict__ vals, int32_t i) {
@@ -144,8 +152,7 @@ __device__ __forceinline__ int32_t split_delta(const TreeSource &src, int32_t k,
 }
 
 // What the climb writes: the tree's node arrays (by Karras id), the Z-ordered
-// particles, the kept-node counts, and the split weights and exchange slots
-// the upper levels use.
+// particles, the kept-node counts, and the split weights the upper levels use.
 struct TreeOut {
     float4 *sorted;
     int32_t *left, *right, *rf, *rl, *parent, *leaf_parent;
@@ -153,7 +160,6 @@ struct TreeOut {
     uint32_t *kept;   // kept[l] counts the nodes [l, r] longer than kept_leaf
     float *cost;      // cost model only
     int32_t *delta;   // [n]: delta[k] for k < n - 1, delta[n - 1] = -1
-    int32_t *slot;    // [n]: exchange slot of each split
     int32_t kept_leaf;
 };
 
@@ -187,6 +193,20 @@ __device__ __forceinline__ int32_t child_at(int32_t g, int32_t e) {
     return e <= g ? (e == g ? ~g : g) : (e == g + 1 ? ~(g + 1) : g + 1);
 }
 
+// The climbs exchange through LDS only, so their ordering waits for LDS and
+// not, at every step, for the node arrays' stores to reach memory.
+__device__ __forceinline__ int32_t slot_exchange(int32_t *slot, int32_t v) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    const int32_t e = __hip_atomic_exchange(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    return e;
+}
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // A node of the climb: range, bounding split weights, box, cost and children.
 struct Climb {
     int32_t l, r, dl, dr, cl, cr;
@@ -195,8 +215,8 @@ struct Climb {
 };
 
 // First level: one chunk of kFitChunk sorted positions per workgroup; also
-// gathers the chunk's particles in Z order and leaves its split weights and
-// cleared exchange slots for the upper levels.  A node finished here has its
+// gathers the chunk's particles in Z order and leaves its split weights for the
+// upper levels.  A node finished here has its
 // id, range and children inside the chunk, so everything written about it
 // (its range, split and box, its children's parent, the kept counts) is
 // collected in LDS and written out at the end with coalesced stores.
@@ -253,19 +273,18 @@ __global__ __launch_bounds__(kFitThreads) void k_tree_local(const uint32_t *__re
         s_nr[t] = -1;
         s_par[t] = kUnset;
         s_lpar[t] = kUnset;
-        out.slot[c0 + t] = kSlotEmpty;
     }
     if (t == 0) s_fcount = 0;
-    __syncthreads();
+    lds_barrier();
     for (int32_t j = t; j <= m; j += kFitThreads) {
         const int32_t k = c0 - 1 + j;
         const int32_t d = (k < 0 || k + 1 >= n) ? -1 : split_delta(src, k, s_keykept[j], s_keykept[j + 1]);
         s_delta[j] = d;
         if (k >= c0) out.delta[k] = d;  // this chunk's splits c0 .. c0 + m - 1
     }
-    __syncthreads();
+    lds_barrier();
     if (t < m) s_keykept[t] = 0u;
-    __syncthreads();
+    lds_barrier();
     if (t < m) {
         Climb u;
         u.l = u.r = c0 + t;
@@ -306,8 +325,7 @@ __global__ __launch_bounds__(kFitThreads) void k_tree_local(const uint32_t *__re
                 frontier_push(K, &s_fcount, s_front, err);
                 break;
             }
-            const int32_t e = __hip_atomic_exchange(&s_slot[g - c0], goes_left ? u.l : u.r, __ATOMIC_ACQ_REL,
-                                                    __HIP_MEMORY_SCOPE_WORKGROUP);
+            const int32_t e = slot_exchange(&s_slot[g - c0], goes_left ? u.l : u.r);
             if (e == kSlotEmpty) break;  // the sibling finishes the parent
             s_slot[g - c0] = kSlotDone;
             const int32_t sib = child_at(g, e);
@@ -347,7 +365,7 @@ __global__ __launch_bounds__(kFitThreads) void k_tree_local(const uint32_t *__re
                                    goes_left ? own : scost, goes_left ? scost : own);
         }
     }
-    __syncthreads();
+    lds_barrier();
     // first arrivals whose sibling never came: their parent straddles a border
     for (int32_t j = t; j < m - 1; j += kFitThreads) {
         const int32_t e = s_slot[j];
@@ -370,145 +388,174 @@ __global__ __launch_bounds__(kFitThreads) void k_tree_local(const uint32_t *__re
         if (s_lpar[t] != kUnset) out.leaf_parent[K] = s_lpar[t];
         out.kept[K] = s_keykept[t];  // the chunk's own nodes are the only ones starting here so far
     }
-    __syncthreads();
+    lds_barrier();
     const uint32_t fc = min(s_fcount, (uint32_t)kFrontierCap);
-    for (uint32_t i = t; i < fc; i += kFitThreads) front[(int64_t)blockIdx.x * kFrontierCap + i] = s_front[i];
+    for (uint32_t i = t; i < fc; i += kFitThreads) front[(int64_t)blockIdx.x * kFrontierStride + i] = s_front[i];
     if (t == 0) fcount[blockIdx.x] = fc;
 }
 
-// One level above the first: chunks of `chunk` positions, climbing from the
-// frontiers of the `fan` previous-level chunks each contains, with the
-// exchange slots in global memory (workgroup-scope atomics: a split's two
-// children meet in one chunk).  A step waits for two round trips: the
-// exchange, then the sibling's box with the new bounding weight.
+// One level above the first.  The frontier nodes of a chunk's kFitFanout
+// chunks of the level before are put in order and become the leaves of
+// a climb in LDS; a finished node's box takes the place of an entry it covers
+// (its id in entry numbers, as Karras's ids in positions) and the node arrays
+// are written when the climb is done: each step's nine scattered stores would
+// fill the wavefront's queue of outstanding ones and stall it.  Four dependent
+// round trips to memory (counts, entries, ranges and boxes, split weights) and
+// the longest climb, about 800 cycles a step, set its time; climbing in global
+// memory took two round trips a step: 29.5 -> 18.0 us per level at N = 1M,
+// 38.0 -> 21.8 at 8M.
 template <bool kCost>
-__global__ __launch_bounds__(kFitThreads) void k_tree_level(int32_t n, int64_t chunk, int32_t nprev,
+__global__ __launch_bounds__(kFitThreads) void k_tree_level(int32_t nprev,
                                                             const int32_t *__restrict__ front_in,
                                                             const uint32_t *__restrict__ fcount_in, TreeOut out,
                                                             int32_t *__restrict__ front_out,
                                                             uint32_t *__restrict__ fcount_out, int32_t *err,
                                                             Collapse col) {
+    constexpr int kFan = kFitFanout<kCost>;
+    __shared__ int32_t s_first[kLevelCap<kCost>], s_last[kLevelCap<kCost>];  // positions of each entry, in order
+    __shared__ float s_box[6][kLevelCap<kCost>];       // entries, then nodes by id
+    __shared__ float s_cost[kCost ? kLevelCap<kCost> : 1];
+    __shared__ int32_t s_slot[kLevelCap<kCost>];       // entries unordered, then the slot of the split after an entry
+    __shared__ int8_t s_delta[kLevelCap<kCost> + 1];   // s_delta[i]: weight of the split before entry i
     __shared__ int32_t s_front[kFrontierCap];
     __shared__ uint32_t s_fcount;
-    __shared__ uint32_t s_off[kFitFanout + 1];
-    __shared__ int32_t s_pend[kPendCap];  // splits where a climb stopped as the first arrival
-    __shared__ uint32_t s_npend;
-    const int64_t c0 = (int64_t)blockIdx.x * chunk;
-    const int64_t c1 = min(c0 + chunk, (int64_t)n);
-    const int32_t j0 = blockIdx.x * kFitFanout;
-    // The frontier entries of the fan-in chunks, numbered consecutively, so
-    // that each thread climbs from at most a few of them.
-    if (threadIdx.x < kFitFanout) {
-        const int32_t jc = j0 + (int32_t)threadIdx.x;
-        s_off[threadIdx.x + 1] = jc < nprev ? min(fcount_in[jc], (uint32_t)kFrontierCap) : 0u;
+    __shared__ uint32_t s_off[kFan + 1];
+    const int32_t j0 = blockIdx.x * kFan;
+    const int32_t t = threadIdx.x;
+    // the frontier entries of the fan-in chunks, numbered consecutively
+    if (t < kFan) {
+        const int32_t jc = j0 + t;
+        s_off[t + 1] = jc < nprev ? min(fcount_in[jc], (uint32_t)kFrontierCap) : 0u;
     }
-    if (threadIdx.x == 0) {
+    if (t == 0) {
         s_fcount = 0;
-        s_npend = 0;
         s_off[0] = 0;
     }
-    __syncthreads();
-    if (threadIdx.x == 0)
-        for (int k = 1; k <= kFitFanout; ++k) s_off[k] += s_off[k - 1];
-    __syncthreads();
-    const uint32_t total = s_off[kFitFanout];
-    for (uint32_t e = threadIdx.x; e < total; e += kFitThreads) {
-        // the chunk k holding entry e: s_off[k] <= e < s_off[k + 1]
-        int lo = 0, hi = kFitFanout;
+    lds_barrier();
+    if (t == 0)
+        for (int k = 1; k <= kFan; ++k) s_off[k] += s_off[k - 1];
+    lds_barrier();
+    const int32_t total = (int32_t)s_off[kFan];
+    // the fan-in chunk k of entry e: s_off[k] <= e < s_off[k + 1]
+    auto chunk_of = [&](int32_t e) {
+        int lo = 0, hi = kFan;
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
-            if (s_off[mid] <= e) lo = mid; else hi = mid;
+            if ((int32_t)s_off[mid] <= e) lo = mid; else hi = mid;
         }
-        const int32_t c = front_in[(int64_t)(j0 + lo) * kFrontierCap + (e - s_off[lo])];
-        // the entry was written when its parent's split was found: restart there
-        Climb u;
-        u.cl = u.cr = 0;
-        if (c < 0) {
-            u.l = u.r = ~c;
-            const float4 q = out.sorted[~c];
-            u.lo[0] = u.hi[0] = q.x;
-            u.lo[1] = u.hi[1] = q.y;
-            u.lo[2] = u.hi[2] = q.z;
-            u.cost = col.kVball;
-        } else {
-            u.l = out.rf[c];
-            u.r = out.rl[c];
-            const float4 a = out.box[2 * (int64_t)c], b = out.box[2 * (int64_t)c + 1];
-            u.lo[0] = a.x; u.lo[1] = a.y; u.lo[2] = a.z;
-            u.hi[0] = b.x; u.hi[1] = b.y; u.hi[2] = b.z;
-            u.cost = kCost ? out.cost[c] : 0.0f;
+        return lo;
+    };
+    for (int32_t e = t; e < total; e += kFitThreads) {
+        const int k = chunk_of(e);
+        s_slot[e] = front_in[(int64_t)(j0 + k) * kFrontierStride + (e - (int32_t)s_off[k])];
+    }
+    lds_barrier();
+    for (int32_t e = t; e < total; e += kFitThreads) {
+        const int k = chunk_of(e);
+        const int32_t a = (int32_t)s_off[k], b = (int32_t)s_off[k + 1], c = s_slot[e], f = c < 0 ? ~c : c;
+        int32_t rank = a;  // (a node's id lies inside its range, so ids order the nodes)
+        for (int32_t j = a; j < b; ++j) rank += (s_slot[j] < 0 ? ~s_slot[j] : s_slot[j]) < f ? 1 : 0;
+        s_first[rank] = c;
+    }
+    lds_barrier();
+    for (int32_t i = t; i < total; i += kFitThreads) {
+        const int32_t K = s_first[i];
+        const float4 *pa = K < 0 ? out.sorted + ~K : out.box + 2 * (int64_t)K;
+        const float4 *pb = K < 0 ? out.sorted + ~K : out.box + 2 * (int64_t)K + 1;
+        const float4 lo = *pa, hi = *pb;
+        const int32_t l = K < 0 ? ~K : out.rf[K], r = K < 0 ? ~K : out.rl[K];
+        s_first[i] = l;
+        s_last[i] = r;
+        const int32_t dl = l > 0 ? out.delta[l - 1] : -1, dr = out.delta[r];
+        s_delta[i] = (int8_t)dl;
+        if (i == total - 1) s_delta[total] = (int8_t)dr;
+        s_slot[i] = kSlotEmpty;
+        s_box[0][i] = lo.x;
+        s_box[1][i] = lo.y;
+        s_box[2][i] = lo.z;
+        s_box[3][i] = hi.x;
+        s_box[4][i] = hi.y;
+        s_box[5][i] = hi.z;
+        if (kCost) s_cost[i] = K < 0 ? col.kVball : out.cost[K];
+    }
+    lds_barrier();
+    for (int32_t i = t; i < total; i += kFitThreads) {
+        int32_t a = i, b = i;  // entries of the node carried
+        int32_t dl = s_delta[a], dr = s_delta[b + 1];
+        float lo[3], hi[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            lo[d] = s_box[d][i];
+            hi[d] = s_box[3 + d][i];
         }
-        u.dl = u.l > 0 ? out.delta[u.l - 1] : -1;
-        u.dr = out.delta[u.r];
-        bool fresh = false;
+        float cost = kCost ? s_cost[i] : 0.0f;
         for (int step = 0; step < kMaxDepth; ++step) {
-            const bool leaf = u.l == u.r;
-            const bool root = u.dl < 0 && u.dr < 0;
-            const bool goes_left = u.dr > u.dl;
-            const int32_t K = leaf ? ~u.l : (goes_left && !root ? u.r : u.l);
-            if (fresh) write_node<kCost>(out, K, u.l, u.r, u.cl, u.cr, u.lo, u.hi, u.cost);
-            if (root) {
-                out.parent[K] = -1;  // (a climb reaches a root only through a merge)
+            const bool goes_left = dr > dl;  // this node is the left child of the split after it
+            const int32_t g = goes_left ? b : a - 1;
+            if (g < 0 || g >= total - 1) {
+                const int32_t l = s_first[a], r = s_last[b];
+                frontier_push(l == r ? ~l : (goes_left ? r : l), &s_fcount, s_front, err);
                 break;
             }
-            const int32_t g = goes_left ? u.r : u.l - 1;
-            if (g < c0 || g >= c1 - 1) {
-                frontier_push(K, &s_fcount, s_front, err);
-                break;
+            const int32_t ex = slot_exchange(&s_slot[g], goes_left ? a : b);
+            if (ex == kSlotEmpty) break;  // the sibling finishes the parent
+            const int32_t sib = ex <= g ? g : g + 1;
+            const float own = fabsf(cost), other = kCost ? fabsf(s_cost[sib]) : 0.0f;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                lo[d] = fminf(lo[d], s_box[d][sib]);
+                hi[d] = fmaxf(hi[d], s_box[3 + d][sib]);
             }
-            const int32_t ex = __hip_atomic_exchange(&out.slot[g], goes_left ? u.l : u.r, __ATOMIC_ACQ_REL,
-                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (ex == kSlotEmpty) {
-                const uint32_t at = atomicAdd(&s_npend, 1u);
-                if (at < (uint32_t)kPendCap) s_pend[at] = g; else atomicOr(err, 2);
-                break;
-            }
-            out.slot[g] = kSlotDone;
-            const int32_t sib = child_at(g, ex);
-            // the sibling's box and cost and the new far weight, loaded together
-            const float4 *pa = sib < 0 ? out.sorted + ~sib : out.box + 2 * (int64_t)sib;
-            const float4 *pb = sib < 0 ? out.sorted + ~sib : out.box + 2 * (int64_t)sib + 1;
-            const float4 slo = *pa, shi = *pb;
-            const float scost = kCost ? (sib < 0 ? col.kVball : fabsf(out.cost[sib])) : 0.0f;
-            const int32_t dnew = goes_left ? out.delta[ex] : (ex > 0 ? out.delta[ex - 1] : -1);
-            const float own = fabsf(u.cost);
             if (goes_left) {
-                u.r = ex;
-                u.dr = dnew;
-                u.cl = K;
-                u.cr = sib;
+                b = ex;
+                dr = s_delta[b + 1];
             } else {
-                u.l = ex;
-                u.dl = dnew;
-                u.cl = sib;
-                u.cr = K;
+                a = ex;
+                dl = s_delta[a];
             }
-            u.lo[0] = fminf(u.lo[0], slo.x);
-            u.lo[1] = fminf(u.lo[1], slo.y);
-            u.lo[2] = fminf(u.lo[2], slo.z);
-            u.hi[0] = fmaxf(u.hi[0], shi.x);
-            u.hi[1] = fmaxf(u.hi[1], shi.y);
-            u.hi[2] = fmaxf(u.hi[2], shi.z);
             if (kCost)
-                u.cost = node_cost(col, u.r - u.l + 1, u.lo[0], u.lo[1], u.lo[2], u.hi[0], u.hi[1], u.hi[2],
-                                   goes_left ? own : scost, goes_left ? scost : own);
-            fresh = true;
+                cost = node_cost(col, s_last[b] - s_first[a] + 1, lo[0], lo[1], lo[2], hi[0], hi[1], hi[2],
+                                 goes_left ? own : other, goes_left ? other : own);
+            s_slot[g] = kSlotNode | a << 13 | b;
+            const bool root = dl < 0 && dr < 0;
+            const int32_t at = dr > dl && !root ? b : a;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                s_box[d][at] = lo[d];
+                s_box[3 + d][at] = hi[d];
+            }
+            if (kCost) s_cost[at] = cost;
+            if (root) break;
         }
     }
-    __syncthreads();
-    // first arrivals whose sibling never came go to the next level, with their
-    // slots cleared for it
-    const uint32_t np = min(s_npend, (uint32_t)kPendCap);
-    for (uint32_t j = threadIdx.x; j < np; j += kFitThreads) {
-        const int32_t g = s_pend[j];
-        const int32_t ex = out.slot[g];
-        if (ex >= 0) frontier_push(child_at(g, ex), &s_fcount, s_front, err);
-        out.slot[g] = kSlotEmpty;
+    lds_barrier();
+    // the finished nodes, by split (ids are unique, so no box was overwritten)
+    for (int32_t g = t; g < total - 1; g += kFitThreads) {
+        const int32_t e = s_slot[g];
+        if (e >= kSlotEmpty) continue;
+        const int32_t a = (e >> 13) & 0x1FFF, b = e & 0x1FFF;
+        const int32_t dl = s_delta[a], dr = s_delta[b + 1];
+        const bool root = dl < 0 && dr < 0, right_id = dr > dl && !root;
+        const int32_t l = s_first[a], r = s_last[b], split = s_last[g], at = right_id ? b : a;
+        const float lo[3] = {s_box[0][at], s_box[1][at], s_box[2][at]};
+        const float hi[3] = {s_box[3][at], s_box[4][at], s_box[5][at]};
+        const int32_t K = right_id ? r : l;
+        write_node<kCost>(out, K, l, r, l == split ? ~l : split, split + 1 == r ? ~r : split + 1, lo, hi,
+                          kCost ? s_cost[at] : 0.0f);
+        if (root) out.parent[K] = -1;  // (a climb reaches a root only through a merge)
     }
-    __syncthreads();
+    // first arrivals whose sibling never came go to the next level
+    for (int32_t j = t; j < total - 1; j += kFitThreads) {
+        const int32_t ex = s_slot[j];
+        if (ex >= 0) {
+            const int32_t split = s_last[j], far = ex <= j ? s_first[ex] : s_last[ex];
+            frontier_push(child_at(split, far), &s_fcount, s_front, err);
+        }
+    }
+    lds_barrier();
     const uint32_t fc = min(s_fcount, (uint32_t)kFrontierCap);
-    for (uint32_t i = threadIdx.x; i < fc; i += kFitThreads) front_out[(int64_t)blockIdx.x * kFrontierCap + i] = s_front[i];
-    if (threadIdx.x == 0) fcount_out[blockIdx.x] = fc;
+    for (uint32_t i = t; i < fc; i += kFitThreads) front_out[(int64_t)blockIdx.x * kFrontierStride + i] = s_front[i];
+    if (t == 0) fcount_out[blockIdx.x] = fc;
 }
 
 // Root box, grid spacing and slot range of each type's tree.
@@ -660,7 +707,7 @@ template <bool kCost>
 void launch_tree_t(const Workspace &w, int32_t n, const TreeSource &src, int32_t kept_leaf, const Collapse &col,
                    hipStream_t s) {
     const TreeOut out{w.sorted, w.left, w.right, w.rf, w.rl, w.parent, w.leaf_parent, w.box, w.kept,
-                      w.cost, reinterpret_cast<int32_t *>(w.visit), reinterpret_cast<int32_t *>(w.keys2), kept_leaf};
+                      w.cost, reinterpret_cast<int32_t *>(w.visit), kept_leaf};
     int32_t nchunks = fit_chunks0(n);
     hipLaunchKernelGGL(k_tree_local<kCost>, dim3(nchunks), dim3(kFitThreads), 0, s, w.keys, w.vals, n, src, out,
                        w.front[0], w.fcount[0], w.err, col);
@@ -668,9 +715,9 @@ void launch_tree_t(const Workspace &w, int32_t n, const TreeSource &src, int32_t
     int which = 0;
     while (chunk < n) {
         const int32_t nprev = nchunks;
-        chunk *= kFitFanout;
+        chunk *= kFitFanout<kCost>;
         nchunks = (int32_t)((n + chunk - 1) / chunk);
-        hipLaunchKernelGGL(k_tree_level<kCost>, dim3(nchunks), dim3(kFitThreads), 0, s, n, chunk, nprev,
+        hipLaunchKernelGGL(k_tree_level<kCost>, dim3(nchunks), dim3(kFitThreads), 0, s, nprev,
                            w.front[which], w.fcount[which], out, w.front[which ^ 1], w.fcount[which ^ 1], w.err, col);
         which ^= 1;
     }
@@ -703,17 +750,17 @@ size_t workspace_bytes(int32_t cap) {
     size_t b = 0;
     b += 4 * al(c * 4);                       // keys, vals, keys2, vals2
     b += al(256 * tiles * 4) + al(256 * 4);   // histograms
-    b += al(c * 16);                         // sorted
+    b += al((c + kSpare) * 16);               // sorted
     b += 6 * al(c * 4);                       // left right rf rl parent leaf_parent
     b += al(c * 4);                           // visit (split weights, then kept flags)
     b += al(c * 4);                           // cost (subtree collapse)
     b += al(c * 32);                          // boxes (lower and upper bound per node)
     b += al((c + 1) * 4) + al(sb * 4);        // kept + scan partials
     b += al(c * 32) + al(c * 4);              // records + ropes
-    b += al(c * 16);                          // cell boxes (paper-mode lists)
+    b += al((c + kSpare) * 16);                // cell boxes (paper-mode lists)
     b += al(QBVH_MAX_TYPES * sizeof(TreeMeta)) + al(QBVH_MAX_TYPES * 4) + al(4);
     const size_t nf = (size_t)fit_chunks0((int32_t)c);
-    b += 2 * (al(nf * kFrontierCap * 4) + al(nf * 4));  // tree-build frontiers (ping-pong)
+    b += 2 * (al(nf * kFrontierStride * 4) + al(nf * 4));  // tree-build frontiers (ping-pong)
     return b;
 }
 
@@ -737,7 +784,7 @@ void workspace_carve(Workspace &w, void *base, int32_t cap) {
     w.vals2 = (uint32_t *)take(c * 4);
     w.hist = (uint32_t *)take(256 * tiles * 4);
     w.digit_total = (uint32_t *)take(256 * 4);
-    w.sorted = (float4 *)take(c * 16);
+    w.sorted = (float4 *)take((c + kSpare) * 16);
     w.left = (int32_t *)take(c * 4);
     w.right = (int32_t *)take(c * 4);
     w.rf = (int32_t *)take(c * 4);
@@ -750,14 +797,14 @@ void workspace_carve(Workspace &w, void *base, int32_t cap) {
     w.kept = (uint32_t *)take((c + 1) * 4);
     w.scan_part = (uint32_t *)take(sb * 4);
     w.records = (uint4 *)take(c * 32);
-    w.qpoint = (uint4 *)take(c * 16);
+    w.qpoint = (uint4 *)take((c + kSpare) * 16);
     w.ropes = (int32_t *)take(c * 4);
     w.meta = (TreeMeta *)take(QBVH_MAX_TYPES * sizeof(TreeMeta));
     w.type_count = (uint32_t *)take(QBVH_MAX_TYPES * 4);
     w.err = (int32_t *)take(4);
     const size_t nf = (size_t)fit_chunks0((int32_t)c);
     for (int i = 0; i < 2; ++i) {
-        w.front[i] = (int32_t *)take(nf * kFrontierCap * 4);
+        w.front[i] = (int32_t *)take(nf * kFrontierStride * 4);
         w.fcount[i] = (uint32_t *)take(nf * 4);
     }
     w.bytes = (size_t)(p - (char *)base);

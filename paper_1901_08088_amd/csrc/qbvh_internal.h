@@ -38,6 +38,10 @@ struct TreeMeta {
 };
 static_assert(sizeof(TreeMeta) == 64, "TreeMeta is 64 bytes");
 
+// Spare entries of the particle arrays: they keep the workspace's size, by which
+// callers plan budgets and nlist_build_noalloc accepts n.
+constexpr int32_t kSpare = 16;
+
 // Device workspace of one built tree (all arrays sized for `cap` particles).
 struct Workspace {
     int32_t cap = 0;
@@ -45,7 +49,7 @@ struct Workspace {
     void *base = nullptr;     // single hipMalloc allocation
     size_t bytes = 0;
     uint32_t *keys = nullptr, *vals = nullptr;
-    uint32_t *keys2 = nullptr, *vals2 = nullptr;  // sort ping-pong; keys2 then holds the tree build's exchange slots
+    uint32_t *keys2 = nullptr, *vals2 = nullptr;  // sort ping-pong
     uint32_t *hist = nullptr;       // [256][tiles]
     uint32_t *digit_total = nullptr;// [256]
     float4 *sorted = nullptr;       // [cap]
