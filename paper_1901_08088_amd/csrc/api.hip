@@ -200,7 +200,7 @@ int check_valid(const int32_t *d_err, hipStream_t s) {
 // The traversal of a built workspace into the caller's outputs; `a` carries
 // the list radii, the box and (fp64 data) the sorted fp64 positions.
 int launch_list(const Workspace &w, int32_t n, int32_t ntypes, const qbvh_opts_t &o, qbi::TravArgs &a,
-                int32_t max_nbr, int32_t mode, int32_t *d_nbr, int32_t *d_count, int32_t *d_overflow,
+                int32_t max_nbr, int32_t mode, int32_t *d_nbr, int32_t *d_count, int32_t *d_overflow, bool cleared,
                 hipStream_t s) {
     a.records = w.records;
     a.sorted = w.sorted;
@@ -217,7 +217,7 @@ int launch_list(const Workspace &w, int32_t n, int32_t ntypes, const qbvh_opts_t
     const bool paper = mode == QBVH_LIST_PAPER;
     hipError_t e = hipSuccess;
     if (paper) e = qbi::launch_qpoint(w, n, ntypes, o.qbits, a.lmax, s);
-    if (e == hipSuccess) e = qbi::launch_traverse(a, o.block_size, vec4, paper, w.qpoint, s);
+    if (e == hipSuccess) e = qbi::launch_traverse(a, o.block_size, vec4, paper, w.qpoint, cleared, s);
     if (e != hipSuccess) return hip_fail(e);
     return QBVH_OK;
 }
@@ -319,7 +319,7 @@ int nlist_build_ex(const qbvh_t *tree, const float *rcut, float skin, int32_t ma
         qbi::fill_trav_box(a, tree->box);
     }
     return launch_list(tree->ws, tree->n, tree->ntypes, tree->opts, a, max_nbr, mode, d_nbr, d_count, d_overflow,
-                       (hipStream_t)stream);
+                       false, (hipStream_t)stream);
 }
 
 int nlist_build(const qbvh_t *tree, const float *rcut, float skin, int32_t max_nbr, int32_t *d_nbr,
@@ -459,14 +459,16 @@ int nlist_build_noalloc(const float *d_pos, const int32_t *d_type, int32_t n, in
     qbi::workspace_carve(w, base, cap);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = qbi::launch_build(w, d_pos, ntypes > 1 ? d_type : nullptr, n, ntypes, box, o.leaf_size, o.qbits,
-                                     o.collapse_radius, o.validate, s);
+                                     o.collapse_radius, o.validate, s, nullptr, nullptr, nullptr,
+                                     o.validate ? nullptr : d_overflow);
     if (e != hipSuccess) return hip_fail(e);
     if (o.validate) {
         rc = check_valid(w.err, s);
         if (rc != QBVH_OK) return rc;
     }
     qbi::fill_trav_box(a, box);
-    return launch_list(w, n, ntypes, o, a, max_nbr, QBVH_LIST_EXACT, d_nbr, d_count, d_overflow, s);
+    return launch_list(w, n, ntypes, o, a, max_nbr, QBVH_LIST_EXACT, d_nbr, d_count, d_overflow,
+                       !o.validate, s);
 }
 
 }  // extern "C"

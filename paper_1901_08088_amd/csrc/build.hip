@@ -33,47 +33,26 @@ __device__ __forceinline__ Segment segment_of(uint32_t key, int32_t n, int32_t n
     return {s, s + (int32_t)type_count[t]};
 }
 
-__global__ __launch_bounds__(kBuildThreads) void k_init(uint32_t *type_count, int32_t *err) {
-    if (threadIdx.x < QBVH_MAX_TYPES) type_count[threadIdx.x] = 0;
+// Clears the error word before a validating Morton kernel sets it (otherwise
+// the Morton kernel clears it: a launch takes about 4.6 us whatever it does).
+__global__ void k_init(int32_t *err) {
     if (threadIdx.x == 0) *err = 0;
 }
 
-// Morton keys from fp32 or fp64 positions.  fp64 data: the bins are taken
-// from each coordinate rounded to nearest fp32 (what the tree is built on)
-// and the optional checks 0 <= x < L are made in fp64 against the fp64 box;
-// fp32 data: L is the fp32 box (compared exactly after promotion).
 template <class T>
-__global__ __launch_bounds__(kBuildThreads) void k_morton(const T *__restrict__ pos,
-                                                          const int32_t *__restrict__ type, int32_t n,
-                                                          int32_t ntypes, double Lx, double Ly, double Lz,
-                                                          double sx, double sy, double sz, int32_t validate,
-                                                          uint32_t *__restrict__ keys,
-                                                          uint32_t *__restrict__ kept, int32_t *err) {
+__global__ __launch_bounds__(kBuildThreads) void k_morton(MortonArgs<T> m, int32_t n, uint32_t *__restrict__ keys) {
     const int32_t k = blockIdx.x * kBuildThreads + threadIdx.x;
-    // the kept counts of positions < n are written by the tree build; the
-    // scan's extra entry is cleared here
-    if (k == n) kept[n] = 0;
-    if (k < n) {
-        const T x = pos[3 * (int64_t)k + 0];
-        const T y = pos[3 * (int64_t)k + 1];
-        const T z = pos[3 * (int64_t)k + 2];
-        int32_t t = type ? type[k] : 0;
-        if (validate) {
-            const bool ok = ((double)x >= 0.0 && (double)x < Lx) && ((double)y >= 0.0 && (double)y < Ly) &&
-                            ((double)z >= 0.0 && (double)z < Lz) && (t >= 0 && t < ntypes);
-            if (!ok) atomicOr(err, 1);
-        }
-        t = t < 0 ? 0 : (t >= ntypes ? ntypes - 1 : t);
-        keys[k] = morton_key((float)x, (float)y, (float)z, sx, sy, sz, t);
-    }
+    if (k == 0) morton_clear(m, n);
+    if (k < n) keys[k] = morton_of(m, k);
 }
 
-// Particles per type, read off the sorted keys (type in bits 30-31) by binary
-// search: no atomics on a few hot counters.
-__global__ void k_type_count(const uint32_t *__restrict__ keys, int32_t n, uint32_t *__restrict__ type_count) {
-    const uint32_t t = threadIdx.x;
-    if (t < QBVH_MAX_TYPES)
-        type_count[t] = (uint32_t)(type_start(keys, 0, n, t + 1) - type_start(keys, 0, n, t));
+// Keys and sort: the Z order of the particles (keys, vals).
+template <class T>
+hipError_t launch_order(const MortonArgs<T> &m, const Workspace &w, int32_t n, hipStream_t s) {
+    if (rank_sorted(n)) return launch_morton_rank(m, n, w.keys, w.vals, s);
+    hipLaunchKernelGGL(k_morton<T>, dim3((unsigned)((n + kBuildThreads - 1) / kBuildThreads)), dim3(kBuildThreads), 0,
+                       s, m, n, w.keys);
+    return launch_radix_sort(w.keys, w.vals, w.keys2, w.vals2, w.hist, w.digit_total, n, w.tiles, s);
 }
 
 // Radix tree and node boxes in one bottom-up pass (Section 2.1: the hierarchy
@@ -227,7 +206,7 @@ __global__ __launch_bounds__(kFitThreads) void k_tree_local(const uint32_t *__re
                                                             const uint32_t *__restrict__ vals, int32_t n,
                                                             TreeSource src, TreeOut out, int32_t *__restrict__ front,
                                                             uint32_t *__restrict__ fcount, int32_t *err,
-                                                            Collapse col) {
+                                                            Collapse col, uint32_t *__restrict__ type_count) {
     __shared__ uint32_t s_keykept[kFitChunk + 2];  // keys c0 - 1 .. c0 + m, then kept counts by l - c0
     __shared__ int32_t s_delta[kFitChunk + 1];     // s_delta[j]: weight of split c0 - 1 + j
     __shared__ float s_pos[3][kFitChunk];
@@ -241,6 +220,10 @@ __global__ __launch_bounds__(kFitThreads) void k_tree_local(const uint32_t *__re
     const int32_t c0 = blockIdx.x * kFitChunk;
     const int32_t m = min(kFitChunk, n - c0);
     const int32_t t = threadIdx.x;
+    // particles per type (single systems of several types), read off the sorted
+    // keys by binary search: no atomics on a few hot counters
+    if (type_count && blockIdx.x == 0 && t < QBVH_MAX_TYPES)
+        type_count[t] = (uint32_t)(type_start(keys, 0, n, (uint32_t)t + 1u) - type_start(keys, 0, n, (uint32_t)t));
     // the particle's loads go out first and complete while the keys are staged
     float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
     if (t < m) {
@@ -559,16 +542,16 @@ __global__ __launch_bounds__(kFitThreads) void k_tree_level(int32_t nprev,
 }
 
 // Root box, grid spacing and slot range of each type's tree.
-__global__ void k_meta(int32_t n, int32_t ntypes, const uint32_t *__restrict__ type_count,
-                       const float4 *__restrict__ sorted, const float4 *__restrict__ box,
-                       const uint32_t *__restrict__ P, int32_t qbits,
-                       int32_t leaf_size, const float *__restrict__ cost, double ext_floor,
-                       TreeMeta *__restrict__ meta) {
-    const int t = threadIdx.x;
-    if (t >= ntypes) return;
-    int32_t s = 0;
-    for (int u = 0; u < t; ++u) s += (int32_t)type_count[u];
-    const int32_t c = (ntypes == 1) ? n : (int32_t)type_count[t];
+__device__ __forceinline__ TreeMeta type_meta(int t, int32_t n, int32_t ntypes,
+                                              const uint32_t *__restrict__ type_count,
+                                              const float4 *__restrict__ sorted, const float4 *__restrict__ box,
+                                              const uint32_t *__restrict__ P, int32_t qbits, int32_t leaf_size,
+                                              const float *__restrict__ cost, double ext_floor) {
+    int32_t s = 0, c = n;
+    if (ntypes > 1 && n > 0) {  // (the counts are left by the tree build)
+        for (int u = 0; u < t; ++u) s += (int32_t)type_count[u];
+        c = (int32_t)type_count[t];
+    }
     float lo[3] = {0.f, 0.f, 0.f}, hi[3] = {0.f, 0.f, 0.f};
     if (c == 1) {
         const float4 p = sorted[s];
@@ -582,7 +565,7 @@ __global__ void k_meta(int32_t n, int32_t ntypes, const uint32_t *__restrict__ t
     }
     // the root (internal node s) is a run when its subtree was collapsed
     const bool root_run = cost ? (c < 2 || cost[s] < 0.0f) : c <= leaf_size;
-    meta[t] = tree_meta(lo, hi, ext_floor, qbits, s, c, root_run, P);
+    return tree_meta(lo, hi, ext_floor, qbits, s, c, root_run, P);
 }
 
 // With the cost model: which internal nodes keep a record.  A node keeps one
@@ -622,9 +605,19 @@ __global__ __launch_bounds__(kBuildThreads) void k_kept_collapse(int32_t n, int3
 // One record per kept internal node (Karras id i).  Only about one id in
 // leaf_size keeps a record, so a workgroup first collects the kept ids of
 // kEmitItems x kBuildThreads consecutive ids into LDS (one ballot per wave and
-// step) and then writes their records with every lane busy.
-constexpr int kEmitItems = 8;
+// step) and then writes their records with every lane busy.  Every workgroup
+// works out the trees' metadata for itself, which costs less than a launch of
+// its own before this one; the first also leaves it for the traversal.
+template <bool kSmall>
+constexpr int kEmitItems = kSmall ? 1 : 8;
 
+//
+// kSmall (systems of at most kSmallEmit particles): P is the unscanned kept
+// counts, and every workgroup, now of fewer ids so that there are enough of
+// them, scans all of them in LDS first, again for less than a launch.
+constexpr int kSmallEmit = 8192;
+
+template <bool kSmall>
 __global__ __launch_bounds__(kBuildThreads) void k_emit(int32_t n, int32_t ntypes,
                                                         const uint32_t *__restrict__ keys,
                                                         const uint32_t *__restrict__ type_count,
@@ -633,18 +626,55 @@ __global__ __launch_bounds__(kBuildThreads) void k_emit(int32_t n, int32_t ntype
                                                         const int32_t *__restrict__ rf, const int32_t *__restrict__ rl,
                                                         const int32_t *__restrict__ parent,
                                                         const float4 *__restrict__ box,
-                                                        const uint32_t *__restrict__ P,
-                                                        const TreeMeta *__restrict__ meta, int32_t leaf_size,
+                                                        const uint32_t *__restrict__ kept,
+                                                        const float *__restrict__ cost, double ext_floor,
+                                                        TreeMeta *__restrict__ meta, int32_t leaf_size,
                                                         const uint32_t *__restrict__ kept_flag, int32_t qbits,
                                                         uint4 *__restrict__ records, int32_t *__restrict__ ropes) {
-    __shared__ int32_t s_ids[kEmitItems * kBuildThreads];
+    __shared__ int32_t s_ids[kEmitItems<kSmall> * kBuildThreads];
     __shared__ uint32_t s_count;
+    __shared__ TreeMeta s_meta[QBVH_MAX_TYPES];
+    __shared__ uint32_t s_P[kSmall ? kSmallEmit + 1 : 1];
+    __shared__ uint32_t s_sum[kBuildThreads / 64];
+    const uint32_t *P = kSmall ? s_P : kept;
     if (threadIdx.x == 0) s_count = 0;
+    if (kSmall) {
+        // each thread's stretch of the counts, then the stretches before it
+        constexpr int kStretch = kSmallEmit / kBuildThreads;
+        uint32_t v[kStretch], sum = 0;
+        const int32_t b = (int32_t)threadIdx.x * kStretch;
+#pragma unroll
+        for (int k = 0; k < kStretch; ++k) {
+            v[k] = b + k < n ? kept[b + k] : 0u;
+            sum += v[k];
+        }
+        uint32_t incl = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t x = __shfl_up(incl, o);
+            if ((int)__lane_id() >= o) incl += x;
+        }
+        if (__lane_id() == 63) s_sum[threadIdx.x >> 6] = incl;
+        __syncthreads();
+        sum = incl - sum;
+        for (int u = 0; u < (int)(threadIdx.x >> 6); ++u) sum += s_sum[u];
+#pragma unroll
+        for (int k = 0; k < kStretch; ++k) {
+            s_P[b + k] = sum;
+            sum += v[k];
+        }
+        if (threadIdx.x == kBuildThreads - 1) s_P[kSmallEmit] = sum;
+        __syncthreads();
+    }
+    if ((int32_t)threadIdx.x < ntypes) {
+        s_meta[threadIdx.x] =
+            type_meta((int)threadIdx.x, n, ntypes, type_count, sorted, box, P, qbits, leaf_size, cost, ext_floor);
+        if (blockIdx.x == 0) meta[threadIdx.x] = s_meta[threadIdx.x];
+    }
     __syncthreads();
     const int32_t lane = (int32_t)__lane_id();
-    const int64_t b0 = (int64_t)blockIdx.x * (kEmitItems * kBuildThreads);
+    const int64_t b0 = (int64_t)blockIdx.x * (kEmitItems<kSmall> * kBuildThreads);
 #pragma unroll
-    for (int k = 0; k < kEmitItems; ++k) {
+    for (int k = 0; k < kEmitItems<kSmall>; ++k) {
         const int64_t i = b0 + k * kBuildThreads + threadIdx.x;
         bool keep = false;
         if (i < n) {
@@ -666,7 +696,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_emit(int32_t n, int32_t ntype
     const uint32_t count = s_count;
     for (uint32_t e = threadIdx.x; e < count; e += kBuildThreads) {
         const int32_t i = s_ids[e];
-        const TreeMeta &m = meta[ntypes == 1 ? 0 : (keys[i] >> 30)];
+        const TreeMeta &m = s_meta[ntypes == 1 ? 0 : (keys[i] >> 30)];
         emit_record(i, rf[i], rl[i], m, sorted, left, parent, box, P, leaf_size, kept_flag, qbits, records,
                     ropes);
     }
@@ -710,7 +740,7 @@ void launch_tree_t(const Workspace &w, int32_t n, const TreeSource &src, int32_t
                       w.cost, reinterpret_cast<int32_t *>(w.visit), kept_leaf};
     int32_t nchunks = fit_chunks0(n);
     hipLaunchKernelGGL(k_tree_local<kCost>, dim3(nchunks), dim3(kFitThreads), 0, s, w.keys, w.vals, n, src, out,
-                       w.front[0], w.fcount[0], w.err, col);
+                       w.front[0], w.fcount[0], w.err, col, src.type_count);
     int64_t chunk = kFitChunk;
     int which = 0;
     while (chunk < n) {
@@ -824,43 +854,43 @@ Collapse collapse_model(float collapse_radius, int32_t leaf_size) {
 
 hipError_t launch_build(const Workspace &w, const float *d_pos, const int32_t *d_type, int32_t n, int32_t ntypes,
                         const float box[3], int32_t leaf_size, int32_t qbits, float collapse_radius, int32_t validate,
-                        hipStream_t s, const double *pos64, double *sorted64, const double *box64) {
+                        hipStream_t s, const double *pos64, double *sorted64, const double *box64, int32_t *clear) {
     const Collapse col = collapse_model(collapse_radius, leaf_size);
     const bool by_cost = col.kVball > 0.0f;
-    hipLaunchKernelGGL(k_init, dim3(1), dim3(64), 0, s, w.type_count, w.err);
-    const double sx = 1023.0 / (double)box[0];
-    const double sy = 1023.0 / (double)box[1];
-    const double sz = 1023.0 / (double)box[2];
-    if (pos64 != nullptr)
-        hipLaunchKernelGGL(k_morton<double>, grid_for((int64_t)n + 1), dim3(kBuildThreads), 0, s, pos64, d_type, n,
-                           ntypes, box64[0], box64[1], box64[2], sx, sy, sz, validate, w.keys, w.kept, w.err);
-    else
-        hipLaunchKernelGGL(k_morton<float>, grid_for((int64_t)n + 1), dim3(kBuildThreads), 0, s, d_pos, d_type, n,
-                           ntypes, (double)box[0], (double)box[1], (double)box[2], sx, sy, sz, validate, w.keys,
-                           w.kept, w.err);
-    hipError_t e = launch_radix_sort(w.keys, w.vals, w.keys2, w.vals2, w.hist, w.digit_total, n, w.tiles, s);
+    if (validate) hipLaunchKernelGGL(k_init, dim3(1), dim3(64), 0, s, w.err);
+    hipError_t e;
+    if (pos64 != nullptr) {
+        MortonArgs<double> m{pos64, d_type, ntypes, validate, {box64[0], box64[1], box64[2]}, {}, w.kept, w.err, clear};
+        for (int d = 0; d < 3; ++d) m.scale[d] = 1023.0 / (double)box[d];
+        e = launch_order(m, w, n, s);
+    } else {
+        MortonArgs<float> m{d_pos, d_type, ntypes, validate, {box[0], box[1], box[2]}, {}, w.kept, w.err, clear};
+        for (int d = 0; d < 3; ++d) m.scale[d] = 1023.0 / (double)box[d];
+        e = launch_order(m, w, n, s);
+    }
     if (e != hipSuccess) return e;
-    if (ntypes > 1) hipLaunchKernelGGL(k_type_count, dim3(1), dim3(64), 0, s, w.keys, n, w.type_count);
     if (n > 0) {
         // (with the cost model, which nodes keep a record is known only after the fit)
-        e = launch_tree(w, n, TreeSource{d_pos, nullptr, nullptr, 0, pos64, sorted64}, by_cost ? INT32_MAX : leaf_size,
-                        col, s);
+        e = launch_tree(w, n, TreeSource{d_pos, nullptr, nullptr, 0, pos64, sorted64, ntypes > 1 ? w.type_count : nullptr},
+                        by_cost ? INT32_MAX : leaf_size, col, s);
         if (e != hipSuccess) return e;
         if (by_cost)
             hipLaunchKernelGGL(k_kept_collapse, grid_for(n), dim3(kBuildThreads), 0, s, n, ntypes, w.keys,
                                w.type_count, w.rf, w.rl, w.parent, w.cost, leaf_size, w.visit, w.kept);
     }
-    e = launch_exclusive_scan(w.kept, n + 1, w.scan_part, s);
-    if (e != hipSuccess) return e;
+    const bool small = n <= kSmallEmit;
+    if (!small) {
+        e = launch_exclusive_scan(w.kept, n + 1, w.scan_part, s);
+        if (e != hipSuccess) return e;
+    }
     const double lmax = (double)fmaxf(box[0], fmaxf(box[1], box[2]));
     const double ext_floor = lmax * 0x1p-24;
-    hipLaunchKernelGGL(k_meta, dim3(1), dim3(64), 0, s, n, ntypes, w.type_count, w.sorted, w.box,
-                       w.kept, qbits, leaf_size, by_cost ? w.cost : nullptr, ext_floor, w.meta);
-    if (n > 0)
-        hipLaunchKernelGGL(k_emit, grid_for((n + kEmitItems - 1) / kEmitItems), dim3(kBuildThreads), 0, s, n, ntypes,
-                           w.keys, w.type_count,
-                           w.sorted, w.left, w.rf, w.rl, w.parent, w.box, w.kept, w.meta,
-                           leaf_size, by_cost ? w.visit : nullptr, qbits, w.records, w.ropes);
+    // (an empty tree's metadata comes from an emit of one idle workgroup)
+    const int32_t items = small ? kEmitItems<true> : kEmitItems<false>;
+    hipLaunchKernelGGL(small ? k_emit<true> : k_emit<false>, grid_for(n > 0 ? (n + items - 1) / items : 1),
+                       dim3(kBuildThreads), 0, s, n, ntypes, w.keys, w.type_count, w.sorted, w.left, w.rf, w.rl,
+                       w.parent, w.box, w.kept, by_cost ? w.cost : nullptr, ext_floor, w.meta, leaf_size,
+                       by_cost ? w.visit : nullptr, qbits, w.records, w.ropes);
     return hipGetLastError();
 }
 

@@ -33,6 +33,47 @@ __device__ __forceinline__ uint32_t morton_key(float x, float y, float z, double
            ((uint32_t)type << 30);
 }
 
+// What the Morton keys of a single system are made from: fp32 or fp64
+// positions.  fp64 data: the bins are taken from each coordinate rounded to
+// nearest fp32 (what the tree is built on) and the optional checks 0 <= x < L
+// are made in fp64 against the fp64 box; fp32 data: L is the fp32 box (compared
+// exactly after promotion).
+template <class T>
+struct MortonArgs {
+    const T *pos;         // [n][3]
+    const int32_t *type;  // [n] or nullptr
+    int32_t ntypes, validate;
+    double L[3], scale[3];
+    uint32_t *kept;       // kept[n] is cleared (the tree build writes the others)
+    int32_t *err;         // cleared without validation (with it k_init has cleared it)
+    int32_t *clear;       // a caller's flag to clear, or nullptr
+};
+
+template <class T>
+__device__ __forceinline__ void morton_clear(const MortonArgs<T> &m, int32_t n) {
+    m.kept[n] = 0;
+    if (!m.validate) *m.err = 0;
+    if (m.clear) *m.clear = 0;
+}
+
+template <class T>
+__device__ __forceinline__ uint32_t morton_of(const MortonArgs<T> &m, int32_t k) {
+    const T x = m.pos[3 * (int64_t)k + 0], y = m.pos[3 * (int64_t)k + 1], z = m.pos[3 * (int64_t)k + 2];
+    int32_t t = m.type ? m.type[k] : 0;
+    if (m.validate) {
+        const bool ok = ((double)x >= 0.0 && (double)x < m.L[0]) && ((double)y >= 0.0 && (double)y < m.L[1]) &&
+                        ((double)z >= 0.0 && (double)z < m.L[2]) && (t >= 0 && t < m.ntypes);
+        if (!ok) atomicOr(m.err, 1);
+    }
+    t = t < 0 ? 0 : (t >= m.ntypes ? m.ntypes - 1 : t);
+    return morton_key((float)x, (float)y, (float)z, m.scale[0], m.scale[1], m.scale[2], t);
+}
+
+// Whether a system's Morton keys and sort take one launch, and that launch.
+bool rank_sorted(int32_t n);
+template <class T>
+hipError_t launch_morton_rank(const MortonArgs<T> &m, int32_t n, uint32_t *keys, uint32_t *vals, hipStream_t s);
+
 struct Segment {
     int32_t s, e;
 };

@@ -166,12 +166,14 @@ void fill_trav_box(TravArgs &a, const double box[3]);
 // d_pos is null and pos64 [n][3] holds the data in the fp64 box box64 (box
 // is box64 rounded to fp32): the tree is built on the data rounded to
 // nearest fp32, validation is done in fp64, and sorted64 [n][4] receives the
-// fp64 positions in Z order.
+// fp64 positions in Z order.  `clear`, when given, is set to 0 (a caller's
+// overflow flag).
 hipError_t launch_build(const Workspace &w, const float *d_pos, const int32_t *d_type, int32_t n,
                         int32_t ntypes, const float box[3], int32_t leaf_size, int32_t qbits,
                         float collapse_radius, int32_t validate, hipStream_t s, const double *pos64 = nullptr,
-                        double *sorted64 = nullptr, const double *box64 = nullptr);
-hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool paper, const uint4 *qpoint,
+                        double *sorted64 = nullptr, const double *box64 = nullptr, int32_t *clear = nullptr);
+// `cleared`: the overflow flag is 0 already.
+hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool paper, const uint4 *qpoint, bool cleared,
                            hipStream_t s);
 // fp64 particle data: the positions rounded to fp32 for the build (with the
 // fp64 range and type checks when validate is set), and after the build the
@@ -201,6 +203,8 @@ struct TreeSource {
     // [n][4] (x, y, z, 0) in Z order
     const double *pos64;
     double *sorted64;
+    // single system of several types: receives the particles per type
+    uint32_t *type_count;
 };
 // Radix tree, Z-ordered particles, node boxes (and costs) and kept-node counts
 // (nodes longer than kept_leaf) from the sorted keys and values.

@@ -11,7 +11,7 @@
 // per digit value and wave, popcount below the lane) and writes through LDS
 // so that global stores land in contiguous runs.  No workgroup waits on
 // another, so every wave always finishes.
-#include "qbvh_internal.h"
+#include "build_common.h"
 
 namespace qbi {
 namespace {
@@ -23,10 +23,17 @@ constexpr int kSortThreads = kSortWaves * 64;       // 512
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;  // 4096 keys per tile
 constexpr int kHistThreads = 256;
+// Up to this many tiles the scatter sums the tiles' digit counts itself, which
+// saves the digit scan's launch (build of 30k particles 99 -> 91 us, 200k 124
+// -> 118, 400k 135 -> 132; 1M, 245 tiles, 173 -> 184).
+constexpr int kFewTiles = 128;
 
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;  // 2048
+// Up to this many blocks the down-sweep adds up the blocks' sums itself, which
+// saves a launch (1 to 2 us of a build, 3 at N = 8M).
+constexpr int kSumBlocks = 4096;
 
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
     const int lane = __lane_id();
@@ -126,7 +133,9 @@ __device__ __forceinline__ int32_t xcd_tile() {
     return (int32_t)(xcd * qq + (xcd < rr ? xcd : rr) + (b >> 3));
 }
 
-template <bool kSeg>
+// kFew: counts tile by tile, hist[256 tile + digit], for the scatter that sums
+// them itself.
+template <bool kSeg, bool kFew>
 __global__ __launch_bounds__(kHistThreads) void k_radix_hist(const uint32_t *__restrict__ keys, int32_t n,
                                                              int32_t shift, uint32_t *__restrict__ hist,
                                                              int32_t tiles, const int32_t *__restrict__ tile_first,
@@ -134,7 +143,8 @@ __global__ __launch_bounds__(kHistThreads) void k_radix_hist(const uint32_t *__r
     __shared__ uint32_t h[kHistThreads / 64][kRadix];
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
-    const TileView tv = tile_view<kSeg>(xcd_tile(), n, tiles, tile_first, seg_off, nseg);
+    const int32_t tile = xcd_tile();
+    const TileView tv = tile_view<kSeg>(tile, n, tiles, tile_first, seg_off, nseg);
     for (int i = tid; i < (kHistThreads / 64) * kRadix; i += kHistThreads) (&h[0][0])[i] = 0;
     __syncthreads();
     if (tv.nvalid == kSortTile && (tv.base & 3) == 0) {
@@ -159,7 +169,7 @@ __global__ __launch_bounds__(kHistThreads) void k_radix_hist(const uint32_t *__r
     uint32_t c = 0;
 #pragma unroll
     for (int w = 0; w < kHistThreads / 64; ++w) c += h[w][tid];
-    hist[tv.hbase + (int64_t)tid * tv.hstride] = c;
+    hist[kFew ? (int64_t)tile * kRadix + tid : tv.hbase + (int64_t)tid * tv.hstride] = c;
 }
 
 // One workgroup per digit: exclusive scan of that digit's tile counts in place.
@@ -190,7 +200,7 @@ __global__ __launch_bounds__(kScanThreads) void k_radix_digit_scan(uint32_t *__r
     if (threadIdx.x == 0) digit_total[blockIdx.x] = carry;
 }
 
-template <bool kSeg>
+template <bool kSeg, bool kFew>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const uint32_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in, uint32_t *__restrict__ keys_out,
     uint32_t *__restrict__ vals_out, int32_t n, int32_t shift, const uint32_t *__restrict__ hist,
@@ -211,7 +221,28 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
 
     for (int i = tid; i < kSortWaves * kRadix; i += kSortThreads) (&s_wcnt[0][0])[i] = 0;
 
-    if (!kSeg) {
+    if (kFew) {
+        // the tiles' counts lie tile by tile, unscanned: half the threads sum a
+        // digit's counts over each half of the tiles, and over those before
+        // this one
+        const int32_t dg = tid & (kRadix - 1), me = xcd_tile(), mid = (tiles + 1) / 2;
+        const int32_t t0 = tid < kRadix ? 0 : mid, t1 = tid < kRadix ? mid : tiles;
+        uint32_t sum = 0, before = 0;
+#pragma unroll 8
+        for (int32_t t = t0; t < t1; ++t) {
+            const uint32_t c = hist[(int64_t)t * kRadix + dg];
+            sum += c;
+            before += t < me ? c : 0u;
+        }
+        s_vals[tid] = sum;
+        s_keys[tid] = before;
+        __syncthreads();
+        const uint32_t dt = tid < kRadix ? s_vals[tid] + s_vals[tid + kRadix] : 0u;
+        if (tid < kRadix) before += s_keys[tid + kRadix];
+        uint32_t tot;
+        const uint32_t gstart = block_exclusive_scan<kSortThreads>(dt, s_scan, tot);
+        if (tid < kRadix) s_goff[tid] = gstart + before;
+    } else if (!kSeg) {
         // global start of each digit: exclusive scan of the digit totals
         uint32_t dt = tid < kRadix ? digit_total[tid] : 0u;
         uint32_t tot;
@@ -287,90 +318,55 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     }
 }
 
-// A whole sort of at most one tile in one workgroup: the four passes of the
-// tile scatter above, each leaving the tile in LDS for the next (a small
-// system's sort in one launch instead of twelve).
-__global__ __launch_bounds__(kSortThreads) void k_radix_sort_tile(uint32_t *__restrict__ keys,
-                                                                  uint32_t *__restrict__ vals, int32_t n) {
-    __shared__ uint32_t s_keys[kSortTile];
-    __shared__ uint32_t s_vals[kSortTile];
-    __shared__ uint32_t s_wcnt[kSortWaves][kRadix];
-    __shared__ uint32_t s_dstart[kRadix];
-    __shared__ uint32_t s_scan[kSortWaves];
+// Morton keys and their sort in one launch, for systems of at most
+// kRankSort particles.  Every workgroup makes all the keys (in LDS) and counts,
+// for each of its 16 particles, the keys that sort before it: that is its
+// position.  n^2 / 2 comparisons spread over the chip take less time than four
+// radix passes, bound by VALU issue, on one compute unit: N = 4000 8.8 us, with
+// the keys and radix passes in one workgroup 18.3, in two launches 4.8 + 17.0.
+// The line lies where nine launches of the radix path catch up (whole build by
+// ranks and by radix passes: 8000 particles 67 and 96 us, 11000 80 and 88,
+// 16000 116 and 92).
+constexpr int kRankSort = 11 * 1024;
+constexpr int kRankThreads = 1024;
+constexpr int kRankItems = 16;
 
-    const int tid = threadIdx.x;
-    const int lane = __lane_id();
-    const int wave = tid >> 6;
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    uint32_t k[kSortItems], v[kSortItems], r[kSortItems];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const int32_t j = wave * 64 * kSortItems + i * 64 + lane;
-        k[i] = j < n ? keys[j] : 0u;
-        v[i] = (uint32_t)j;
+template <class T>
+__global__ __launch_bounds__(kRankThreads) void k_morton_rank(MortonArgs<T> m, int32_t n, uint32_t *__restrict__ keys,
+                                                              uint32_t *__restrict__ vals) {
+    __shared__ __align__(16) uint32_t s_keys[kRankSort];
+    __shared__ uint32_t s_rank[kRankItems];
+    const int tid = threadIdx.x, lane = __lane_id();
+    if (blockIdx.x == 0 && tid == 0) morton_clear(m, n);
+    if (tid < kRankItems) s_rank[tid] = 0;
+    for (int32_t j = tid; j < n; j += kRankThreads) s_keys[j] = morton_of(m, j);
+    __syncthreads();
+    // a wavefront's four groups of 16 lanes take the same 16 particles against
+    // four stretches of the keys
+    const int32_t i = (int32_t)blockIdx.x * kRankItems + (lane & (kRankItems - 1));
+    const uint32_t ki = s_keys[i < n ? i : 0];
+    constexpr int kStretches = kRankThreads / kRankItems;
+    const int32_t len = ((n + 4 * kStretches - 1) / (4 * kStretches)) * 4;
+    const int32_t j0 = (tid / kRankItems) * len, j1 = j0 + len < n ? j0 + len : n;
+    uint32_t before = 0;
+    auto count = [&](uint32_t kj, int32_t j) {
+        if (j < j1) before += (kj < ki || (kj == ki && j < i)) ? 1u : 0u;
+    };
+    for (int32_t j = j0; j < j1; j += 4) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(&s_keys[j]);  // (entries past n are not counted)
+        count(q.x, j);
+        count(q.y, j + 1);
+        count(q.z, j + 2);
+        count(q.w, j + 3);
     }
-    for (int pass = 0; pass < 32 / kRadixBits; ++pass) {
-        const int shift = pass * kRadixBits;
-        for (int i = tid; i < kSortWaves * kRadix; i += kSortThreads) (&s_wcnt[0][0])[i] = 0;
-        __syncthreads();
-        // stable rank within the wave's chunk: items in order i, then lane
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            const bool valid = wave * 64 * kSortItems + i * 64 + lane < n;
-            const uint32_t d = (k[i] >> shift) & (kRadix - 1);
-            const uint64_t peers = digit_peers(d, valid);
-            if (valid) {
-                const uint32_t before = s_wcnt[wave][d];
-                const uint32_t rk = (uint32_t)__popcll(peers & lt_mask);
-                r[i] = before + rk;
-                if (rk == 0) s_wcnt[wave][d] = before + (uint32_t)__popcll(peers);
-            }
-        }
-        __syncthreads();
-        uint32_t cnt = 0;
-        if (tid < kRadix) {
-            uint32_t sum = 0;
-#pragma unroll
-            for (int w = 0; w < kSortWaves; ++w) {
-                const uint32_t c = s_wcnt[w][tid];
-                s_wcnt[w][tid] = sum;
-                sum += c;
-            }
-            cnt = sum;
-        }
-        {
-            uint32_t tot;
-            const uint32_t ds = block_exclusive_scan<kSortThreads>(cnt, s_scan, tot);
-            if (tid < kRadix) s_dstart[tid] = ds;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            if (wave * 64 * kSortItems + i * 64 + lane < n) {
-                const uint32_t d = (k[i] >> shift) & (kRadix - 1);
-                const uint32_t p = s_dstart[d] + s_wcnt[wave][d] + r[i];
-                s_keys[p] = k[i];
-                s_vals[p] = v[i];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            const int32_t j = wave * 64 * kSortItems + i * 64 + lane;
-            if (j < n) {
-                k[i] = s_keys[j];
-                v[i] = s_vals[j];
-            }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const int32_t j = wave * 64 * kSortItems + i * 64 + lane;
-        if (j < n) {
-            keys[j] = k[i];
-            vals[j] = v[i];
-        }
+    before += (uint32_t)__shfl_xor((int32_t)before, 16);
+    before += (uint32_t)__shfl_xor((int32_t)before, 32);
+    if (lane < kRankItems) atomicAdd(&s_rank[lane], before);
+    __syncthreads();
+    if (tid < kRankItems && i < n) {
+        const uint32_t at = s_rank[tid];
+        keys[at] = ki;
+        vals[at] = (uint32_t)i;
     }
 }
 
@@ -444,9 +440,20 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_single(uint32_t *__restri
     }
 }
 
+// kSum: the partials are the blocks' sums, unscanned; a block adds up those
+// before it.
+template <bool kSum>
 __global__ __launch_bounds__(kScanThreads) void k_scan_down(uint32_t *__restrict__ data, int32_t len,
                                                             const uint32_t *__restrict__ partials) {
     __shared__ uint32_t lds[kScanThreads / 64];
+    uint32_t start = 0;
+    if (kSum) {
+        uint32_t part = 0;
+        for (int32_t j = threadIdx.x; j < (int32_t)blockIdx.x; j += kScanThreads) part += partials[j];
+        (void)block_exclusive_scan<kScanThreads>(part, lds, start);
+    } else {
+        start = partials[blockIdx.x];
+    }
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     uint32_t v[kScanItems];
     load_items(data, base, len, v);
@@ -454,7 +461,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(uint32_t *__restrict
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) s += v[k];
     uint32_t tot;
-    uint32_t ex = block_exclusive_scan<kScanThreads>(s, lds, tot) + partials[blockIdx.x];
+    uint32_t ex = block_exclusive_scan<kScanThreads>(s, lds, tot) + start;
     uint32_t o[kScanItems];
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
@@ -478,12 +485,7 @@ int32_t scan_blocks(int32_t len) { return len <= 0 ? 1 : (len + kScanTile - 1) /
 
 hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, uint32_t *vals2, uint32_t *hist,
                              uint32_t *digit_total, int32_t n, int32_t tiles, hipStream_t s) {
-    // (one element still goes through the tile sort, which writes its value)
     if (n <= 0) return hipSuccess;
-    if (n <= kSortTile) {
-        hipLaunchKernelGGL(k_radix_sort_tile, dim3(1), dim3(kSortThreads), 0, s, keys, vals, n);
-        return hipGetLastError();
-    }
     // (whole tiles read their keys 16 bytes at a time)
     if (((reinterpret_cast<uintptr_t>(keys) | reinterpret_cast<uintptr_t>(keys2)) & 15u) != 0) return hipErrorInvalidValue;
     const int32_t t = radix_tiles(n);
@@ -491,11 +493,18 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, ui
     uint32_t *ki = keys, *vi = vals, *ko = keys2, *vo = vals2;
     for (int pass = 0; pass < 32 / kRadixBits; ++pass) {
         const int shift = pass * kRadixBits;
-        hipLaunchKernelGGL(k_radix_hist<false>, dim3(t), dim3(kHistThreads), 0, s, ki, n, shift, hist, t,
-                           nullptr, nullptr, 0);
-        hipLaunchKernelGGL(k_radix_digit_scan, dim3(kRadix), dim3(kScanThreads), 0, s, hist, t, digit_total);
-        hipLaunchKernelGGL(k_radix_scatter<false>, dim3(t), dim3(kSortThreads), 0, s, ki, vi, ko, vo, n, shift,
-                           hist, digit_total, t, nullptr, nullptr, 0, pass == 0);
+        if (t <= kFewTiles) {
+            hipLaunchKernelGGL((k_radix_hist<false, true>), dim3(t), dim3(kHistThreads), 0, s, ki, n, shift, hist, t,
+                               nullptr, nullptr, 0);
+            hipLaunchKernelGGL((k_radix_scatter<false, true>), dim3(t), dim3(kSortThreads), 0, s, ki, vi, ko, vo, n,
+                               shift, hist, nullptr, t, nullptr, nullptr, 0, pass == 0);
+        } else {
+            hipLaunchKernelGGL((k_radix_hist<false, false>), dim3(t), dim3(kHistThreads), 0, s, ki, n, shift, hist, t,
+                               nullptr, nullptr, 0);
+            hipLaunchKernelGGL(k_radix_digit_scan, dim3(kRadix), dim3(kScanThreads), 0, s, hist, t, digit_total);
+            hipLaunchKernelGGL((k_radix_scatter<false, false>), dim3(t), dim3(kSortThreads), 0, s, ki, vi, ko, vo, n,
+                               shift, hist, digit_total, t, nullptr, nullptr, 0, pass == 0);
+        }
         uint32_t *tk = ki, *tv = vi;
         ki = ko;
         vi = vo;
@@ -506,6 +515,18 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, ui
     static_assert((32 / kRadixBits) % 2 == 0, "result must end in the primary buffers");
     return hipGetLastError();
 }
+
+bool rank_sorted(int32_t n) { return n <= kRankSort; }
+
+template <class T>
+hipError_t launch_morton_rank(const MortonArgs<T> &m, int32_t n, uint32_t *keys, uint32_t *vals, hipStream_t s) {
+    if (!rank_sorted(n)) return hipErrorInvalidValue;
+    const int32_t blocks = n > 0 ? (n + kRankItems - 1) / kRankItems : 1;
+    hipLaunchKernelGGL(k_morton_rank<T>, dim3((unsigned)blocks), dim3(kRankThreads), 0, s, m, n, keys, vals);
+    return hipGetLastError();
+}
+template hipError_t launch_morton_rank(const MortonArgs<float> &, int32_t, uint32_t *, uint32_t *, hipStream_t);
+template hipError_t launch_morton_rank(const MortonArgs<double> &, int32_t, uint32_t *, uint32_t *, hipStream_t);
 
 int32_t seg_radix_tiles(int32_t n) { return (n + kSortTile - 1) / kSortTile; }
 
@@ -518,11 +539,11 @@ hipError_t launch_radix_sort_segmented(uint32_t *keys, uint32_t *vals, uint32_t 
     uint32_t *ki = keys, *vi = vals, *ko = keys2, *vo = vals2;
     for (int pass = 0; pass < 32 / kRadixBits; ++pass) {
         const int shift = pass * kRadixBits;
-        hipLaunchKernelGGL(k_radix_hist<true>, dim3(tiles), dim3(kHistThreads), 0, s, ki, n, shift, hist, tiles,
+        hipLaunchKernelGGL((k_radix_hist<true, false>), dim3(tiles), dim3(kHistThreads), 0, s, ki, n, shift, hist, tiles,
                            tile_first, seg_off, nseg);
         hipError_t e = launch_exclusive_scan(hist, kRadix * tiles, scan_part, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_radix_scatter<true>, dim3(tiles), dim3(kSortThreads), 0, s, ki, vi, ko, vo, n, shift,
+        hipLaunchKernelGGL((k_radix_scatter<true, false>), dim3(tiles), dim3(kSortThreads), 0, s, ki, vi, ko, vo, n, shift,
                            hist, nullptr, tiles, tile_first, seg_off, nseg, pass == 0);
         uint32_t *tk = ki, *tv = vi;
         ki = ko;
@@ -542,8 +563,12 @@ hipError_t launch_exclusive_scan(uint32_t *data, int32_t len, uint32_t *partials
     if ((reinterpret_cast<uintptr_t>(data) & 31u) != 0) return hipErrorInvalidValue;
     const int32_t nb = scan_blocks(len);
     hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kScanThreads), 0, s, data, len, partials);
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partials, nb);
-    hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kScanThreads), 0, s, data, len, partials);
+    if (nb <= kSumBlocks) {
+        hipLaunchKernelGGL(k_scan_down<true>, dim3(nb), dim3(kScanThreads), 0, s, data, len, partials);
+    } else {
+        hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partials, nb);
+        hipLaunchKernelGGL(k_scan_down<false>, dim3(nb), dim3(kScanThreads), 0, s, data, len, partials);
+    }
     return hipGetLastError();
 }
 

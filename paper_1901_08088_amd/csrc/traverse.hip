@@ -962,9 +962,9 @@ void launch_block_batch(const BatchLaunch &b, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool paper, const uint4 *qpoint,
+hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool paper, const uint4 *qpoint, bool cleared,
                            hipStream_t s) {
-    hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(64), 0, s, a.overflow);
+    if (!cleared) hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(64), 0, s, a.overflow);
     if (a.n > 0) {
         if (paper)  // fp32 data only
             launch_mode<kPaper>(a, block, vec4, qpoint, s);
