@@ -492,8 +492,9 @@ int run_many(int32_t nsys, const qbvh_system_t *sys, const qbvh_batch_opts_t *op
     fill_table(*c, nsys, sys, trav, cfg, qpw, img);
     e = upload_table(*c, img);
     if (e != hipSuccess) return hip_fail(e);
-    const BatchLaunch b =
+    BatchLaunch b =
         make_launch(*c, nsys, (int32_t)total, (int32_t)tiles, (int32_t)blocks, (int32_t)tblocks, cfg, vec4);
+    b.qpw = qpw;
 
     Pending q{cand, nullptr, nullptr};
     if (tuning) {

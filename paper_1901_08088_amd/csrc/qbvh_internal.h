@@ -124,23 +124,23 @@ struct BatchLaunch {
     TreeMeta *meta;             // [nsys][QBVH_MAX_TYPES]
     int32_t nsys, total, blocks, tiles, tblocks;
     int32_t leaf_size, qbits, block_size;
+    int32_t qpw;                // queries per wavefront, of every system
     bool vec4;
 };
 
 // Host helpers shared by the interface files.
 
 // Queries per wavefront of a single system.  A wavefront walks the union of
-// its queries' paths, so a small system is faster with fewer queries per
-// wavefront (a smaller union each, more wavefronts in parallel) until there
-// are about two wavefronts per SIMD, and below 8 queries until there is about
-// one; a large one keeps all 64 lanes busy.  (Measured on LJ fluids of 1000 to
-// 260000 particles: 2 queries up to 4000, 8 at 15000 and 30000, 16 at 65000,
-// 32 at 130000, 64 from 260000.)
+// its queries' paths and tests its candidates, so a small system is faster
+// with fewer queries per wavefront (a smaller union each, more wavefronts in
+// parallel); a large one keeps all 64 lanes busy.  The lines lie where the
+// traversals of LJ (R = 3.4) and WCA (R = 1.52) fluids cross, in us for the
+// smaller and the larger count: 1000 particles 1 23 / 13, 2 32 / 14; 4000
+// 2 34 / 15, 4 38 / 15; 8000 2 45 / 21, 4 45 / 18; 15000 8 46 / 21, 16 52 / 23;
+// 30000 8 59 / 27, 16 59 / 24; 65000 16 82 / 33, 32 92 / 33; 130000 32 97 / 46,
+// 64 111 / 50; 260000 32 192 / 85, 64 174 / 78.
 inline int32_t queries_per_wave(int64_t n) {
-    int32_t q = 64;
-    while (q > 8 && (n + q - 1) / q < 2048) q /= 2;
-    while (q > 2 && (n + q - 1) / q < 1024) q /= 2;
-    return q;
+    return n < 2048 ? 1 : n < 4096 ? 2 : n < 8192 ? 4 : n < 24576 ? 8 : n < 65536 ? 16 : n < 131072 ? 32 : 64;
 }
 
 constexpr int32_t kMaxParticles = (1 << 27) - 1;  // particle runs store a sorted position in 27 bits

@@ -110,17 +110,26 @@ constexpr int kParts = 64 + 4 * kOpen;
 constexpr int kWords = 16;
 constexpr int kTables = 8;
 
+// Few queries.  With at most 16 queries per wavefront (small systems) a query's
+// four lanes, one per row of 16 lanes, each hold the mask of a quarter of the
+// batch as the products leave it.  They write their entries straight to the
+// row, each from its own place in it, and nothing is queued: serial steps
+// count there, not stores (traversal of 1000 particles 32 -> 23 us, 30k 69 -> 59).
+constexpr int kFewQueries = 16;
+
 // One wavefront's LDS: 9.6 KB, so four wavefronts per SIMD fit a compute unit.
+template <bool kFew>
 struct WaveLds {
-    uint32_t word[kWords + 1][64];  // per query: candidate mask (16 bits, first highest), byte offset into index
-    int32_t index[kTables * 64 + 64 * 4];  // original indices of each batch's candidates; the entries carried over
+    uint32_t word[kFew ? 1 : kWords + 1][64];  // per query: candidate mask (16 bits, first highest), byte offset into index
+    int32_t index[kFew ? 64 : kTables * 64 + 64 * 4];  // original indices of each batch's candidates; the entries
+                                                       // carried over
     int32_t sref[kStack];           // stack: record index, or run reference (< 0)
     uint2 part[kParts];             // queue: first sorted position, length - 1 from bit 27; particles
                                     // queued before the part, image code from bit 16
     uint8_t simg[kStack];           // image codes
     uint8_t map[64];                // scratch: part starts by slot; candidate slot of each query's own particle
 };
-static_assert(sizeof(WaveLds) <= 10240, "four wavefronts per SIMD");
+static_assert(sizeof(WaveLds<false>) <= 10240, "four wavefronts per SIMD");
 
 // Periodic image m in {-1, 0, 1}^3 as three 2-bit fields m + 1; kHome is m = 0.
 constexpr uint32_t kHome = 1u | (1u << 2) | (1u << 4);
@@ -154,7 +163,7 @@ struct TreeTest {
 
 // Writes the rows' waiting entries, all but the last (fewer than 4) of each.
 template <bool kVec4>
-__device__ __forceinline__ void write_rows(Query &q, WaveLds &w, int32_t *nbr, int32_t max_nbr, uint32_t lane) {
+__device__ __forceinline__ void write_rows(Query &q, WaveLds<false> &w, int32_t *nbr, int32_t max_nbr, uint32_t lane) {
     const uint32_t mine = kTables * 64 + lane * 4;  // the lane's carried entries
     w.word[q.words][lane] = 0;
     // the word in hand and the next one
@@ -200,7 +209,7 @@ __device__ __forceinline__ void write_rows(Query &q, WaveLds &w, int32_t *nbr, i
 
 // Queues the candidates `m` (first of 32 slots highest) of a batch; `base` is
 // the byte offset of their indices.
-__device__ __forceinline__ void add_words(uint32_t m, uint32_t base, Query &q, WaveLds &w, uint32_t lane) {
+__device__ __forceinline__ void add_words(uint32_t m, uint32_t base, Query &q, WaveLds<false> &w, uint32_t lane) {
     const uint32_t a = (m & 0xFFFF0000u) | base, b = (m << 16) | (base + 64u);
     w.word[q.words][lane] = a;
     q.words += a >= 0x10000u ? 1u : 0u;
@@ -377,7 +386,8 @@ struct Batch {
     uint32_t img;
 };
 
-__device__ __forceinline__ Batch take_batch(uint32_t at, uint32_t parts, WaveLds &w,
+template <bool kFew>
+__device__ __forceinline__ Batch take_batch(uint32_t at, uint32_t parts, WaveLds<kFew> &w,
                                             const float4 *__restrict__ sorted, uint32_t lane) {
     Batch b;
     const uint2 mine = w.part[min(at + lane, parts - 1u)];
@@ -403,6 +413,19 @@ __device__ __forceinline__ Batch take_batch(uint32_t at, uint32_t parts, WaveLds
     return b;
 }
 
+// A pair too near the cutoff for the product: 0 out, 1 in, 2 in by the fp64
+// arithmetic.  ci < 0: an empty slot.
+template <Mode kMode, class Args>
+__device__ __forceinline__ int decide(const float4 &qp, int32_t k, int32_t ci, uint32_t img, const TreeTest &tt,
+                                      Args &a, const TreeMeta &tree, const float4 *__restrict__ sorted,
+                                      const double *__restrict__ sorted64, const uint4 *__restrict__ qpoint) {
+    if (ci < 0) return 0;
+    if constexpr (kMode == kPaper)
+        return decide_cell(qp, qpoint[ci], img, tt, tree, a.L, a.Lf) ? 1 : 0;
+    else
+        return decide_pair<kMode == kExact64>(qp, k, sorted[ci], ci, img, tt, a.L, sorted64);
+}
+
 // Slots [from, to) of a half batch as a mask, first slot highest.
 __device__ __forceinline__ uint32_t slot_range(uint32_t from, uint32_t to, uint32_t half) {
     const uint32_t lo = half * 32u, a = from > lo ? min(from - lo, 32u) : 0u, b = to > lo ? min(to - lo, 32u) : 0u;
@@ -410,14 +433,13 @@ __device__ __forceinline__ uint32_t slot_range(uint32_t from, uint32_t to, uint3
     return b > a ? (uint32_t)((ones >> b) & ~(ones >> a)) : 0u;
 }
 
-// The batch against the wavefront's queries; accepted candidates are queued
-// for the rows.  `table` is the index table it uses.
-template <bool kVec4, Mode kMode, class Args>
-__device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Batch &t, uint32_t table, int groups,
-                                           const float *bq, const float *cq, float ox, float oy, float oz,
-                                           int32_t kw0, Query &q, WaveLds &w, const float4 *__restrict__ sorted,
-                                           const double *__restrict__ sorted64, const uint4 *__restrict__ qpoint,
-                                           const TreeMeta &tree, uint32_t lane) {
+// The batch's candidates as matrix rows (c), their original indices in the
+// given index table, and which of them are queries of this wavefront.  Returns
+// whether some candidate comes through a shifted image.
+template <bool kFew, class Args>
+__device__ __forceinline__ bool stage_batch(Args &a, const Batch &t, uint32_t table, float ox, float oy, float oz,
+                                            int32_t kw0, WaveLds<kFew> &w, float (&c)[4], uint64_t &mine,
+                                            uint32_t lane) {
     const uint32_t slot = slot_of(lane);
     const bool on = t.idx >= 0;
     float osx = ox, osy = oy, osz = oz;
@@ -427,26 +449,41 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
         osy = (float)((double)oy + (double)((int)((t.img >> 2) & 3u) - 1) * a.L[1]);
         osz = (float)((double)oz + (double)((int)((t.img >> 4) & 3u) - 1) * a.L[2]);
     }
-    float c[4];
     c[0] = t.p.x - osx;
     c[1] = t.p.y - osy;
     c[2] = t.p.z - osz;
     c[3] = on ? __builtin_fmaf(c[2], c[2], __builtin_fmaf(c[1], c[1], c[0] * c[0])) : 1e30f;
     w.index[table * 64u + slot] = ~__float_as_int(t.p.w);
     // a query's own particle is never listed: it can only come up unshifted
-    const uint64_t mine = __ballot(on && t.img == kHome && (uint32_t)(t.idx - kw0) < 64u);
-    uint32_t self_lo = 0, self_hi = 0;
+    mine = __ballot(on && t.img == kHome && (uint32_t)(t.idx - kw0) < 64u);
     if (mine) {
         w.map[lane] = 64;
         wave_lds_sync();
         if (lane_bit(mine)) w.map[t.idx - kw0] = (uint8_t)slot;
-        wave_lds_sync();
+    }
+    wave_lds_sync();
+    transpose4(c[0], c[1], c[2], c[3]);
+    return shifted;
+}
+
+// The batch against the wavefront's queries; accepted candidates are queued
+// for the rows.  `table` is the index table it uses.
+template <bool kVec4, Mode kMode, class Args>
+__device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Batch &t, uint32_t table, int groups,
+                                           const float *bq, const float *cq, float ox, float oy, float oz,
+                                           int32_t kw0, Query &q, WaveLds<false> &w,
+                                           const float4 *__restrict__ sorted, const double *__restrict__ sorted64,
+                                           const uint4 *__restrict__ qpoint, const TreeMeta &tree, uint32_t lane) {
+    float c[4];
+    uint64_t mine;
+    const bool shifted = stage_batch<false>(a, t, table, ox, oy, oz, kw0, w, c, mine, lane);
+    uint32_t self_lo = 0, self_hi = 0;
+    if (mine) {
         const uint32_t s = w.map[lane];
         self_lo = s < 32u ? 0x80000000u >> s : 0u;
         self_hi = s >= 32u && s < 64u ? 0x80000000u >> (s - 32u) : 0u;
         wave_lds_sync();
     }
-    transpose4(c[0], c[1], c[2], c[3]);
 
     uint32_t m[4] = {0u, 0u, 0u, 0u};
     float nr[4] = {__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
@@ -484,13 +521,7 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
             const int32_t ci = __shfl(t.idx, from);
             const uint32_t im = (uint32_t)__shfl((int32_t)t.img, from);
             if ((nlo | nhi) != 0u) {
-                int r = 0;
-                if (ci >= 0) {
-                    if constexpr (kMode == kPaper)
-                        r = decide_cell(qp, qpoint[ci], im, tt, tree, a.L, a.Lf) ? 1 : 0;
-                    else
-                        r = decide_pair<kMode == kExact64>(qp, q.k, sorted[ci], ci, im, tt, a.L, sorted64);
-                }
+                const int r = decide<kMode>(qp, q.k, ci, im, tt, a, tree, sorted, sorted64, qpoint);
                 if (b < 32u) {
                     nlo ^= bit;
                     lo |= r == 1 ? bit : 0u;
@@ -540,6 +571,98 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
     wave_lds_sync();
 }
 
+// How many of a 64-slot mask's first p slots are set (first slot highest).
+__device__ __forceinline__ int32_t set_before(uint64_t m, uint32_t p) {
+    return p == 0u ? 0 : __popcll(m >> (64u - p));
+}
+
+// The batch against at most kFewQueries queries: lane l has query l % 16 and
+// slots 16 (l / 16) .. + 15.
+template <Mode kMode, class Args>
+__device__ __forceinline__ void test_batch_few(Args &a, const TreeTest &tt, const Batch &t, float bq, float cq,
+                                               float ox, float oy, float oz, int32_t kw0, Query &q,
+                                               WaveLds<true> &w, const float4 *__restrict__ sorted,
+                                               const double *__restrict__ sorted64,
+                                               const uint4 *__restrict__ qpoint, const TreeMeta &tree,
+                                               uint32_t lane) {
+    float c[4];
+    uint64_t mine;
+    const bool shifted = stage_batch<true>(a, t, 0, ox, oy, oz, kw0, w, c, mine, lane);
+    const uint32_t row = lane >> 4;
+    const int qi = (int)(lane & 15u);
+    uint32_t self = 0;
+    if (mine) {
+        const uint32_t s = w.map[qi];
+        self = (s >> 4) == row ? 0x80000000u >> (s & 15u) : 0u;
+        wave_lds_sync();
+    }
+    uint32_t m;
+    float nr;
+    test_group(c, bq, cq, m, nr);
+    m = (m << 16) & ~self;
+    const float band = shifted ? tt.band_img : tt.band;
+    uint32_t x = 0;  // accepted by the fp64 arithmetic
+    if (__any(nr <= band) || tt.force) {
+        // some pair lies too near the cutoff for the product to decide
+        uint32_t near = tt.force ? 0xFFFF0000u : near_group(c, bq, cq, band) << 16;
+        near = q.valid ? near & ~self : 0u;
+        m &= ~near;
+        const float4 qp = sorted[q.k];
+        while (__any(near != 0u)) {
+            const uint32_t b = (uint32_t)__builtin_clz(near | 1u) & 15u, bit = 0x80000000u >> b;
+            const int from = (int)slot_of(row * 16u + b);
+            const int32_t ci = __shfl(t.idx, from);
+            const uint32_t im = (uint32_t)__shfl((int32_t)t.img, from);
+            if (near != 0u) {
+                const int r = decide<kMode>(qp, q.k, ci, im, tt, a, tree, sorted, sorted64, qpoint);
+                near ^= bit;
+                m |= r == 1 ? bit : 0u;
+                x |= r == 2 ? bit : 0u;
+            }
+        }
+    }
+    int32_t *out = a.nbr + (int64_t)q.orig * a.max_nbr;
+    if (kMode != kPaper && __any(x != 0u)) {
+        // a part's candidates that the fp64 arithmetic accepted follow those
+        // the fp32 distance accepted: each entry's place from the whole masks
+        uint64_t M = 0, X = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            M = (M << 16) | ((uint32_t)__shfl((int32_t)m, qi + 16 * r) >> 16);
+            X = (X << 16) | ((uint32_t)__shfl((int32_t)x, qi + 16 * r) >> 16);
+        }
+        uint32_t all = m | x;
+        while (all) {
+            const uint32_t b = (uint32_t)__builtin_clz(all), bit = 0x80000000u >> b, s = row * 16u + b;
+            all ^= bit;
+            const uint64_t upto = t.starts & (~0ull >> (63u - s)), after = t.starts & ~(~0ull >> (63u - s));
+            const uint32_t p0 = 63u - (uint32_t)__builtin_clzll(upto),
+                           p1 = after ? (uint32_t)__builtin_ctzll(after) : t.slots;
+            int32_t at = q.cnt + set_before(M | X, p0);
+            if (m & bit)
+                at += set_before(M, s) - set_before(M, p0);
+            else
+                at += set_before(M, p1) - set_before(M, p0) + set_before(X, s) - set_before(X, p0);
+            if (at < a.max_nbr) out[at] = w.index[s];
+        }
+        q.cnt += __popcll(M | X);
+    } else {
+        const int32_t n = __popc(m);
+        const int32_t n0 = __shfl(n, qi), n1 = __shfl(n, qi + 16), n2 = __shfl(n, qi + 32), n3 = __shfl(n, qi + 48);
+        int32_t at = q.cnt + (row > 0u ? n0 : 0) + (row > 1u ? n1 : 0) + (row > 2u ? n2 : 0);
+        const int32_t *idx = &w.index[row * 16u];
+        while (m) {
+            const uint32_t b = (uint32_t)__builtin_clz(m);
+            m ^= 0x80000000u >> b;
+            const int32_t e = idx[b];
+            if (at < a.max_nbr) out[at] = e;
+            ++at;
+        }
+        q.cnt += (n0 + n1) + (n2 + n3);
+    }
+    wave_lds_sync();
+}
+
 // ------------------------------------------------------------------ walk
 
 // An integer that orders like the float (and back).
@@ -585,21 +708,28 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
 
 // One wavefront of queries; this lane's query is position `li` of the system
 // `a` (li >= a.n: an idle lane; the valid lanes come first).
-template <bool kVec4, Mode kMode, class Args>
+template <bool kVec4, Mode kMode, bool kFew, class Args>
 __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *__restrict__ records,
                                               const float4 *__restrict__ sorted, const double *__restrict__ sorted64,
                                               const uint4 *__restrict__ qpoint, const TreeMeta *__restrict__ meta,
-                                              WaveLds &w) {
+                                              WaveLds<kFew> &w) {
     const uint32_t lane = (uint32_t)(threadIdx.x & 63u);
     Query q;
-    q.valid = li < a.n;
-    const int32_t nq = (int32_t)__popcll(__ballot(q.valid));
+    const bool valid = li < a.n;
+    const int32_t nq = (int32_t)__popcll(__ballot(valid));
     if (nq == 0) return;
     const int32_t kw0 = uniform(a.start + li);  // lane 0 is valid
     const uint32_t nend = (uint32_t)(a.start + a.n);
     q.k = kw0 + min((int32_t)lane, nq - 1);  // idle lanes repeat the last query
     const float4 qp = sorted[q.k];
     q.orig = ~__float_as_int(qp.w);
+    q.valid = valid;
+    if (kFew) {  // the queries' four lanes each
+        const int own = min((int)(lane & 15u), nq - 1);
+        q.k = kw0 + own;
+        q.orig = __shfl(q.orig, own);
+        q.valid = (int32_t)(lane & 15u) < nq;
+    }
     q.cnt = 0;
     q.done = 0;
     q.words = 0;
@@ -682,7 +812,7 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         }
         // (squares of such coordinates would overflow)
         tt.force = !(M2 < 1e28f) || !(a.lmax < 1e14);
-        const float c0 = q.valid ? q2 - (float)mid : 1e30f;
+        const float c0 = valid ? q2 - (float)mid : 1e30f;
         float cq[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) cq[g] = __shfl(c0, 16 * g + (int)(lane & 15u));
@@ -797,13 +927,19 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
             if (queued >= 64u || size == 0u) {
                 uint32_t done = 0, rest = queued;
                 while (rest >= 64u || (size == 0u && rest > 0u)) {
-                    if (table == (uint32_t)kTables || __any(q.words > (uint32_t)kWords - 4u)) {
-                        write_rows<kVec4>(q, w, a.nbr, a.max_nbr, lane);
-                        table = 0;
+                    if constexpr (!kFew) {
+                        if (table == (uint32_t)kTables || __any(q.words > (uint32_t)kWords - 4u)) {
+                            write_rows<kVec4>(q, w, a.nbr, a.max_nbr, lane);
+                            table = 0;
+                        }
                     }
                     const Batch t = take_batch(done, parts, w, sorted, lane);
-                    test_batch<kVec4, kMode>(a, tt, t, table, groups, bq, cq, ox, oy, oz, kw0, q, w, sorted, sorted64,
-                                             qpoint, m, lane);
+                    if constexpr (kFew)
+                        test_batch_few<kMode>(a, tt, t, bq[0], cq[0], ox, oy, oz, kw0, q, w, sorted, sorted64, qpoint,
+                                              m, lane);
+                    else
+                        test_batch<kVec4, kMode>(a, tt, t, table, groups, bq, cq, ox, oy, oz, kw0, q, w, sorted,
+                                                 sorted64, qpoint, m, lane);
                     ++table;
                     done += t.parts;
                     rest -= t.slots;
@@ -820,13 +956,14 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         }
     }
 
-    write_rows<kVec4>(q, w, a.nbr, a.max_nbr, lane);
-    if (!q.valid) return;
+    if constexpr (!kFew) write_rows<kVec4>(q, w, a.nbr, a.max_nbr, lane);
+    if (!q.valid || (kFew && lane >= (uint32_t)kFewQueries)) return;
     a.count[q.orig] = q.cnt;
+    if (q.cnt > a.max_nbr) atomicOr(a.overflow, 1);
+    if (kFew) return;
     int32_t *row = a.nbr + ((int64_t)q.orig * a.max_nbr + q.done);
     for (uint32_t e = 0; e < q.carry; ++e)
         if (q.done + (int32_t)e < a.max_nbr) row[e] = w.index[kTables * 64 + lane * 4 + e];
-    if (q.cnt > a.max_nbr) atomicOr(a.overflow, 1);
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs; each XCD gets one
@@ -883,13 +1020,13 @@ __device__ __forceinline__ int32_t query_position(Args &a, const TreeMeta *__res
     return a.n;
 }
 
-template <bool kVec4, int kBlock, Mode kMode>
+template <bool kVec4, int kBlock, Mode kMode, bool kFew>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_traverse(
     TravArgs a, const uint4 *__restrict__ records, const float4 *__restrict__ sorted,
     const uint4 *__restrict__ qpoint, const TreeMeta *__restrict__ meta) {
-    __shared__ WaveLds s_wave[kBlock / 64];
+    __shared__ WaveLds<kFew> s_wave[kBlock / 64];
     const int32_t li = query_position<kBlock>(a, meta, xcd_logical_block(), (int32_t)gridDim.x);
-    traverse_wave<kVec4, kMode, const TravArgs>(a, li, records, sorted, a.sorted64, qpoint, meta,
+    traverse_wave<kVec4, kMode, kFew, const TravArgs>(a, li, records, sorted, a.sorted64, qpoint, meta,
                                                 s_wave[threadIdx.x >> 6]);
 }
 
@@ -897,11 +1034,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // belongs to one system (found from the per-system first-workgroup table) and
 // reads that system's arguments from the device table, so every per-system
 // value stays wave-uniform.
-template <bool kVec4, int kBlock>
+template <bool kVec4, int kBlock, bool kFew>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_traverse_batch(
     const TravArgs *__restrict__ table, const int32_t *__restrict__ tblk_first, int32_t nsys,
     const uint4 *__restrict__ records, const float4 *__restrict__ sorted, const TreeMeta *__restrict__ meta_all) {
-    __shared__ WaveLds s_wave[kBlock / 64];
+    __shared__ WaveLds<kFew> s_wave[kBlock / 64];
     const int32_t logical = xcd_logical_block();
     const int32_t sys = find_seg(tblk_first, nsys, logical);
     // the system's arguments are read through the constant address space, as
@@ -911,8 +1048,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     ConstArgs *args = reinterpret_cast<ConstArgs *>(reinterpret_cast<uintptr_t>(table + sys));
     const TreeMeta *meta = meta_all + sys * QBVH_MAX_TYPES;
     const int32_t li = query_position<kBlock>(*args, meta, logical - tblk_first[sys], tblk_first[sys + 1] - tblk_first[sys]);
-    traverse_wave<kVec4, kExact, ConstArgs>(*args, li, records, sorted, nullptr, nullptr, meta,
-                                            s_wave[threadIdx.x >> 6]);
+    traverse_wave<kVec4, kExact, kFew, ConstArgs>(*args, li, records, sorted, nullptr, nullptr, meta,
+                                                  s_wave[threadIdx.x >> 6]);
 }
 
 __global__ void k_clear_flag(int32_t *f) {
@@ -922,14 +1059,23 @@ __global__ void k_clear_flag(int32_t *f) {
 template <bool kVec4, int kBlock, Mode kMode>
 void launch_one(const TravArgs &a, const uint4 *qpoint, hipStream_t s) {
     const unsigned grid = (unsigned)trav_blocks(a.n, a.ntypes, kBlock, a.qpw);
-    hipLaunchKernelGGL((k_traverse<kVec4, kBlock, kMode>), dim3(grid), dim3(kBlock), 0, s, a, a.records, a.sorted,
-                       qpoint, a.meta);
+    // (rows of few queries are written entry by entry, whatever their alignment)
+    if (a.qpw <= kFewQueries)
+        hipLaunchKernelGGL((k_traverse<false, kBlock, kMode, true>), dim3(grid), dim3(kBlock), 0, s, a, a.records,
+                           a.sorted, qpoint, a.meta);
+    else
+        hipLaunchKernelGGL((k_traverse<kVec4, kBlock, kMode, false>), dim3(grid), dim3(kBlock), 0, s, a, a.records,
+                           a.sorted, qpoint, a.meta);
 }
 
 template <bool kVec4, int kBlock>
 void launch_one_batch(const BatchLaunch &b, hipStream_t s) {
-    hipLaunchKernelGGL((k_traverse_batch<kVec4, kBlock>), dim3((unsigned)b.tblocks), dim3(kBlock), 0, s, b.trav,
-                       b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
+    if (b.qpw <= kFewQueries)
+        hipLaunchKernelGGL((k_traverse_batch<false, kBlock, true>), dim3((unsigned)b.tblocks), dim3(kBlock), 0, s,
+                           b.trav, b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
+    else
+        hipLaunchKernelGGL((k_traverse_batch<kVec4, kBlock, false>), dim3((unsigned)b.tblocks), dim3(kBlock), 0, s,
+                           b.trav, b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
 }
 
 template <Mode kMode, bool kVec4>

@@ -85,3 +85,21 @@ def test_paper_mode(n, qpw, edges, r, qbits):
                    rcut=np.array([[r]], np.float32), skin=0.0, name="paper_edge")
     nbr, cnt, ovf = P._paper_rows(cfg, {"queries_per_wave": qpw, "qbits": qbits, "leaf_size": 7})
     P._check(cfg, qbits, nbr, cnt, ovf, 512)
+
+
+@pytest.mark.parametrize("sizes", [(1, 300, 17), (700, 65, 1500), (4000, 129, 2500), (12000, 9000, 5000)])
+def test_small_batches(sizes):
+    # batches small enough for 1, 2, 4 and 16 queries per wavefront
+    from nlist_check import batch_buffers
+    import paper_1901_08088_amd as Q
+    import torch
+    rng = np.random.default_rng(sum(sizes))
+    cfgs = []
+    for n in sizes:
+        L = max(8.0, (n / 0.6) ** (1.0 / 3.0))
+        cfgs.append(_config(rng.uniform(0, L, (n, 3)), L, 2.2, 0.3))
+    bufs = batch_buffers(cfgs, max_nbr=128)
+    Q.nlist_build_many(bufs)
+    torch.cuda.synchronize()
+    for cfg, b in zip(cfgs, bufs):
+        compare_rows(cfg, b["nbr"].cpu().numpy(), b["count"].cpu().numpy(), int(b["overflow"].item()), 128)
