@@ -35,12 +35,17 @@ __device__ __forceinline__ Segment batch_segment(uint32_t key, int32_t off, cons
     return {s, s + (int32_t)tc[t]};
 }
 
-// Clears the per-system type counters, the error word and every system's
+// Sets the per-system type counts of systems of one type (the others are
+// counted after the sort), clears the error word and every system's
 // overflow flag (kernels, not memsets, so the sequence can be captured).
-__global__ __launch_bounds__(kBuildThreads) void k_b_init(int32_t nsys, uint32_t *__restrict__ type_count,
+__global__ __launch_bounds__(kBuildThreads) void k_b_init(int32_t nsys, const SysBuild *__restrict__ sysb,
+                                                          uint32_t *__restrict__ type_count,
                                                           const TravArgs *__restrict__ trav, int32_t *err) {
     const int32_t i = blockIdx.x * kBuildThreads + threadIdx.x;
-    if (i < nsys * QBVH_MAX_TYPES) type_count[i] = 0;
+    if (i < nsys * QBVH_MAX_TYPES) {
+        const SysBuild &y = sysb[i / QBVH_MAX_TYPES];
+        type_count[i] = y.ntypes == 1 && i % QBVH_MAX_TYPES == 0 ? (uint32_t)y.n : 0u;
+    }
     if (i < nsys) trav[i].overflow[0] = 0;
     if (i == 0) *err = 0;
 }
@@ -64,7 +69,8 @@ __global__ __launch_bounds__(kBuildThreads) void k_b_morton(const int32_t *__res
 }
 
 // Particles per (system, type), read off each system's sorted keys by binary
-// search (every entry written, types a system lacks included).
+// search (every entry written, types a system lacks included).  Only launched
+// for batches with a system of several types: its searches take 10 us.
 __global__ __launch_bounds__(kBuildThreads) void k_b_type_count(int32_t nsys, const SysBuild *__restrict__ sysb,
                                                                 const uint32_t *__restrict__ keys,
                                                                 uint32_t *__restrict__ type_count) {
@@ -75,18 +81,10 @@ __global__ __launch_bounds__(kBuildThreads) void k_b_type_count(int32_t nsys, co
     type_count[i] = (uint32_t)(type_start(keys, y.off, y.off + y.n, t + 1) - type_start(keys, y.off, y.off + y.n, t));
 }
 
-// Tree description of every (system, type).
-__global__ __launch_bounds__(64) void k_b_meta(int32_t nsys, const SysBuild *__restrict__ sysb,
-                                               const uint32_t *__restrict__ type_count,
+// Tree description of type t of a system.
+__device__ __forceinline__ TreeMeta batch_meta(const SysBuild &y, int32_t t, const uint32_t *__restrict__ tc,
                                                const float4 *__restrict__ sorted, const float4 *__restrict__ box,
-                                               const uint32_t *__restrict__ P,
-                                               int32_t qbits, int32_t leaf_size, TreeMeta *__restrict__ meta) {
-    const int32_t idx = blockIdx.x * 64 + threadIdx.x;
-    const int32_t sys = idx / QBVH_MAX_TYPES, t = idx % QBVH_MAX_TYPES;
-    if (sys >= nsys) return;
-    const SysBuild &y = sysb[sys];
-    if (t >= y.ntypes) return;
-    const uint32_t *tc = type_count + sys * QBVH_MAX_TYPES;
+                                               const uint32_t *__restrict__ P, int32_t qbits, int32_t leaf_size) {
     int32_t s = y.off;
     for (int u = 0; u < t; ++u) s += (int32_t)tc[u];
     const int32_t c = (int32_t)tc[t];
@@ -101,9 +99,12 @@ __global__ __launch_bounds__(64) void k_b_meta(int32_t nsys, const SysBuild *__r
         lo[0] = a.x; lo[1] = a.y; lo[2] = a.z;
         hi[0] = b.x; hi[1] = b.y; hi[2] = b.z;
     }
-    meta[idx] = tree_meta(lo, hi, y.ext_floor, qbits, s, c, c <= leaf_size, P);
+    return tree_meta(lo, hi, y.ext_floor, qbits, s, c, c <= leaf_size, P);
 }
 
+// Every workgroup works out its system's metadata for itself (less than a
+// launch of its own before this one); the system's first leaves it for the
+// traversal.
 __global__ __launch_bounds__(kBuildThreads) void k_b_emit(const int32_t *__restrict__ blk_first, int32_t nsys,
                                                           const SysBuild *__restrict__ sysb,
                                                           const uint32_t *__restrict__ keys,
@@ -114,17 +115,24 @@ __global__ __launch_bounds__(kBuildThreads) void k_b_emit(const int32_t *__restr
                                                           const int32_t *__restrict__ parent,
                                                           const float4 *__restrict__ box,
                                                           const uint32_t *__restrict__ P,
-                                                          const TreeMeta *__restrict__ meta, int32_t leaf_size,
+                                                          TreeMeta *__restrict__ meta, int32_t leaf_size,
                                                           int32_t qbits, uint4 *__restrict__ records,
                                                           int32_t *__restrict__ ropes) {
     // the workgroup's kept ids first (about one in leaf_size), so that the
     // record writes run on full wavefronts
     __shared__ int32_t s_ids[kBuildThreads];
     __shared__ uint32_t s_count;
-    if (threadIdx.x == 0) s_count = 0;
-    __syncthreads();
+    __shared__ TreeMeta s_meta[QBVH_MAX_TYPES];
     const Item it = item_of(blk_first, nsys);
     const SysBuild &y = sysb[it.sys];
+    if (threadIdx.x == 0) s_count = 0;
+    if ((int32_t)threadIdx.x < y.ntypes) {
+        s_meta[threadIdx.x] = batch_meta(y, (int32_t)threadIdx.x, type_count + it.sys * QBVH_MAX_TYPES, sorted, box, P,
+                                         qbits, leaf_size);
+        if (it.local == (int32_t)threadIdx.x)  // (the system's first workgroup)
+            meta[it.sys * QBVH_MAX_TYPES + threadIdx.x] = s_meta[threadIdx.x];
+    }
+    __syncthreads();
     const int32_t i = y.off + it.local;
     bool keep = false;
     if (it.local < y.n) {
@@ -144,7 +152,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_b_emit(const int32_t *__restr
     __syncthreads();
     if (threadIdx.x >= s_count) return;
     const int32_t k = s_ids[threadIdx.x];
-    const TreeMeta &m = meta[it.sys * QBVH_MAX_TYPES + (keys[k] >> 30)];
+    const TreeMeta &m = s_meta[keys[k] >> 30];
     emit_record(k, rf[k], rl[k], m, sorted, left, parent, box, P, leaf_size, nullptr, qbits, records,
                 ropes);
 }
@@ -155,15 +163,16 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t s) {
     const Workspace &w = b.ws;
     const int32_t ninit = b.nsys * QBVH_MAX_TYPES;
     hipLaunchKernelGGL(k_b_init, dim3((unsigned)((ninit + kBuildThreads - 1) / kBuildThreads)), dim3(kBuildThreads),
-                       0, s, b.nsys, b.type_count, b.trav, w.err);
+                       0, s, b.nsys, b.sysb, b.type_count, b.trav, w.err);
     if (b.blocks > 0)
         hipLaunchKernelGGL(k_b_morton, dim3((unsigned)b.blocks), dim3(kBuildThreads), 0, s, b.blk_first, b.nsys,
                            b.sysb, b.total, w.keys, w.kept);
     hipError_t e = launch_radix_sort_segmented(w.keys, w.vals, w.keys2, w.vals2, b.hist, b.scan_part, b.total,
                                                b.tiles, b.tile_first, b.sys_off, b.nsys, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_b_type_count, dim3((unsigned)((ninit + kBuildThreads - 1) / kBuildThreads)),
-                       dim3(kBuildThreads), 0, s, b.nsys, b.sysb, w.keys, b.type_count);
+    if (b.mixed)
+        hipLaunchKernelGGL(k_b_type_count, dim3((unsigned)((ninit + kBuildThreads - 1) / kBuildThreads)),
+                           dim3(kBuildThreads), 0, s, b.nsys, b.sysb, w.keys, b.type_count);
     if (b.total > 0) {
         e = launch_tree(w, b.total, TreeSource{nullptr, b.sysb, b.sys_off, b.nsys, nullptr, nullptr, nullptr}, b.leaf_size,
                         Collapse{0.f, 0.f, 0.f, b.leaf_size}, s);
@@ -171,8 +180,6 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t s) {
     }
     e = launch_exclusive_scan(w.kept, b.total + 1, b.scan_part, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_b_meta, dim3((unsigned)((ninit + 63) / 64)), dim3(64), 0, s, b.nsys, b.sysb, b.type_count,
-                       w.sorted, w.box, w.kept, b.qbits, b.leaf_size, b.meta);
     if (b.total > 0)
         hipLaunchKernelGGL(k_b_emit, dim3((unsigned)b.blocks), dim3(kBuildThreads), 0, s, b.blk_first, b.nsys, b.sysb,
                            w.keys, b.type_count, w.sorted, w.left, w.rf, w.rl, w.parent, w.box,

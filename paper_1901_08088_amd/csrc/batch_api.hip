@@ -495,6 +495,7 @@ int run_many(int32_t nsys, const qbvh_system_t *sys, const qbvh_batch_opts_t *op
     BatchLaunch b =
         make_launch(*c, nsys, (int32_t)total, (int32_t)tiles, (int32_t)blocks, (int32_t)tblocks, cfg, vec4);
     b.qpw = qpw;
+    b.mixed = std::any_of(sys, sys + nsys, [](const qbvh_system_t &y) { return y.ntypes > 1; });
 
     Pending q{cand, nullptr, nullptr};
     if (tuning) {

@@ -125,6 +125,7 @@ struct BatchLaunch {
     int32_t nsys, total, blocks, tiles, tblocks;
     int32_t leaf_size, qbits, block_size;
     int32_t qpw;                // queries per wavefront, of every system
+    bool mixed;                 // some system has several types
     bool vec4;
 };
 
