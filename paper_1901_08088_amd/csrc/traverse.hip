@@ -35,12 +35,12 @@
 //
 // Cost.  At N = 8M (LJ, R = 3.4) a wavefront issues 13.0k VALU instructions
 // and 436 matrix products (26 batches, 25 rounds) and the VALU is busy 66% of
-// the time; of 4.21 ms the walk takes 1.0, the tests 1.8, taking the rows'
+// the time; of 4.12 ms the walk takes 1.0, the tests 1.8, taking the rows'
 // entries from the masks 0.8 and storing the rows 0.65 (4.5 GB).  With one lane
 // per query walking and testing every candidate itself a wavefront issued
 // 26.1k VALU and 21.1k scalar instructions.  Traversal before and now: LJ 8M
-// 6.09 -> 4.21 ms, 1M 942 -> 517 us, 4000 102 -> 38 us, WCA 1M 533 -> 235 us,
-// two-type mixture 1M 523 -> 278 us.
+// 6.09 -> 4.12 ms, 1M 942 -> 509 us, 4000 102 -> 33 us, WCA 1M 533 -> 230 us,
+// two-type mixture 1M 523 -> 274 us.
 //
 // Paper-mode lists (Section 2.3: a particle is listed when the query's sphere
 // overlaps the particle's own cell box, with no distance check) take the same
@@ -120,9 +120,10 @@ constexpr int kFewQueries = 16;
 // One wavefront's LDS: 9.6 KB, so four wavefronts per SIMD fit a compute unit.
 template <bool kFew>
 struct WaveLds {
-    uint32_t word[kFew ? 1 : kWords + 1][64];  // per query: candidate mask (16 bits, first highest), byte offset into index
-    int32_t index[kFew ? 64 : kTables * 64 + 64 * 4];  // original indices of each batch's candidates; the entries
-                                                       // carried over
+    uint32_t word[kFew ? 1 : kWords + 1][64];  // per query: candidate mask (16 bits, first highest), byte
+                                               // offset into index
+    int32_t index[kFew ? 64 : kTables * 64 + 64 * 4];  // original indices of each batch's candidates; the
+                                                       // entries carried over
     int32_t sref[kStack];           // stack: record index, or run reference (< 0)
     uint2 part[kParts];             // queue: first sorted position, length - 1 from bit 27; particles
                                     // queued before the part, image code from bit 16
@@ -452,7 +453,11 @@ __device__ __forceinline__ bool stage_batch(Args &a, const Batch &t, uint32_t ta
     c[0] = t.p.x - osx;
     c[1] = t.p.y - osy;
     c[2] = t.p.z - osz;
-    c[3] = on ? __builtin_fmaf(c[2], c[2], __builtin_fmaf(c[1], c[1], c[0] * c[0])) : 1e30f;
+    c[3] = __builtin_fmaf(c[2], c[2], __builtin_fmaf(c[1], c[1], c[0] * c[0]));
+    if (!on || !(c[3] < 1e37f)) {  // (not a number: the sign of such a product would mean nothing)
+        c[0] = c[1] = c[2] = 0.0f;
+        c[3] = 1e30f;
+    }
     w.index[table * 64u + slot] = ~__float_as_int(t.p.w);
     // a query's own particle is never listed: it can only come up unshifted
     mine = __ballot(on && t.img == kHome && (uint32_t)(t.idx - kw0) < 64u);
@@ -764,6 +769,7 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
     const float rx = qp.x - ox, ry = qp.y - oy, rz = qp.z - oz;
     const float q2 = __builtin_fmaf(rz, rz, __builtin_fmaf(ry, ry, rx * rx));
     const float M2 = from_key(wave_max(order_key(q2)));  // (rounded: the bands below leave room for it)
+    const bool odd = __any(!(q2 >= 0.0f));
     float bq[4] = {-2.0f * rx, -2.0f * ry, -2.0f * rz, 1.0f};
     transpose4(bq[0], bq[1], bq[2], bq[3]);
 
@@ -810,8 +816,9 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
             tt.band_img =
                 uniform(pair_band(R, rin, rout, 1.7320508075688772 * 0x1p-22 * (2.0 * a.lmax + 2.0 * R), e_o, M));
         }
-        // (squares of such coordinates would overflow)
-        tt.force = !(M2 < 1e28f) || !(a.lmax < 1e14);
+        // (squares of such coordinates would overflow; a query that is not a
+        // number has no sign to go by)
+        tt.force = !(M2 < 1e28f) || !(a.lmax < 1e14) || odd;
         const float c0 = valid ? q2 - (float)mid : 1e30f;
         float cq[4];
 #pragma unroll
