@@ -44,10 +44,11 @@
 //
 // Paper-mode lists (Section 2.3: a particle is listed when the query's sphere
 // overlaps the particle's own cell box, with no distance check) take the same
-// walk and the same products.  The cell box holds the particle, so a pair
-// within R is listed; one farther apart than the tight radius and the cell's
-// diagonal is not; the pairs between, as a wider band, are decided one by one
-// by the cell box (see decide_cell).
+// walk and the same products, with the middle of the cell box for the particle:
+// within R and the cell's inscribed radius a pair is listed, beyond the tight
+// radius and half the cell's diagonal it is not; the pairs between are decided
+// one by one by the cell box (see decide_cell).  With the particle itself the
+// pairs between span a whole diagonal, five times as many.
 //
 // Row order.  A row lists, image by image and tree order within an image, the
 // candidates of each run part that the fp32 distance accepts, then those of
@@ -138,6 +139,12 @@ constexpr uint32_t kHome = 1u | (1u << 2) | (1u << 4);
 // List semantics: exact lists of fp32 or of fp64 data, paper-mode lists.
 enum Mode { kExact, kExact64, kPaper };
 
+// Paper mode: an image of a query in a tree's grid.
+struct CellQuery {
+    float p[3];  // position in bins
+    bool in;     // the sphere touches the tree's root box
+};
+
 // Per-query state of a lane.
 struct Query {
     int32_t k, orig;
@@ -146,17 +153,21 @@ struct Query {
     uint32_t words;   // words waiting
     uint32_t carry;   // entries carried over (fewer than 4)
     bool valid;
+    CellQuery home;   // paper mode: itself, unshifted, as the present tree sees it
 };
 
 // A type tree as the test sees it (wave-uniform).
 struct TreeTest {
     float r2in, r2out;   // accept and reject thresholds of the fp32 distance
     double r2;           // exact squared list radius
-    float band, band_img;  // |v| that needs the fp32 distance: home image, other images
+    // |v| that needs the fp32 distance: home image, other images (paper mode:
+    // that needs the cell box; batches with a cell of no width on some axis)
+    float band, band_img;
     bool force;          // coordinates too large for the product: every pair needs it
     // paper mode: bin width of each axis, squared tight radius, squared radius
     // of the image test
     double h[3];
+    float hf[3];
     float rp2, rimg2;
 };
 
@@ -328,23 +339,36 @@ __device__ __forceinline__ int decide_pair(const float4 &qp, int32_t k, const fl
 // 2^-24 of 65535 bins per axis) and of the fp32 distance.  A periodic image
 // counts when the sphere touches the tree's root box, in fp32 with an outward
 // pad of 2^-18 of the largest box edge plus 2^-20 relative.
+// The query's side of this takes three fp64 divisions, so the unshifted image's
+// is kept for a whole tree.  LJ 8M on a 10-bit grid: 12.66 -> 11.99 ms, and 8.53
+// with v taken to the cells' middles (100k 310 -> 296 -> 265 us for build and
+// list; a lane per query testing every cell box took 10.8 ms and 489 us).
 template <class LArr, class FArr>
-__device__ __forceinline__ bool decide_cell(const float4 &qp, const uint4 &b, uint32_t img, const TreeTest &tt,
-                                            const TreeMeta &m, const LArr &L, const FArr &Lf) {
+__device__ __forceinline__ CellQuery cell_query(const float4 &qp, uint32_t img, const TreeTest &tt, const TreeMeta &m,
+                                                const LArr &L, const FArr &Lf) {
     const float x[3] = {qp.x, qp.y, qp.z};
-    const uint32_t w[3] = {b.x, b.y, b.z};
-    float c[3], e2[3];
+    CellQuery q;
+    float e2[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         const int sh = (int)((img >> (2 * d)) & 3u) - 1;
-        const float p = (float)((((double)x[d] + (double)sh * L[d]) - (double)m.lo[d]) / tt.h[d]);
-        c[d] = (__builtin_amdgcn_fmed3f(p, (float)(w[d] & 0xFFFFu), (float)(w[d] >> 16)) - p) * (float)tt.h[d];
+        q.p[d] = (float)((((double)x[d] + (double)sh * L[d]) - (double)m.lo[d]) / tt.h[d]);
         const float y = x[d] + (float)sh * Lf[d];
         const float e = fmaxf(fmaxf(m.lo[d] - y, y - m.hi[d]), 0.0f);
         e2[d] = e * e;
     }
+    q.in = (e2[0] + e2[1]) + e2[2] <= tt.rimg2;
+    return q;
+}
+
+__device__ __forceinline__ bool decide_cell(const CellQuery &q, const uint4 &b, const TreeTest &tt) {
+    const uint32_t w[3] = {b.x, b.y, b.z};
+    float c[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+        c[d] = (__builtin_amdgcn_fmed3f(q.p[d], (float)(w[d] & 0xFFFFu), (float)(w[d] >> 16)) - q.p[d]) * tt.hf[d];
     const float d2 = __builtin_fmaf(c[2], c[2], __builtin_fmaf(c[1], c[1], c[0] * c[0]));
-    return d2 <= tt.rp2 && (e2[0] + e2[1]) + e2[2] <= tt.rimg2;
+    return d2 <= tt.rp2 && q.in;
 }
 
 // Band of the matrix-core test.  Let T be a pair's squared distance as the
@@ -362,8 +386,8 @@ __device__ __forceinline__ bool decide_cell(const float4 &qp, const uint4 &b, ui
 // R^2) + 2.5 R (u S + 3.5 u L_max) covers them with room, which also keeps
 // candidates far from the cutoff (their error grows with |c|^2 2^-20, their
 // distance with |c|^2) from ever falling below -band.  In paper mode v is
-// taken against the middle of R^2 and the squared rejection radius, and the
-// band is half their difference and E.
+// taken against the middle of the squared acceptance and rejection radii, and
+// the band is half their difference and E.
 __device__ __forceinline__ double product_error(double R, double e_o, double M) {
     const double u = 0x1p-24, S = 2.0 * M + R;
     return 24.0 * u * (S * S + R * R) + 2.5 * R * (u * S + e_o);
@@ -382,14 +406,16 @@ __device__ __forceinline__ float pair_band(double R, double rin, double rout, do
 struct Batch {
     uint64_t starts;   // slots at which a part starts
     uint32_t parts, slots;
-    float4 p;
+    float4 p;          // (paper mode: the middle of its cell box)
     int32_t idx;       // sorted position, -1: an empty slot
     uint32_t img;
+    bool flat;         // paper mode: some candidate's cell box has no width on some axis
 };
 
-template <bool kFew>
+template <Mode kMode, bool kFew>
 __device__ __forceinline__ Batch take_batch(uint32_t at, uint32_t parts, WaveLds<kFew> &w,
-                                            const float4 *__restrict__ sorted, uint32_t lane) {
+                                            const float4 *__restrict__ sorted, const uint4 *__restrict__ qpoint,
+                                            const TreeTest &tt, const TreeMeta &m, uint32_t lane) {
     Batch b;
     const uint2 mine = w.part[min(at + lane, parts - 1u)];
     const uint32_t base = uniform(mine.y & 0xFFFFu);
@@ -409,7 +435,18 @@ __device__ __forceinline__ Batch take_batch(uint32_t at, uint32_t parts, WaveLds
     const bool on = slot < b.slots;
     b.img = part.y >> 16;
     b.idx = (int32_t)((part.x & 0x7FFFFFFu) + (on ? slot - ((part.y & 0xFFFFu) - base) : 0u));
-    b.p = sorted[b.idx];
+    b.flat = false;
+    if constexpr (kMode == kPaper) {
+        const uint4 c = qpoint[b.idx];
+        auto middle = [&](uint32_t x, int d) {
+            return __builtin_fmaf(tt.hf[d], 0.5f * (float)((x & 0xFFFFu) + (x >> 16)), m.lo[d]);
+        };
+        auto width0 = [](uint32_t x) { return (x & 0xFFFFu) == (x >> 16); };
+        b.p = make_float4(middle(c.x, 0), middle(c.y, 1), middle(c.z, 2), __int_as_float(~(int32_t)c.w));
+        b.flat = __any(on && (width0(c.x) || width0(c.y) || width0(c.z)));
+    } else {
+        b.p = sorted[b.idx];
+    }
     if (!on) b.idx = -1;
     return b;
 }
@@ -417,14 +454,16 @@ __device__ __forceinline__ Batch take_batch(uint32_t at, uint32_t parts, WaveLds
 // A pair too near the cutoff for the product: 0 out, 1 in, 2 in by the fp64
 // arithmetic.  ci < 0: an empty slot.
 template <Mode kMode, class Args>
-__device__ __forceinline__ int decide(const float4 &qp, int32_t k, int32_t ci, uint32_t img, const TreeTest &tt,
+__device__ __forceinline__ int decide(const float4 &qp, const Query &q, int32_t ci, uint32_t img, const TreeTest &tt,
                                       Args &a, const TreeMeta &tree, const float4 *__restrict__ sorted,
                                       const double *__restrict__ sorted64, const uint4 *__restrict__ qpoint) {
     if (ci < 0) return 0;
-    if constexpr (kMode == kPaper)
-        return decide_cell(qp, qpoint[ci], img, tt, tree, a.L, a.Lf) ? 1 : 0;
-    else
-        return decide_pair<kMode == kExact64>(qp, k, sorted[ci], ci, img, tt, a.L, sorted64);
+    if constexpr (kMode == kPaper) {
+        CellQuery c = q.home;
+        if (img != kHome) c = cell_query(qp, img, tt, tree, a.L, a.Lf);
+        return decide_cell(c, qpoint[ci], tt) ? 1 : 0;
+    } else
+        return decide_pair<kMode == kExact64>(qp, q.k, sorted[ci], ci, img, tt, a.L, sorted64);
 }
 
 // Slots [from, to) of a half batch as a mask, first slot highest.
@@ -500,7 +539,7 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
         if (groups > 1) test_group(c, bq[1], cq[1], m[1], nr[1]);
         if (groups > 2) test_group(c, bq[2], cq[2], m[2], nr[2]);
     }
-    const float band = shifted ? tt.band_img : tt.band;
+    const float band = (kMode == kPaper ? t.flat : shifted) ? tt.band_img : tt.band;
     const bool near_any = __any(fminf(fminf(nr[0], nr[1]), fminf(nr[2], nr[3])) <= band) || tt.force;
     transpose4(m[0], m[1], m[2], m[3]);
     uint32_t lo = ((m[0] << 16) | m[1]) & ~self_lo, hi = ((m[2] << 16) | m[3]) & ~self_hi;
@@ -526,7 +565,7 @@ __device__ __forceinline__ void test_batch(Args &a, const TreeTest &tt, const Ba
             const int32_t ci = __shfl(t.idx, from);
             const uint32_t im = (uint32_t)__shfl((int32_t)t.img, from);
             if ((nlo | nhi) != 0u) {
-                const int r = decide<kMode>(qp, q.k, ci, im, tt, a, tree, sorted, sorted64, qpoint);
+                const int r = decide<kMode>(qp, q, ci, im, tt, a, tree, sorted, sorted64, qpoint);
                 if (b < 32u) {
                     nlo ^= bit;
                     lo |= r == 1 ? bit : 0u;
@@ -605,7 +644,7 @@ __device__ __forceinline__ void test_batch_few(Args &a, const TreeTest &tt, cons
     float nr;
     test_group(c, bq, cq, m, nr);
     m = (m << 16) & ~self;
-    const float band = shifted ? tt.band_img : tt.band;
+    const float band = (kMode == kPaper ? t.flat : shifted) ? tt.band_img : tt.band;
     uint32_t x = 0;  // accepted by the fp64 arithmetic
     if (__any(nr <= band) || tt.force) {
         // some pair lies too near the cutoff for the product to decide
@@ -619,7 +658,7 @@ __device__ __forceinline__ void test_batch_few(Args &a, const TreeTest &tt, cons
             const int32_t ci = __shfl(t.idx, from);
             const uint32_t im = (uint32_t)__shfl((int32_t)t.img, from);
             if (near != 0u) {
-                const int r = decide<kMode>(qp, q.k, ci, im, tt, a, tree, sorted, sorted64, qpoint);
+                const int r = decide<kMode>(qp, q, ci, im, tt, a, tree, sorted, sorted64, qpoint);
                 near ^= bit;
                 m |= r == 1 ? bit : 0u;
                 x |= r == 2 ? bit : 0u;
@@ -795,22 +834,31 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         const double e_o = 3.5 * 0x1p-24 * a.lmax;  // of a shifted origin
         double mid = r2;                            // v is the squared distance less this
         if constexpr (kMode == kPaper) {
-            // listed surely within R, surely not beyond the tight radius and a
-            // cell's diagonal (with room for the rounding of the cell test)
-            double hmax = 0.0, diag = 0.0;
+            // v is the distance to the middle of the candidate's cell box:
+            // listed surely within R and the cell's inscribed radius, surely
+            // not beyond the tight radius and half its diagonal (with room for
+            // the rounding of the cell test)
+            double hmax = 0.0, hmin = INFINITY, diag = 0.0;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 tt.h[d] = axis_spacing(m.lo[d], m.hi[d], a.lmax * 0x1p-24, a.qbits);
                 hmax = fmax(hmax, tt.h[d]);
+                hmin = fmin(hmin, tt.h[d]);
                 diag += tt.h[d] * tt.h[d];
+                tt.hf[d] = (float)tt.h[d];
             }
             const double rp = R * (1.0 + 0x1p-20) + 0.02 * hmax;
             tt.rp2 = (float)(rp * rp * (1.0 + 0x1p-20));
             const float rimg = (float)R * (1.0f + 0x1p-20f) + (float)(a.lmax * 0x1p-18);
             tt.rimg2 = rimg * rimg;
-            const double far = rp * (1.0 + 0x1p-18) + sqrt(diag) + 0.05 * hmax;
-            mid = 0.5 * (r2 + far * far);
-            tt.band = tt.band_img = uniform(round_band(0.5 * (far * far - r2) + product_error(far, e_o, M)));
+            q.home = cell_query(sorted[q.k], kHome, tt, m, a.L, a.Lf);
+            const double far = rp * (1.0 + 0x1p-18) + 0.5 * sqrt(diag) + 0.05 * hmax;
+            const double in = R + 0.5 * hmin * (1.0 - 0x1p-10);
+            mid = 0.5 * (in * in + far * far);
+            // (the middle is rounded by at most 6 2^-24 L_max)
+            const double e = product_error(far, e_o + 6.0 * 0x1p-24 * a.lmax, M);
+            tt.band = uniform(round_band(0.5 * (far * far - in * in) + e));
+            tt.band_img = uniform(round_band(mid - r2 + e));
         } else {
             tt.band = uniform(pair_band(R, rin, rout, R * 0x1p-21, 0.0, M));
             tt.band_img =
@@ -946,7 +994,7 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
                         }
                     }
                     if constexpr (!kFew) __builtin_amdgcn_s_setprio(2);
-                    const Batch t = take_batch(done, parts, w, sorted, lane);
+                    const Batch t = take_batch<kMode>(done, parts, w, sorted, qpoint, tt, m, lane);
                     if constexpr (!kFew) __builtin_amdgcn_s_setprio(0);
                     if constexpr (kFew)
                         test_batch_few<kMode>(a, tt, t, bq[0], cq[0], ox, oy, oz, kw0, q, w, sorted, sorted64, qpoint,

@@ -87,6 +87,21 @@ def test_paper_mode(n, qpw, edges, r, qbits):
     P._check(cfg, qbits, nbr, cnt, ovf, 512)
 
 
+@pytest.mark.parametrize("flat", [1.0, 0.5, 0.0])
+@pytest.mark.parametrize("qpw", [8, 64])
+def test_paper_mode_flat_cells(flat, qpw):
+    # unit bins and a share of particles exactly on them: their cells have no
+    # width, so that only the list radius itself is a sure accept
+    import test_gpu_paper as P
+    rng = np.random.default_rng(21)
+    pos = rng.uniform(0, 255.0, (3000, 3))
+    pos = np.where(rng.uniform(size=(3000, 1)) < flat, np.round(pos), pos)
+    pos[0], pos[1] = 0.0, 255.0
+    cfg = _config(pos, 260.0, 20.0)
+    nbr, cnt, ovf = P._paper_rows(cfg, {"queries_per_wave": qpw, "qbits": 8})
+    P._check(cfg, 8, nbr, cnt, ovf, 512)
+
+
 @pytest.mark.parametrize("sizes", [(1, 300, 17), (700, 65, 1500), (4000, 129, 2500), (12000, 9000, 5000)])
 def test_small_batches(sizes):
     # batches small enough for 1, 2, 4 and 16 queries per wavefront
