@@ -3,7 +3,7 @@
 
 One step = the whole hot path on one synthetic configuration: qbvh_build
 (Morton codes, radix sort, gather, radix tree, bottom-up boxes, quantized
-preorder layout) followed by nlist_build (stackless traversal with the exact
+preorder layout) followed by nlist_build (tree traversal with the exact
 distance filter, rows written to a device [N][max_nbr] buffer).  Inputs are
 resident in device memory before the timed region.
 
@@ -166,16 +166,17 @@ def band_report(cfg, queries=None, threads: int = 0) -> dict:
 # factor the same counters read for a plain elementwise copy of known size (the
 # --copy-probe-mib kernel).  Valid only for the kernel sources it was taken on:
 # ``traffic`` is reported as null once their hash differs.
-TRAFFIC = {"sources": "46520ba402bbbee4", "workload": "lj8m",
+TRAFFIC = {"sources": "a0ce59fc43337ced", "workload": "lj8m",
            "opts": {"leaf_size": 16, "qbits": 16, "block_size": 64},
-           "fetch_kib": 1528910.0, "write_kib": 6610126.0, "copy_factor": 1.0,
-           # FETCH_SIZE per byte read: 0.500 for vector loads (the copy probe), 1.000 for
-           # scalar loads (profiles/fetch_size_calibration.md)
+           "fetch_kib": 492221.0, "write_kib": 5681606.0, "copy_factor": 1.0,
+           # FETCH_SIZE per byte read: 0.500 for vector loads (the copy probe; the kernel's
+           # nodes, particles and queries), 1.000 for scalar loads
+           # (profiles/fetch_size_calibration.md)
            "fetch_factor": 0.500012, "fetch_factor_scalar": 1.000049,
            "profile": "profiles/k_traverse_lj8m_counters.md",
            # SQ_INSTS_VALU x 4 / (1024 SIMDs x kernel cycles): the VALU issues one wave64
            # instruction per 4 cycles per SIMD, so this is the kernel's VALU issue roofline
-           "valu_busy": 0.90}
+           "valu_busy": 0.65}
 KERNEL_SOURCES = ("paper_1901_08088_amd/csrc/traverse.hip", "paper_1901_08088_amd/csrc/qbvh_internal.h",
                   "paper_1901_08088_amd/csrc/build_common.h", "paper_1901_08088_amd/csrc/launch_geometry.h")
 

@@ -33,8 +33,8 @@
 // list definition, so the lists are exact.  The band is derived at
 // pair_band().
 //
-// Cost.  At N = 8M (LJ, R = 3.4) a wavefront issues 13.0k VALU instructions
-// and 436 matrix products (26 batches, 25 rounds) and the VALU is busy 66% of
+// Cost.  At N = 8M (LJ, R = 3.4) a wavefront issues 13.1k VALU instructions
+// and 436 matrix products (26 batches, 25 rounds) and the VALU is busy 65% of
 // the time; of 4.12 ms the walk takes 1.0, the tests 1.8, taking the rows'
 // entries from the masks 0.8 and storing the rows 0.65 (4.5 GB).  With one lane
 // per query walking and testing every candidate itself a wavefront issued
