@@ -331,8 +331,15 @@ constexpr int kRankSort = 11 * 1024;
 constexpr int kRankThreads = 1024;
 constexpr int kRankItems = 16;
 
-template <class T>
-__global__ __launch_bounds__(kRankThreads) void k_morton_rank(MortonArgs<T> m, int32_t n, uint32_t *__restrict__ keys,
+// Keys that are there already.
+struct KeyArray {
+    const uint32_t *keys;
+};
+__device__ __forceinline__ uint32_t morton_of(const KeyArray &k, int32_t i) { return k.keys[i]; }
+__device__ __forceinline__ void morton_clear(const KeyArray &, int32_t) {}
+
+template <class Src>
+__global__ __launch_bounds__(kRankThreads) void k_morton_rank(Src m, int32_t n, uint32_t *__restrict__ keys,
                                                               uint32_t *__restrict__ vals) {
     __shared__ __align__(16) uint32_t s_keys[kRankSort];
     __shared__ uint32_t s_rank[kRankItems];
@@ -368,6 +375,16 @@ __global__ __launch_bounds__(kRankThreads) void k_morton_rank(MortonArgs<T> m, i
         keys[at] = ki;
         vals[at] = (uint32_t)i;
     }
+}
+
+__global__ __launch_bounds__(kHistThreads) void k_copy_pairs(int32_t n, const uint32_t *__restrict__ keys_in,
+                                                             const uint32_t *__restrict__ vals_in,
+                                                             uint32_t *__restrict__ keys_out,
+                                                             uint32_t *__restrict__ vals_out) {
+    const int32_t i = (int32_t)blockIdx.x * kHistThreads + (int32_t)threadIdx.x;
+    if (i >= n) return;
+    keys_out[i] = keys_in[i];
+    vals_out[i] = vals_in[i];
 }
 
 // ---------------------------------------------------------------- exclusive scan
@@ -488,6 +505,17 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, ui
     if (n <= 0) return hipSuccess;
     // (whole tiles read their keys 16 bytes at a time)
     if (((reinterpret_cast<uintptr_t>(keys) | reinterpret_cast<uintptr_t>(keys2)) & 15u) != 0) return hipErrorInvalidValue;
+    // Small arrays (the grid's cell keys) by rank too, every workgroup reading
+    // all keys, so the order goes to the other buffers and is copied back: two
+    // launches for eight (whole grid list: 8000 particles 91 -> 52 us, 11000 94 -> 70;
+    // 4000 46 -> 40 against one workgroup sorting a single tile).
+    if (n <= kRankSort) {
+        hipLaunchKernelGGL(k_morton_rank<KeyArray>, dim3((unsigned)((n + kRankItems - 1) / kRankItems)),
+                           dim3(kRankThreads), 0, s, KeyArray{keys}, n, keys2, vals2);
+        hipLaunchKernelGGL(k_copy_pairs, dim3((unsigned)((n + kHistThreads - 1) / kHistThreads)), dim3(kHistThreads), 0,
+                           s, n, keys2, vals2, keys, vals);
+        return hipGetLastError();
+    }
     const int32_t t = radix_tiles(n);
     (void)tiles;
     uint32_t *ki = keys, *vi = vals, *ko = keys2, *vo = vals2;
@@ -522,7 +550,7 @@ template <class T>
 hipError_t launch_morton_rank(const MortonArgs<T> &m, int32_t n, uint32_t *keys, uint32_t *vals, hipStream_t s) {
     if (!rank_sorted(n)) return hipErrorInvalidValue;
     const int32_t blocks = n > 0 ? (n + kRankItems - 1) / kRankItems : 1;
-    hipLaunchKernelGGL(k_morton_rank<T>, dim3((unsigned)blocks), dim3(kRankThreads), 0, s, m, n, keys, vals);
+    hipLaunchKernelGGL(k_morton_rank<MortonArgs<T>>, dim3((unsigned)blocks), dim3(kRankThreads), 0, s, m, n, keys, vals);
     return hipGetLastError();
 }
 template hipError_t launch_morton_rank(const MortonArgs<float> &, int32_t, uint32_t *, uint32_t *, hipStream_t);
