@@ -805,7 +805,11 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
     const float ox = uniform(0.5f * (fminf(wlo[0][0], wlo[1][0]) + fmaxf(whi[0][0], whi[1][0]))),
                 oy = uniform(0.5f * (fminf(wlo[0][1], wlo[1][1]) + fmaxf(whi[0][1], whi[1][1]))),
                 oz = uniform(0.5f * (fminf(wlo[0][2], wlo[1][2]) + fmaxf(whi[0][2], whi[1][2])));
-    const float rx = qp.x - ox, ry = qp.y - oy, rz = qp.z - oz;
+    // Idle lanes take the origin itself: with their constant (c0 below) every
+    // product of theirs is 1e30 + |c|^2, positive whatever the coordinates (the
+    // candidates' are finite), so none of their bits is ever set and the row
+    // that they share with the last query is its own.
+    const float rx = valid ? qp.x - ox : 0.0f, ry = valid ? qp.y - oy : 0.0f, rz = valid ? qp.z - oz : 0.0f;
     const float q2 = __builtin_fmaf(rz, rz, __builtin_fmaf(ry, ry, rx * rx));
     const float M2 = from_key(wave_max(order_key(q2)));  // (rounded: the bands below leave room for it)
     const bool odd = __any(!(q2 >= 0.0f));
