@@ -22,10 +22,11 @@
 //
 // The search region is the union of kSegs boxes around consecutive queries,
 // cut where neighbouring queries lie farthest apart (Z order jumps), grown by
-// R.  For 64 queries of an LJ fluid at R = 3.4 four boxes meet 3% more
-// candidates than the 64 spheres themselves do, and two boxes, which take half
-// the instructions per node, measured faster on every workload (N = 1M: LJ 565
-// -> 560 us, WCA 268 -> 257 us).
+// R, or the queries' own spheres where these are much less (see kSphereCost).
+// For 64 queries of an LJ fluid at R = 3.4 four boxes meet 3% more candidates
+// than the 64 spheres themselves do, and two boxes, which take half the
+// instructions per node, measured faster on every workload (N = 1M: LJ 565 ->
+// 560 us, WCA 268 -> 257 us).
 //
 // Exactness.  |v| <= band (v the product's d^2 - R^2) marks the pairs that
 // need more: they are decided, one by one, by an fp32 distance with a proven
@@ -85,6 +86,24 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 // Search-region boxes per wavefront.
 constexpr int kSegs = 2;
+// Scattered queries.  Where a wavefront's queries lie far apart (a type with few
+// particles, the vapour around a droplet), two boxes around them may hold half
+// the system: then nodes are tested against each query's own sphere instead.
+// With V the boxes' volume grown by R, U the spheres' union and rho the tree's
+// density, boxes meet rho (V - U) more candidates, 64 to a batch of about 500
+// instructions; the spheres cost 13 instructions per query and round, in
+// rho U / 64 rounds and those at the top of the tree, where few nodes are on the
+// stack, and in any case some latency per round.  So spheres are taken when
+//   rho (V - U (1 + nq / 40)) > 8 (nq + 8).
+// Measured, boxes only and with this rule (whole call): 60 particles of a second
+// type among 1M 6340 -> 710 us, among 4M 29.1 -> 2.87 ms, 300 among 100k 613 ->
+// 339 us; 1M particles of a droplet with 1% vapour 5.18 -> 0.67 ms; a gas of
+// density 0.001, where V / U is large and rho V small, 320 -> 321 us (682 when
+// the volumes alone decide).  2 (nq + 8) in place of 8 takes spheres too often
+// (two types of 20k and 980k 458 -> 482 us), 16 too rarely (droplet of 100k with
+// 1% vapour 199 -> 294 us).
+constexpr float kSphereCost = 1.0f / 40.0f;
+constexpr float kSphereRounds = 8.0f;
 // Nodes opened per round (two lanes each).
 constexpr int kOpen = 32;
 // Stack entries.  A round that opens p nodes adds at most p entries; p is held
@@ -816,6 +835,43 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
     float bq[4] = {-2.0f * rx, -2.0f * ry, -2.0f * rz, 1.0f};
     transpose4(bq[0], bq[1], bq[2], bq[3]);
 
+    // Trees that the queries lie too far apart for (see kSphereCost), in volumes
+    // in units of R^3.  Most wavefronts are done with the first, rougher test.
+    uint32_t scattered = 0;
+    for (int tb = 0; tb < a.ntypes; ++tb) {
+        const TreeMeta &m = meta[tb];
+        const double r2 = a.rlist2[ta * QBVH_MAX_TYPES + tb];
+        if (m.count == 0 || !(r2 >= 0.0)) continue;
+        constexpr float kBall = 4.1887902f;
+        const float iR = __builtin_amdgcn_rsqf((float)r2);
+        // a box grown by R (Steiner's formula)
+        auto grown = [&](float x, float y, float z) {
+            return ((x * y * z + 2.0f * (x * y + y * z + z * x)) + 3.1415927f * (x + y + z)) + kBall;
+        };
+        float all[3], room = 1.0f;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            all[d] = (fmaxf(whi[0][d], whi[1][d]) - fminf(wlo[0][d], wlo[1][d])) * iR;
+            room *= (m.hi[d] - m.lo[d]) * iR + 2.0f;
+        }
+        const float boxes = grown(all[0], all[1], all[2]);
+        const float cost = 1.0f + kSphereCost * (float)nq, rounds = kSphereRounds * (float)(nq + 8) * room;
+        const float count = (float)m.count;
+        if (uniform(count * (boxes - kBall * cost) > rounds ? 1 : 0)) {
+            float each = 0.0f;
+#pragma unroll
+            for (int s = 0; s < kSegs; ++s)
+                each += grown((whi[s][0] - wlo[s][0]) * iR, (whi[s][1] - wlo[s][1]) * iR, (whi[s][2] - wlo[s][2]) * iR);
+            // the spheres' union: at most one sphere and, for each further query
+            // at distance g from the one before, the share 3/4 g / R of a sphere
+            const float share = fminf(0.75f * iR * __builtin_amdgcn_sqrtf(__int_as_float(max(gap, 0))), 1.0f);
+            const uint32_t sum = wave_prefix_sum((uint32_t)(share * 1024.0f));
+            const float spheres = kBall * (1.0f + (float)__builtin_amdgcn_readlane((int32_t)sum, 63) * 0x1p-10f);
+            const bool far = count * (fminf(boxes, each) - spheres * cost) > rounds;
+            scattered |= uniform(far ? 1u << tb : 0u);
+        }
+    }
+
     uint32_t table = 0;  // index tables in use
     for (int tb = 0; tb < a.ntypes; ++tb) {
         const TreeMeta &m = meta[tb];
@@ -879,9 +935,13 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         // Node test in grid units.  A quantized bound is an exact float; a
         // search box bound and an image shift are rounded once each, the
         // radius is padded by two bins, 2^-20 of itself and 2^-21 of the
-        // largest box edge in bins (far above those roundings).
+        // largest box edge in bins (far above those roundings; for the spheres,
+        // whose centres paper mode rounds three times, twice that).
         const double ih = m.inv_h;
-        const double rgp = (R + rshift) * ih * (1.0 + 0x1p-20) + 2.0 + 0x1p-21 * (a.lmax * ih);
+        // (grid positions in a root box without bounds are not numbers: there
+        // the boxes, which such a bound opens, are searched)
+        const bool by_sphere = ((scattered >> tb) & 1u) != 0u && ih > 0.0;
+        const double rgp = (R + rshift) * ih * (1.0 + 0x1p-20) + 2.0 + (by_sphere ? 0x1p-20 : 0x1p-21) * (a.lmax * ih);
         const float r2g = uniform((float)(rgp * rgp * (1.0 + 0x1p-20)));
         float sl[kSegs][3], sh[kSegs][3];
 #pragma unroll
@@ -895,7 +955,6 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         const float gLx = uniform((float)(a.L[0] * ih)), gLy = uniform((float)(a.L[1] * ih)),
                     gLz = uniform((float)(a.L[2] * ih));
         const int32_t end = m.end;
-
         // every image's root, the first image on top
         if (lane < 27u) {
             const uint32_t img = lane % 3u | ((lane / 3u) % 3u) << 2 | (lane / 9u) << 4;
@@ -943,12 +1002,36 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
                 hz -= tz;
             }
             float best = __builtin_inff();
+            if (by_sphere) {
+                // (the lanes past the queries repeat the last one)
+                const float4 own = sorted[q.k];
+                float ux, uy, uz;
+                if constexpr (kMode == kPaper) {  // (fewer registers to spare)
+                    const float ihf = (float)ih;
+                    ux = (own.x - m.lo[0]) * ihf, uy = (own.y - m.lo[1]) * ihf, uz = (own.z - m.lo[2]) * ihf;
+                } else {
+                    ux = (float)(((double)own.x - (double)m.lo[0]) * ih);
+                    uy = (float)(((double)own.y - (double)m.lo[1]) * ih);
+                    uz = (float)(((double)own.z - (double)m.lo[2]) * ih);
+                }
+                for (int i = 0; i < nq; i += 4) {
 #pragma unroll
-            for (int s = 0; s < kSegs; ++s) {
-                const float cx = fmaxf(fmaxf(lx - sh[s][0], sl[s][0] - hx), 0.0f);
-                const float cy = fmaxf(fmaxf(ly - sh[s][1], sl[s][1] - hy), 0.0f);
-                const float cz = fmaxf(fmaxf(lz - sh[s][2], sl[s][2] - hz), 0.0f);
-                best = fminf(best, __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx)));
+                    for (int j = 0; j < 4; ++j) {
+                        const float x = lane_value(ux, i + j), y = lane_value(uy, i + j), z = lane_value(uz, i + j);
+                        const float cx = __builtin_amdgcn_fmed3f(x, lx, hx) - x;
+                        const float cy = __builtin_amdgcn_fmed3f(y, ly, hy) - y;
+                        const float cz = __builtin_amdgcn_fmed3f(z, lz, hz) - z;
+                        best = fminf(best, __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx)));
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < kSegs; ++s) {
+                    const float cx = fmaxf(fmaxf(lx - sh[s][0], sl[s][0] - hx), 0.0f);
+                    const float cy = fmaxf(fmaxf(ly - sh[s][1], sl[s][1] - hy), 0.0f);
+                    const float cz = fmaxf(fmaxf(lz - sh[s][2], sl[s][2] - hz), 0.0f);
+                    best = fminf(best, __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx)));
+                }
             }
             const uint32_t v = (uint32_t)~nref;
             const uint32_t first = v >> kRunCountBits, count = (v & (uint32_t)kRunCountMask) + 1u;
