@@ -51,7 +51,7 @@ struct Plan {
     int next = 0;
     bool frozen = false;
     Cfg chosen{};
-    std::map<Cfg, hipGraphExec_t> graphs;
+    std::map<std::pair<Cfg, bool>, hipGraphExec_t> graphs;  // by configuration and BatchLaunch::wide
     int64_t calls = 0;
     int32_t graphs_captured = 0;
 };
@@ -156,7 +156,7 @@ hipError_t poll(BatchCtx &c, Plan &p, bool wait) {
             p.chosen = p.cands[bi];
             p.frozen = true;
             for (auto it = p.graphs.begin(); it != p.graphs.end();) {
-                if (it->first == p.chosen) {
+                if (it->first.first == p.chosen) {
                     ++it;
                 } else {
                     (void)hipGraphExecDestroy(it->second);
@@ -495,6 +495,7 @@ int run_many(int32_t nsys, const qbvh_system_t *sys, const qbvh_batch_opts_t *op
     BatchLaunch b =
         make_launch(*c, nsys, (int32_t)total, (int32_t)tiles, (int32_t)blocks, (int32_t)tblocks, cfg, vec4);
     b.qpw = qpw;
+    b.wide = std::any_of(trav.begin(), trav.end(), wide_box);
     b.mixed = std::any_of(sys, sys + nsys, [](const qbvh_system_t &y) { return y.ntypes > 1; });
 
     Pending q{cand, nullptr, nullptr};
@@ -505,12 +506,13 @@ int run_many(int32_t nsys, const qbvh_system_t *sys, const qbvh_batch_opts_t *op
         if (e != hipSuccess) return hip_fail(e);
     }
     if (use_graph) {
-        auto git = p.graphs.find(cfg);
+        const auto which = std::make_pair(cfg, b.wide);
+        auto git = p.graphs.find(which);
         if (git == p.graphs.end()) {
             hipGraphExec_t ex = nullptr;
             e = capture(*c, b, &ex);
             if (e != hipSuccess) return hip_fail(e);
-            git = p.graphs.emplace(cfg, ex).first;
+            git = p.graphs.emplace(which, ex).first;
             ++p.graphs_captured;
         }
         e = hipGraphLaunch(git->second, stream);

@@ -127,6 +127,7 @@ struct BatchLaunch {
     int32_t qpw;                // queries per wavefront, of every system
     bool mixed;                 // some system has several types
     bool vec4;
+    bool wide;                  // some system's box is wide (wide_box)
 };
 
 // Host helpers shared by the interface files.
@@ -182,6 +183,9 @@ hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool pap
 // Paper-mode cell boxes; lmax is the largest periodic box edge (the extent floor is lmax 2^-24).
 hipError_t launch_qpoint(const Workspace &w, int32_t n, int32_t ntypes, int32_t qbits, double lmax, hipStream_t s);
 hipError_t launch_traverse_batch(const BatchLaunch &b, hipStream_t s);
+// Whether a wavefront of the system may hold queries so far apart that it takes
+// them in parts: a matter of speed alone, the lists are the same.
+bool wide_box(const TravArgs &a);
 hipError_t launch_batch(const BatchLaunch &b, hipStream_t s);
 // Stable sort of keys[0, n); vals receives each sorted key's input position
 // (the caller writes only the keys).

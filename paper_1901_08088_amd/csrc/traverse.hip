@@ -104,6 +104,20 @@ constexpr int kSegs = 2;
 // 1% vapour 199 -> 294 us).
 constexpr float kSphereCost = 1.0f / 40.0f;
 constexpr float kSphereRounds = 8.0f;
+// Queries in places far apart.  The band of pairs that the products leave to the
+// exact test grows with the square of the wavefront's extent (see pair_band): at
+// a gap of 512 R between two queries it holds 37% of R^2, from about 850 R all.
+// So a wavefront with up to kWideGaps gaps wider than kWideGap R (it spans
+// clusters in a wide box) takes its queries up to the first gap, then the rest,
+// each part with its own origin and boxes.  (More gaps: a thin gas, with few
+// pairs to test.)  100 clusters of 2000 particles at R = 2.8 in a box of edge
+// 10^4 1400 -> 414 us, of edge 10^5 1619 -> 508, 8 of 25000 in 10^4 2.61 -> 0.92
+// ms (whole calls).  The parts take 8 more registers from the walk, which costs 2%
+// of LJ 1M, so only boxes with room for such a gap get the kernels with them.  A
+// line at 256 R would give those clusters another 2% to 20% and takes 3% from 1M
+// particles of a gas of density 0.001.
+constexpr float kWideGap = 512.0f;
+constexpr int kWideGaps = 3;
 // Nodes opened per round (two lanes each).
 constexpr int kOpen = 32;
 // Stack entries.  A round that opens p nodes adds at most p entries; p is held
@@ -1115,6 +1129,46 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         if (q.done + (int32_t)e < a.max_nbr) row[e] = w.index[kTables * 64 + lane * 4 + e];
 }
 
+// How many of the `rest` queries from position `first` on a wavefront takes at
+// once: those before a wide gap.
+template <class Args>
+__device__ __forceinline__ int32_t part_size(Args &a, int32_t first, int32_t rest, const float4 *__restrict__ sorted,
+                                             const TreeMeta *__restrict__ meta) {
+    const int32_t lane = (int32_t)(threadIdx.x & 63u), k0 = a.start + first;
+    const float4 p = sorted[k0 + min(lane, rest - 1)];
+    const float x = p.x - __shfl_up(p.x, 1), y = p.y - __shfl_up(p.y, 1), z = p.z - __shfl_up(p.z, 1);
+    const float gap2 = __builtin_fmaf(z, z, __builtin_fmaf(y, y, x * x));
+    int ta = 0;
+    for (int t = 1; t < a.ntypes; ++t)
+        if (k0 >= meta[t].start && meta[t].count > 0) ta = t;
+    ta = uniform(ta);
+    double r2 = INFINITY;
+    for (int t = 0; t < a.ntypes; ++t) {
+        const double q = a.rlist2[ta * QBVH_MAX_TYPES + t];
+        if (q >= 0.0) r2 = fmin(r2, q);
+    }
+    const uint64_t wide = __ballot(lane > 0 && gap2 > (float)r2 * (kWideGap * kWideGap));
+    return wide != 0 && __popcll(wide) <= kWideGaps ? (int32_t)__builtin_ctzll(wide) : rest;
+}
+
+// A wavefront of queries in as many parts as its wide gaps ask for.
+template <bool kVec4, Mode kMode, bool kFew, class Args>
+__device__ __forceinline__ void traverse_parts(Args &a, int32_t li, const uint4 *__restrict__ records,
+                                               const float4 *__restrict__ sorted, const double *__restrict__ sorted64,
+                                               const uint4 *__restrict__ qpoint, const TreeMeta *__restrict__ meta,
+                                               WaveLds<kFew> &w) {
+    const int32_t lane = (int32_t)(threadIdx.x & 63u);
+    int32_t rest = (int32_t)__popcll(__ballot(li < a.n)), first = uniform(li);
+    while (rest > 0) {
+        const int32_t part = part_size(a, first, rest, sorted, meta);
+        traverse_wave<kVec4, kMode, kFew, Args>(a, lane < part ? first + lane : a.n, records, sorted, sorted64, qpoint,
+                                                meta, w);
+        rest -= part;
+        first += part;
+        wave_lds_sync();
+    }
+}
+
 // Workgroups are dealt round-robin to the 8 XCDs; each XCD gets one
 // contiguous stretch of the Z-ordered queries so its L2 holds one region.
 __device__ __forceinline__ int32_t xcd_logical_block() {
@@ -1130,21 +1184,25 @@ __device__ __forceinline__ int32_t lane_query(Args &a, const TreeMeta *__restric
                           (int32_t)(threadIdx.x & 63u));
 }
 
-template <bool kVec4, int kBlock, Mode kMode, bool kFew>
+template <bool kVec4, int kBlock, Mode kMode, bool kFew, bool kWide>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_traverse(
     TravArgs a, const uint4 *__restrict__ records, const float4 *__restrict__ sorted,
     const uint4 *__restrict__ qpoint, const TreeMeta *__restrict__ meta) {
     __shared__ WaveLds<kFew> s_wave[kBlock / 64];
     const int32_t li = lane_query<kBlock>(a, meta, xcd_logical_block(), (int32_t)gridDim.x);
-    traverse_wave<kVec4, kMode, kFew, const TravArgs>(a, li, records, sorted, a.sorted64, qpoint, meta,
-                                                s_wave[threadIdx.x >> 6]);
+    if constexpr (kWide)
+        traverse_parts<kVec4, kMode, kFew, const TravArgs>(a, li, records, sorted, a.sorted64, qpoint, meta,
+                                                           s_wave[threadIdx.x >> 6]);
+    else
+        traverse_wave<kVec4, kMode, kFew, const TravArgs>(a, li, records, sorted, a.sorted64, qpoint, meta,
+                                                          s_wave[threadIdx.x >> 6]);
 }
 
 // Batched form: the workgroups of all systems form one grid; each workgroup
 // belongs to one system (found from the per-system first-workgroup table) and
 // reads that system's arguments from the device table, so every per-system
 // value stays wave-uniform.
-template <bool kVec4, int kBlock, bool kFew>
+template <bool kVec4, int kBlock, bool kFew, bool kWide>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_traverse_batch(
     const TravArgs *__restrict__ table, const int32_t *__restrict__ tblk_first, int32_t nsys,
     const uint4 *__restrict__ records, const float4 *__restrict__ sorted, const TreeMeta *__restrict__ meta_all) {
@@ -1158,34 +1216,45 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     ConstArgs *args = reinterpret_cast<ConstArgs *>(reinterpret_cast<uintptr_t>(table + sys));
     const TreeMeta *meta = meta_all + sys * QBVH_MAX_TYPES;
     const int32_t li = lane_query<kBlock>(*args, meta, logical - tblk_first[sys], tblk_first[sys + 1] - tblk_first[sys]);
-    traverse_wave<kVec4, kExact, kFew, ConstArgs>(*args, li, records, sorted, nullptr, nullptr, meta,
-                                                  s_wave[threadIdx.x >> 6]);
+    if constexpr (kWide)
+        traverse_parts<kVec4, kExact, kFew, ConstArgs>(*args, li, records, sorted, nullptr, nullptr, meta,
+                                                       s_wave[threadIdx.x >> 6]);
+    else
+        traverse_wave<kVec4, kExact, kFew, ConstArgs>(*args, li, records, sorted, nullptr, nullptr, meta,
+                                                      s_wave[threadIdx.x >> 6]);
 }
 
 __global__ void k_clear_flag(int32_t *f) {
     if (threadIdx.x == 0) *f = 0;
 }
 
+// (few queries per wavefront: small systems, which gain nothing from parts)
 template <bool kVec4, int kBlock, Mode kMode>
 void launch_one(const TravArgs &a, const uint4 *qpoint, hipStream_t s) {
     const unsigned grid = (unsigned)trav_blocks(a.n, a.ntypes, kBlock, a.qpw);
     // (rows of few queries are written entry by entry, whatever their alignment)
     if (a.qpw <= kFewQueries)
-        hipLaunchKernelGGL((k_traverse<false, kBlock, kMode, true>), dim3(grid), dim3(kBlock), 0, s, a, a.records,
-                           a.sorted, qpoint, a.meta);
+        hipLaunchKernelGGL((k_traverse<false, kBlock, kMode, true, false>), dim3(grid), dim3(kBlock), 0, s, a,
+                           a.records, a.sorted, qpoint, a.meta);
+    else if (wide_box(a))
+        hipLaunchKernelGGL((k_traverse<kVec4, kBlock, kMode, false, true>), dim3(grid), dim3(kBlock), 0, s, a,
+                           a.records, a.sorted, qpoint, a.meta);
     else
-        hipLaunchKernelGGL((k_traverse<kVec4, kBlock, kMode, false>), dim3(grid), dim3(kBlock), 0, s, a, a.records,
-                           a.sorted, qpoint, a.meta);
+        hipLaunchKernelGGL((k_traverse<kVec4, kBlock, kMode, false, false>), dim3(grid), dim3(kBlock), 0, s, a,
+                           a.records, a.sorted, qpoint, a.meta);
 }
 
 template <bool kVec4, int kBlock>
 void launch_one_batch(const BatchLaunch &b, hipStream_t s) {
     if (b.qpw <= kFewQueries)
-        hipLaunchKernelGGL((k_traverse_batch<false, kBlock, true>), dim3((unsigned)b.tblocks), dim3(kBlock), 0, s,
-                           b.trav, b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
+        hipLaunchKernelGGL((k_traverse_batch<false, kBlock, true, false>), dim3((unsigned)b.tblocks), dim3(kBlock), 0,
+                           s, b.trav, b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
+    else if (b.wide)
+        hipLaunchKernelGGL((k_traverse_batch<kVec4, kBlock, false, true>), dim3((unsigned)b.tblocks), dim3(kBlock), 0,
+                           s, b.trav, b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
     else
-        hipLaunchKernelGGL((k_traverse_batch<kVec4, kBlock, false>), dim3((unsigned)b.tblocks), dim3(kBlock), 0, s,
-                           b.trav, b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
+        hipLaunchKernelGGL((k_traverse_batch<kVec4, kBlock, false, false>), dim3((unsigned)b.tblocks), dim3(kBlock), 0,
+                           s, b.trav, b.tblk_first, b.nsys, b.ws.records, b.ws.sorted, b.meta);
 }
 
 template <Mode kMode, bool kVec4>
@@ -1217,6 +1286,23 @@ void launch_block_batch(const BatchLaunch &b, hipStream_t s) {
 }
 
 }  // namespace
+
+bool wide_box(const TravArgs &a) {
+    double r2 = INFINITY;
+    for (int t = 0; t < a.ntypes; ++t)
+        for (int u = 0; u < a.ntypes; ++u) {
+            const double x = a.rlist2[t * QBVH_MAX_TYPES + u];
+            if (x >= 0.0) r2 = fmin(r2, x);
+        }
+    // (no two particles are farther apart than the box's diagonal; with one in
+    // every R^3 there is no room for such gaps)
+    double d2 = 0.0, volume = 1.0;
+    for (int d = 0; d < 3; ++d) {
+        d2 += a.L[d] * a.L[d];
+        volume *= a.L[d];
+    }
+    return d2 > r2 * ((double)kWideGap * kWideGap) && (double)a.n * r2 * sqrt(r2) < volume;
+}
 
 hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool paper, const uint4 *qpoint, bool cleared,
                            hipStream_t s) {
