@@ -850,9 +850,10 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
     transpose4(bq[0], bq[1], bq[2], bq[3]);
 
     // Trees that the queries lie too far apart for (see kSphereCost), in volumes
-    // in units of R^3.  Most wavefronts are done with the first, rougher test.
+    // in units of R^3.  Most wavefronts are done with the first, rougher test (a
+    // single query's box is its sphere's).
     uint32_t scattered = 0;
-    for (int tb = 0; tb < a.ntypes; ++tb) {
+    for (int tb = 0; tb < (nq > 1 ? a.ntypes : 0); ++tb) {
         const TreeMeta &m = meta[tb];
         const double r2 = a.rlist2[ta * QBVH_MAX_TYPES + tb];
         if (m.count == 0 || !(r2 >= 0.0)) continue;
