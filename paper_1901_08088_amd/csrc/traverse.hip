@@ -104,6 +104,13 @@ constexpr int kSegs = 2;
 // 1% vapour 199 -> 294 us).
 constexpr float kSphereCost = 1.0f / 40.0f;
 constexpr float kSphereRounds = 8.0f;
+// A tree that cannot tell its particles apart (many more of them in a Morton bin
+// than the spheres hold) is searched whole by spheres too, so they are given up
+// for it after this many rounds in a row in which they miss no more than an eighth
+// of the nodes: 500k particles, most of them outside the box and
+// so in its first bin, 60 -> 12 ms (boxes only 11.6).  12 rounds give
+// them up too early (1M particles in 40 clusters 2.74 -> 3.09 ms).
+constexpr int32_t kPatience = 16;
 // Queries in places far apart.  The band of pairs that the products leave to the
 // exact test grows with the square of the wavefront's extent (see pair_band): at
 // a gap of 512 R between two queries it holds 37% of R^2, from about 850 R all.
@@ -986,6 +993,9 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
         const float gLx = uniform((float)(a.L[0] * ih)), gLy = uniform((float)(a.L[1] * ih)),
                     gLz = uniform((float)(a.L[2] * ih));
         const int32_t end = m.end;
+        // rounds that the spheres may go without a gain (see kPatience)
+        int32_t patience = by_sphere ? kPatience : 0;
+
         // every image's root, the first image on top
         if (lane < 27u) {
             const uint32_t img = lane % 3u | ((lane / 3u) % 3u) << 2 | (lane / 9u) << 4;
@@ -1033,7 +1043,7 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
                 hz -= tz;
             }
             float best = __builtin_inff();
-            if (by_sphere) {
+            if (patience > 0) {
                 // (the lanes past the queries repeat the last one)
                 const float4 own = sorted[q.k];
                 float ux, uy, uz;
@@ -1055,6 +1065,8 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
                         best = fminf(best, __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx)));
                     }
                 }
+                const uint64_t opened = A & ~R0, missed = opened & __ballot(!(best <= r2g));
+                patience = 8 * __popcll(missed) > __popcll(opened) ? kPatience : patience - 1;
             } else {
 #pragma unroll
                 for (int s = 0; s < kSegs; ++s) {
