@@ -136,6 +136,11 @@ constexpr int kOpen = 32;
 constexpr int kDepthMax = 64;
 constexpr int kStack = 160;
 static_assert(kStack - kDepthMax >= 27 + kOpen, "room for every image's root");
+// The square of a distance that nothing listed has: what an empty slot's or an
+// idle lane's products start from.  Above every |q|^2, R^2 and band of boxes whose
+// edges are below 1e17 (to larger ones, and to wavefronts as wide, the products do
+// not apply), and low enough that its sum with any |c|^2 below 1e37 is finite.
+constexpr float kFar = 1e36f;
 // Queue of run parts: parts of fewer than 64 particles in all wait when a
 // round adds those of at most 2 kOpen runs, two parts each.
 constexpr int kParts = 64 + 4 * kOpen;
@@ -535,7 +540,7 @@ __device__ __forceinline__ bool stage_batch(Args &a, const Batch &t, uint32_t ta
     c[3] = __builtin_fmaf(c[2], c[2], __builtin_fmaf(c[1], c[1], c[0] * c[0]));
     if (!on || !(c[3] < 1e37f)) {  // (not a number: the sign of such a product would mean nothing)
         c[0] = c[1] = c[2] = 0.0f;
-        c[3] = 1e30f;
+        c[3] = kFar;
     }
     w.index[table * 64u + slot] = ~__float_as_int(t.p.w);
     // a query's own particle is never listed: it can only come up unshifted
@@ -864,7 +869,7 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
                 oy = uniform(0.5f * (fminf(wlo[0][1], wlo[1][1]) + fmaxf(whi[0][1], whi[1][1]))),
                 oz = uniform(0.5f * (fminf(wlo[0][2], wlo[1][2]) + fmaxf(whi[0][2], whi[1][2])));
     // Idle lanes take the origin itself: with their constant (c0 below) every
-    // product of theirs is 1e30 + |c|^2, positive whatever the coordinates (the
+    // product of theirs is kFar + |c|^2, positive whatever the coordinates (the
     // candidates' are finite), so none of their bits is ever set and the row
     // that they share with the last query is its own.
     const float rx = valid ? qp.x - ox : 0.0f, ry = valid ? qp.y - oy : 0.0f, rz = valid ? qp.z - oz : 0.0f;
@@ -963,9 +968,9 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
             tt.band_img =
                 uniform(pair_band(R, rin, rout, 1.7320508075688772 * 0x1p-22 * (2.0 * a.lmax + 2.0 * R), e_o, M));
         }
-        // (squares of such coordinates would overflow)
-        tt.force = !(M2 < 1e28f) || !(a.lmax < 1e14);
-        const float c0 = valid ? q2 - (float)mid : 1e30f;
+        // (squares of such coordinates come near kFar or overflow)
+        tt.force = !(M2 < kFar * 1e-2f) || !(a.lmax < 1e17);
+        const float c0 = valid ? q2 - (float)mid : kFar;
         float cq[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) cq[g] = __shfl(c0, 16 * g + (int)(lane & 15u));
