@@ -288,8 +288,7 @@ int nlist_build_grid(qgrid_t **grid, const float *d_pos, int32_t n, const float 
     hipLaunchKernelGGL(qbi::k_grid_clear_flag, dim3(1), dim3(64), 0, s, d_overflow);
     if (n > 0) {
         hipLaunchKernelGGL(qbi::k_cell_key, qbi::blocks_for(n), dim3(qbi::kGridThreads), 0, s, d_pos, n, g, G->keys);
-        hipError_t e = qbi::launch_radix_sort(G->keys, G->vals, G->keys2, G->vals2, G->hist, G->digit_total, n,
-                                              qbi::radix_tiles(n), s);
+        hipError_t e = qbi::launch_radix_sort(G->keys, G->vals, G->keys2, G->vals2, G->hist, G->digit_total, n, s);
         if (e != hipSuccess) return qbi::hip_fail(e);
         hipLaunchKernelGGL(qbi::k_cell_clear, qbi::blocks_for(ncells), dim3(qbi::kGridThreads), 0, s, G->cell_start,
                            G->cell_end, ncells);

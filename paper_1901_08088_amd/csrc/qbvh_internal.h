@@ -45,12 +45,11 @@ constexpr int32_t kSpare = 16;
 // Device workspace of one built tree (all arrays sized for `cap` particles).
 struct Workspace {
     int32_t cap = 0;
-    int32_t tiles = 0;        // radix-sort tiles for cap
     void *base = nullptr;     // single hipMalloc allocation
     size_t bytes = 0;
     uint32_t *keys = nullptr, *vals = nullptr;
     uint32_t *keys2 = nullptr, *vals2 = nullptr;  // sort ping-pong
-    uint32_t *hist = nullptr;       // [256][tiles]
+    uint32_t *hist = nullptr;       // [256][radix_tiles(cap)]
     uint32_t *digit_total = nullptr;// [256]
     float4 *sorted = nullptr;       // [cap]
     int32_t *left = nullptr, *right = nullptr, *rf = nullptr, *rl = nullptr;
@@ -93,7 +92,7 @@ struct TravArgs {
     int32_t ntypes;
     int32_t max_nbr;
     int32_t start;    // first sorted position of this system (0 for a single system)
-    int32_t qpw;      // queries per wavefront (64, or 32/16/8 for small systems)
+    int32_t qpw;      // queries per wavefront: a power of 2 from 1 to 64
     int32_t qbits;    // grid bits of the tree (paper-mode cell boxes)
 };
 
@@ -177,9 +176,6 @@ hipError_t launch_build(const Workspace &w, const float *d_pos, const int32_t *d
 // `cleared`: the overflow flag is 0 already.
 hipError_t launch_traverse(const TravArgs &a, int32_t block, bool vec4, bool paper, const uint4 *qpoint, bool cleared,
                            hipStream_t s);
-// fp64 particle data: the positions rounded to fp32 for the build (with the
-// fp64 range and type checks when validate is set), and after the build the
-// fp64 positions in sorted order.
 // Paper-mode cell boxes; lmax is the largest periodic box edge (the extent floor is lmax 2^-24).
 hipError_t launch_qpoint(const Workspace &w, int32_t n, int32_t ntypes, int32_t qbits, double lmax, hipStream_t s);
 hipError_t launch_traverse_batch(const BatchLaunch &b, hipStream_t s);
@@ -190,8 +186,7 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t s);
 // Stable sort of keys[0, n); vals receives each sorted key's input position
 // (the caller writes only the keys).
 hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, uint32_t *vals2,
-                             uint32_t *hist, uint32_t *digit_total, int32_t n, int32_t tiles,
-                             hipStream_t s);
+                             uint32_t *hist, uint32_t *digit_total, int32_t n, hipStream_t s);
 hipError_t launch_exclusive_scan(uint32_t *data, int32_t len, uint32_t *partials, hipStream_t s);
 struct Collapse;
 // Where the tree build takes its particles and tree boundaries from: a single
