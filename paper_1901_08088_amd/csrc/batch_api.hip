@@ -3,7 +3,8 @@
 //
 // A batch shape is the list of (n, ntypes) of its systems plus whether every
 // system's rows take 16-byte stores.  Per shape the library keeps the
-// autotuner's measurements and one captured graph per configuration tried.
+// autotuner's measurements and one captured graph per configuration tried and
+// kind of traversal (with or without parts, see wide_box).
 // Everything that may change between calls of one shape (input and output
 // pointers, boxes, cutoffs, row capacities) lives in a device table that the
 // graph's kernels read, so a replay only needs the table re-uploaded when its
