@@ -107,9 +107,9 @@ constexpr float kSphereRounds = 8.0f;
 // A tree that cannot tell its particles apart (many more of them in a Morton bin
 // than the spheres hold) is searched whole by spheres too, so they are given up
 // for it after this many rounds in a row in which they miss no more than an eighth
-// of the nodes: 500k particles, most of them outside the box and
-// so in its first bin, 60 -> 12 ms (boxes only 11.6).  12 rounds give
-// them up too early (1M particles in 40 clusters 2.74 -> 3.09 ms).
+// of the nodes: 500k particles, most of them outside the box and so in its first
+// bin, 60 -> 12 ms (boxes only 11.6).  12 rounds give them up too early (1M
+// particles in 40 clusters 2.74 -> 3.09 ms).
 constexpr int32_t kPatience = 16;
 // Queries in places far apart.  The band of pairs that the products leave to the
 // exact test grows with the square of the wavefront's extent (see pair_band): at
@@ -824,11 +824,10 @@ __device__ __forceinline__ void traverse_wave(Args &a, int32_t li, const uint4 *
             return;
         }
         const int from = (int)__builtin_ctzll(finite);
-        if (!lane_bit(finite)) {
-            qp.x = lane_value(qp.x, from);
-            qp.y = lane_value(qp.y, from);
-            qp.z = lane_value(qp.z, from);
-        }
+        const float x = lane_value(qp.x, from), y = lane_value(qp.y, from), z = lane_value(qp.z, from);
+        qp.x = lane_bit(finite) ? qp.x : x;
+        qp.y = lane_bit(finite) ? qp.y : y;
+        qp.z = lane_bit(finite) ? qp.z : z;
     }
     q.valid = valid;
     if (kFew) {  // the queries' four lanes each
