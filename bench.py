@@ -82,9 +82,9 @@ def log(msg: str) -> None:
 def traversal_bytes(n: int, nrecords: int, stored_pairs: int) -> int:
     """Algorithmic HBM bytes of one traversal launch: the Z-ordered particle
     array (16 B per particle, queries and candidates alike) read once, every
-    record (32 B) and its rope (4 B) read once, every stored neighbor index
-    (4 B) and every count (4 B) written once."""
-    return 16 * n + 36 * nrecords + 4 * stored_pairs + 4 * n
+    record (32 B) read once, every stored neighbor index (4 B) and every count
+    (4 B) written once."""
+    return 16 * n + 32 * nrecords + 4 * stored_pairs + 4 * n
 
 
 def host_info() -> dict:
@@ -166,9 +166,9 @@ def band_report(cfg, queries=None, threads: int = 0) -> dict:
 # factor the same counters read for a plain elementwise copy of known size (the
 # --copy-probe-mib kernel).  Valid only for the kernel sources it was taken on:
 # ``traffic`` is reported as null once their hash differs.
-TRAFFIC = {"sources": "a0ce59fc43337ced", "workload": "lj8m",
+TRAFFIC = {"sources": "93f283f85ae8cbd7", "workload": "lj8m",
            "opts": {"leaf_size": 16, "qbits": 16, "block_size": 64},
-           "fetch_kib": 492221.0, "write_kib": 5681606.0, "copy_factor": 1.0,
+           "fetch_kib": 480173.0, "write_kib": 5655427.0, "copy_factor": 1.0,
            # FETCH_SIZE per byte read: 0.500 for vector loads (the copy probe; the kernel's
            # nodes, particles and queries), 1.000 for scalar loads
            # (profiles/fetch_size_calibration.md)
