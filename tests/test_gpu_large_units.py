@@ -29,7 +29,7 @@ def test_rows(L, qpw):
 
 
 def test_time():
-    # (twice as long when all pairs go to the exact test)
+    # (six times as long when all pairs go to the exact test)
     torch = require_gpu()
     best = []
     for L in (100.0, 1e15):

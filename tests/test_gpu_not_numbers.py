@@ -82,7 +82,7 @@ def test_paper_mode_queries(qpw):
 
 
 def test_time_beside_them():
-    # (three hundred times as long when such a query searches the whole system)
+    # (more than a thousand times as long when such a query searches the whole system)
     torch = require_gpu()
     best = []
     for bad in (np.zeros(0, int), np.arange(7, 20001, 4000)):
